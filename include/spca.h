@@ -344,8 +344,12 @@ const char* spca_last_error(void);
 /* ---------------------------------------------------------------------- */
 /* Building blocks of one AM iteration, exported for testing and tuning.   */
 
-/* C = P * Q^T in FP32 with FP32 MFMA accumulation (the two products of an
- * AM iteration, Section 4: U^T = X^T A^T and V^T = Y^T A).  P is M x K,
+/* C = P * Q^T in FP32 with FP32 accumulation (the two products of an AM
+ * iteration, Section 4: U^T = X^T A^T and V^T = Y^T A).  From K = 192 on the
+ * product runs, where that is faster, on BF16 matrix instructions over three
+ * BF16 parts of each operand, whose sum is the FP32 value: errors no larger
+ * than those of the FP32 instructions, infinities, NaN and tiny operands as
+ * those treat them.  P is M x K,
  * Q is N x K, C is M x N, all row-major in device memory with leading
  * dimensions ldp, ldq >= K and ldc >= N.  ldp and ldq must be multiples of
  * 4 and P, Q 16-byte aligned (SPCA_EINVAL otherwise).                    */
@@ -377,7 +381,7 @@ int spca_gemm_nt_f32_shape(void* stream, const float* P, int64_t ldp,
                            int64_t M, int64_t N, int64_t K, int shape,
                            int splits);
 
-/* The tile shape and K split the library picks for an M x N x K product
+/* The FP32 tile shape and K split the library picks for an M x N x K product
  * (deterministic, from a model of CU occupancy and tile efficiency).     */
 /* Tuning table of the product tiles: one line per entry,
  *   "elem_bytes max_splits bucket(M) bucket(N) bucket(K) shape splits"
@@ -387,7 +391,11 @@ int spca_gemm_nt_f32_shape(void* stream, const float* P, int64_t ldp,
  * import adds (or replaces) entries from such text (EINVAL on a malformed
  * line, and then nothing is imported); clear removes every entry.  Plans
  * (spca_gemm_nt_f32_plan and the solves) use an entry of their bucket
- * before the cost model.  Host-only: no device is touched.                */
+ * before the cost model.  Shapes 64 to 71 (elem_bytes 4) are the tiles on
+ * BF16 parts: they hold for spca_gemm_nt_f32 and for the iterations of a
+ * solve that may use such tiles (from the 33rd on, without total_starts >
+ * r); a solve's earlier iterations stay on FP32 tiles, whose entries hold
+ * for them.  Host-only: no device is touched.                             */
 int spca_tune_table_export(char* buf, size_t cap, size_t* len);
 int spca_tune_table_import(const char* text);
 int spca_tune_table_clear(void);

@@ -327,37 +327,6 @@ __global__ __launch_bounds__(WM* WN* kWave, DEPTH == 2 ? 3 : 1) void gemm_nt_ker
                                M, N, tm * BM, tn * BN, kbeg, kend, lds);
 }
 
-// Grouped products: one launch over the tiles of several independent
-// products (GemmGroupDesc), each tile owned by the product whose tile range
-// holds its block index.  The products of a request none of whose starts
-// still runs (running[req] == 0) are skipped.
-template <int BM, int BN, int WM, int WN>
-__global__ __launch_bounds__(WM* WN* kWave) void gemm_group_kernel(
-    const GemmGroupDesc* __restrict__ d, int count, const int32_t* __restrict__ running) {
-  using Cfg = GemmCfg<BM, BN, WM, WN>;
-  constexpr int SK = kChunks * Elem<float>::kPerChunk;
-  __shared__ __attribute__((aligned(16))) float lds[2 * Cfg::kStage];
-  const int b = blockIdx.x;
-  // the last product whose first tile is at or below b (tile0 ascending)
-  int lo = 0, hi = count - 1;
-  while (lo < hi) {
-    const int mid = (lo + hi + 1) / 2;
-    if (d[mid].tile0 <= b) lo = mid; else hi = mid - 1;
-  }
-  const GemmGroupDesc g = d[lo];
-  if (running != nullptr && running[g.req] == 0) return;
-  const int local = b - g.tile0;
-  const int split = local % g.splits;
-  const int t = local / g.splits;
-  const int tm = t % g.tiles_m;
-  const int tn = t / g.tiles_m;
-  const int kbeg = split * g.kslabs_per_split * SK;
-  int kend = kbeg + g.kslabs_per_split * SK;
-  kend = kend < g.K ? kend : g.K;
-  gemm_tile<float, BM, BN, WM, WN>(g.P, g.ldp, g.Q, g.ldq, g.C + (int64_t)split * g.split_stride,
-                                   g.ldc, g.M, g.N, tm * BM, tn * BN, kbeg, kend, lds);
-}
-
 // Compiled tile shapes.  occ = workgroups a CU holds at once (LDS and
 // registers); eff = relative MFMA efficiency of the shape measured on
 // MI355X (larger per-wave tiles reuse each LDS read for more MFMAs); eff16
@@ -481,6 +450,11 @@ std::mutex g_tune_mu;
 std::map<TuneKey, GemmPlan> g_tune;
 
 int bucket(int64_t x) { return (int)std::lround(2.0 * std::log2((double)(x > 0 ? x : 1))); }
+// a compiled FP32 / BF16 tile, or (FP32 only) a BF16-part tile
+bool shape_known(int shape, int eb) {
+  return (shape >= 0 && shape < kNumShapes) ||
+         (eb == 4 && shape >= kSplitShape0 && shape < kSplitShape0 + gemm_num_split_shapes());
+}
 TuneKey key_of(int64_t M, int64_t N, int64_t K, int ms, int eb) {
   return TuneKey{eb, ms, bucket(M), bucket(N), bucket(K)};
 }
@@ -522,8 +496,8 @@ bool tune_table_load(const char* text, std::string* err) {
     TuneKey k;
     GemmPlan g;
     if (!(ls >> k.eb >> k.ms >> k.bm >> k.bn >> k.bk >> g.shape >> g.splits) ||
-        (k.eb != 2 && k.eb != 4) || g.shape < 0 || g.shape >= gemm_num_shapes() ||
-        g.splits < 1 || g.splits > k.ms) {
+        (k.eb != 2 && k.eb != 4) || !shape_known(g.shape, k.eb) || g.splits < 1 ||
+        g.splits > k.ms) {
       *err = "bad tuning entry on line " + std::to_string(ln);
       return false;
     }
@@ -562,8 +536,64 @@ GemmPlan plan_gemm_nt(int64_t M, int64_t N, int64_t K, int max_splits,
   return model_plan_gemm_nt(M, N, K, max_splits, elem_bytes);
 }
 
+namespace {
+// modelled time of a plan of model_plan_gemm_nt: its cycles take 1.2 times as
+// long as at 2.4 GHz, plus the launch
+double f32_model_us(double cycles) { return cycles * 1.2 / 2400.0 + 3.0; }
+}  // namespace
+
+GemmPlan plan_f32(int64_t M, int64_t N, int64_t K, int max_splits, double* us_out) {
+  GemmPlan t;
+  if (us_out != nullptr) *us_out = 0.0;
+  if (tuned_plan(M, N, K, max_splits, 4, &t) && t.shape < kStreamShape0)
+    return plan_gemm_nt(M, N, K, max_splits, 4);
+  double cycles = 0.0, stream_us = 0.0;
+  GemmPlan g = model_plan_gemm_nt(M, N, K, max_splits, 4, &cycles);
+  double us = f32_model_us(cycles);
+  // One-wave tiles where few tiles and a long K loop leave the workgroup
+  // tiles waiting for memory: 64 x 2000 x 2500 86 to 29 us, 16 x 300 x 750 29
+  // to 8 us, 1024 x 1000 x 1250 54 to 38 us.  Where the matrix cores are
+  // busy the workgroup tiles are as fast (64 x 20000 x 1000: 56 and 50 us),
+  // hence the margin.
+  const int v = model_stream(M, N, K, g.splits, &stream_us);
+  if (stream_us < 0.85 * us) {
+    us = stream_us;
+    g.shape = kStreamShape0 + v;
+  }
+  if (us_out != nullptr) *us_out = us;
+  return g;
+}
+
+GemmPlan plan_product_f32(int64_t M, int64_t N, int64_t K, int max_splits, int64_t ldp,
+                          int64_t ldq, bool signs, int fixed_splits, double* us_out) {
+  const bool split = split_possible(K, ldp, ldq);
+  GemmPlan t;
+  if (us_out != nullptr) *us_out = 0.0;
+  if (tuned_plan(M, N, K, max_splits, 4, &t)) {
+    const bool parts = t.shape >= kSplitShape0;
+    // an entry covers a size bucket, in which K may be too small for it
+    if (parts && !split) return model_plan_gemm_nt(M, N, K, max_splits, 4);
+    t = plan_gemm_nt(M, N, K, max_splits, 4);
+    if (fixed_splits > 0) t.splits = fixed_splits;
+    return t;
+  }
+  // Both models in microseconds.  The FP32 tiles stay ahead only where K is
+  // short and the large tiles are mostly padding: 300 x 45359 x 240 takes 83
+  // us on them and 91 us on BF16 parts; over 60 sizes with 16 to 1024 rows,
+  // K from 200 to 50000, the parts are 1.03 to 20 times faster otherwise.
+  double us = 0.0, parts_us = 0.0;
+  const GemmPlan f32 = plan_f32(M, N, K, max_splits, &us);
+  if (us_out != nullptr) *us_out = us;
+  if (!split) return f32;
+  const GemmPlan parts =
+      model_plan_split(M, N, K, max_splits, signs, fixed_splits, &parts_us);
+  if (parts_us + 3.0 >= us) return f32;
+  if (us_out != nullptr) *us_out = parts_us + 3.0;
+  return parts;
+}
+
 GemmPlan model_plan_gemm_nt(int64_t M, int64_t N, int64_t K, int max_splits,
-                            int elem_bytes) {
+                            int elem_bytes, double* cycles_out) {
   GemmPlan best{0, 1};
   double best_cost = 1e300;
   const int64_t slab_k = 128 / elem_bytes;
@@ -597,19 +627,29 @@ GemmPlan model_plan_gemm_nt(int64_t M, int64_t N, int64_t K, int max_splits,
       }
     }
   }
+  if (cycles_out != nullptr) *cycles_out = best_cost;
   return best;
 }
 
 int gemm_num_shapes() { return kNumShapes; }
 int gemm_shape_bm(int shape) {
+  if (shape >= kSplitShape0) return split_shape_bm(shape);
   return shape >= 0 && shape < kNumShapes ? kShapes[shape].bm : 0;
 }
 
 void gemm_nt_f32(hipStream_t st, const float* P, int64_t ldp, const float* Q,
                  int64_t ldq, float* C, int64_t ldc, int64_t M, int64_t N,
                  int64_t K, const int32_t* gate, int32_t gate_run,
-                 GemmPlan plan, int64_t split_stride, const int32_t* kdev) {
+                 GemmPlan plan, int64_t split_stride, const int32_t* kdev, bool signs) {
   if (M <= 0 || N <= 0) return;
+  if (plan.shape >= kSplitShape0) {
+    gemm_nt_split(st, P, ldp, Q, ldq, C, ldc, M, N, K, gate, gate_run, plan, split_stride, signs);
+    return;
+  }
+  if (plan.shape >= kStreamShape0) {
+    gemm_nt_stream(st, P, ldp, Q, ldq, C, ldc, M, N, K, gate, gate_run, plan, split_stride);
+    return;
+  }
   if (kdev != nullptr) plan.splits = 1;
   dispatch<float>(plan.shape, st, P, ldp, Q, ldq, C, ldc, M, N, K, plan.splits,
                   split_stride, gate, gate_run, kdev);
@@ -622,28 +662,6 @@ void gemm_nt_bf16(hipStream_t st, const uint16_t* P, int64_t ldp,
   if (M <= 0 || N <= 0) return;
   dispatch<uint16_t>(plan.shape, st, P, ldp, Q, ldq, C, ldc, M, N, K,
                      plan.splits, split_stride, gate, gate_run, nullptr);
-}
-
-void gemm_group_tiles(GemmGroupDesc* d, int count, int* total_tiles) {
-  int t = 0;
-  for (int q = 0; q < count; ++q) {
-    d[q].tiles_m = (int32_t)ceil_div((int64_t)d[q].M, (int64_t)kGroupBM);
-    const int tiles_n = (int)ceil_div((int64_t)d[q].N, (int64_t)kGroupBN);
-    const int kslabs = (int)ceil_div((int64_t)d[q].K, (int64_t)kChunks * 4);
-    if (d[q].splits < 1) d[q].splits = 1;
-    d[q].kslabs_per_split = (int32_t)ceil_div((int64_t)kslabs, (int64_t)d[q].splits);
-    d[q].tile0 = t;
-    t += d[q].tiles_m * tiles_n * d[q].splits;
-  }
-  *total_tiles = t;
-}
-
-void gemm_nt_f32_group(hipStream_t st, const GemmGroupDesc* d_dev, int count, int total_tiles,
-                       const int32_t* running) {
-  if (count <= 0 || total_tiles <= 0) return;
-  static_assert(kGroupBM == 64 && kGroupBN == 128, "group tile shape");
-  hipLaunchKernelGGL((gemm_group_kernel<64, 128, 2, 2>), dim3((unsigned)total_tiles),
-                     dim3(4 * kWave), 0, st, d_dev, count, running);
 }
 
 }  // namespace spca

@@ -1,0 +1,820 @@
+// FP32 products on the BF16 matrix cores: C = P * Q^T with FP32 operands,
+// each operand split on the fly into three BF16 parts whose sum is the FP32
+// value exactly (8 significant bits each, round to nearest),
+//   x = h + m + l,  h = bf16(x),  m = bf16(x - h),  l = bf16(x - h - m),
+// and the products h h', h m', m h', m m', h l', l h' accumulated in FP32.
+// The three left out (m l', l m', l l') are below 2^-24 of the product, the
+// size of one FP32 rounding; a sum of K terms is rounded once or twice per 32
+// K instead of once per term, so that the error against FP64 is below that of
+// the FP32 matrix instructions (normwise, unit Gaussian rows, K = 1000: 2.1e-7
+// and 1.6e-7 for the two kernels below, FP32 MFMA 5.7e-7; with 5% of P
+// nonzero 1.3e-7, 1.0e-7 and 1.3e-7).  The BF16 rate is 16 times the FP32 one
+// (2.5 PFLOP/s against 157 TFLOP/s), so six products cost 3/8 of the FP32
+// ones.  When P holds signs (y = sgn(u): 0 and +-1 are BF16 numbers) three
+// products do.
+//
+// Range.  Sums that overflow, hold an infinity or NaN, or lie so low that
+// parts of an operand fall under the BF16 or FP32 range are recomputed with
+// FP32 MFMAs straight from global memory (redo, below): infinities and NaN
+// come out as the FP32 instructions give them, and operands down to the
+// denormals keep their FP32 accuracy.
+//
+// split_pp_kernel, large tiles (256 x 160 or 256 x 128 per workgroup of 8
+// waves, 64 x 80 or 64 x 64 per wave): both operands staged through LDS as
+// BF16 parts in MFMA fragment order, two stages of 32 K.  The two waves of a
+// SIMD work in turns (an s_barrier per half step): while one issues its 120
+// MFMAs from registers, converting its share of a later slab between them,
+// the other writes converted parts to LDS and reads its next fragments.
+// Bound: the matrix cores, at the clock that the chip's power allows (1.9
+// GHz here: at full rate on random operands they settle there whatever feeds
+// them).  1024 x 10000 x 1000: 107 us (FP32 MFMA 180 us); of that 7 us go to
+// the separate small sums; without the turns (one barrier per slab) 112 us
+// where this form took 100, with 32 x 32 MFMAs 119-123 us.
+//
+// split_ks_kernel, small tiles (16 FM x 16 FN) of which the waves of a
+// workgroup share K: wave w takes the slabs w, w + waves, ..., loads them
+// into an LDS slab of its own (coalesced, global to LDS), converts them in
+// fragment order and multiplies, with no barrier in the loop; the partial
+// tiles are summed in wave order at the end.  Bound: the conversions
+// (6 vector instructions per operand element).  Used where large tiles leave
+// CUs idle: 1024 x 1000 x 10000 137 us (FP32 MFMA 401 us), 64 x 2000 x 20000
+// 95 us (770 us), 16 x 300 x 1500 10 us (55 us).
+#include <algorithm>
+#include <cmath>
+
+#include "common.hpp"
+#include "kernels.hpp"
+
+namespace spca {
+namespace {
+
+typedef float fx4 __attribute__((ext_vector_type(4)));
+typedef float fx2 __attribute__((ext_vector_type(2)));
+typedef __bf16 bf8 __attribute__((ext_vector_type(8)));
+typedef __bf16 bf2 __attribute__((ext_vector_type(2)));
+typedef uint32_t ux2 __attribute__((ext_vector_type(2)));
+typedef uint32_t ux4 __attribute__((ext_vector_type(4)));
+
+constexpr int kSlab = 32;  // K per slab: one 16x16x32 MFMA deep
+static_assert(kSplitMinK >= kSlab, "split_pp_kernel may load the first slab of any row");
+
+__device__ __forceinline__ uint32_t pack_bf16(float a, float b) {
+  const fx2 v = {a, b};
+  return __builtin_bit_cast(uint32_t, __builtin_convertvector(v, bf2));
+}
+__device__ __forceinline__ float low_of(uint32_t h) { return __uint_as_float(h << 16); }
+__device__ __forceinline__ float high_of(uint32_t h) { return __uint_as_float(h & 0xffff0000u); }
+
+// The BF16 parts of four consecutive FP32 values (NP = 1: the first only);
+// amax gathers the largest magnitude.
+template <int NP>
+__device__ __forceinline__ void split4(fx4 x, ux2 (&w)[NP], float& amax) {
+  amax = fmaxf(fmaxf(amax, fabsf(x.x)), fabsf(x.y));
+  amax = fmaxf(fmaxf(amax, fabsf(x.z)), fabsf(x.w));
+  uint32_t a = pack_bf16(x.x, x.y), b = pack_bf16(x.z, x.w);
+  w[0] = ux2{a, b};
+  if constexpr (NP == 3) {
+    const float r0 = x.x - low_of(a), r1 = x.y - high_of(a);
+    const float r2 = x.z - low_of(b), r3 = x.w - high_of(b);
+    a = pack_bf16(r0, r1);
+    b = pack_bf16(r2, r3);
+    w[1] = ux2{a, b};
+    w[2] = ux2{pack_bf16(r0 - low_of(a), r1 - high_of(a)),
+               pack_bf16(r2 - low_of(b), r3 - high_of(b))};
+  }
+}
+
+// Four consecutive values of a row from K position k (zero from kend on).
+__device__ __forceinline__ fx4 load_tail(const float* s, int k, int kend) {
+  fx4 r = {0.f, 0.f, 0.f, 0.f};
+  if (k + 3 < kend) {
+    r = *reinterpret_cast<const fx4*>(s);
+  } else {
+    if (k < kend) r.x = s[0];
+    if (k + 1 < kend) r.y = s[1];
+    if (k + 2 < kend) r.z = s[2];
+  }
+  return r;
+}
+
+// the part products of one block column, smallest terms first: all but h h'
+// into small[i], h h' into acc[i] (the two may be the same)
+template <int FM, int NP>
+__device__ __forceinline__ void mfma_parts(const bf8 (&q)[3], const bf8 (&p)[FM][NP],
+                                           fx4 (&small)[FM], fx4 (&acc)[FM]) {
+  auto mm = [&](int a, int b, fx4 (&c)[FM]) {
+#pragma unroll
+    for (int i = 0; i < FM; ++i)
+      c[i] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(q[b], p[i][a], c[i], 0, 0, 0);
+  };
+  if constexpr (NP == 1) {
+    mm(0, 2, small);
+    mm(0, 1, small);
+    mm(0, 0, acc);
+  } else {
+    mm(0, 2, small);
+    mm(2, 0, small);
+    mm(1, 1, small);
+    mm(0, 1, small);
+    mm(1, 0, small);
+    mm(0, 0, acc);
+  }
+}
+
+// Whether a sum may have lost accuracy to the range of the parts.  With
+// K <= 2^31 terms, B the largest magnitude of the operands in the tile:
+// parts under 2^-133 lose at most 2^-134 B per term and products under
+// 2^-126 at most their own size, so sums of at least 2^-80 (1 + B) keep
+// FP32 accuracy for K up to 2^20, and so do exact zeros of operands that
+// are not themselves tiny.  Overflow, infinities and NaN show as a sum that
+// is not finite.
+__device__ __forceinline__ bool suspect(float s, float amax_p, float amax_q) {
+  const float a = fabsf(s);
+  const float floor_ = 0x1p-80f * (1.f + fmaxf(amax_p, amax_q));
+  if (!(a <= 3.4028234e38f)) return true;
+  if (a == 0.f)
+    return (amax_p > 0.f && amax_p < 0x1p-80f) || (amax_q > 0.f && amax_q < 0x1p-80f);
+  return a < floor_;
+}
+
+// FP32 MFMAs straight from global memory: the 16 x 16 block (C layout of the
+// 16x16 MFMAs) of rows m0.. of P and n0.. of Q over [kbeg, kend).  Rows past
+// the end repeat the last one.  K enters in the order of gemm_nt_kernel (8 at
+// a time: 0 4, 1 5, 2 6, 3 7), so that sums which overflow end the same way.
+__device__ __forceinline__ fx4 f32_block(const float* __restrict__ P, int64_t ldp,
+                                         const float* __restrict__ Q, int64_t ldq, int M, int N,
+                                         int m0, int n0, int kbeg, int kend) {
+  const int lane = threadIdx.x % kWave, lr = lane % 16, lc = lane / 16;
+  const float* p = P + (int64_t)(m0 + lr < M ? m0 + lr : M - 1) * ldp;
+  const float* q = Q + (int64_t)(n0 + lr < N ? n0 + lr : N - 1) * ldq;
+  fx4 c = {0.f, 0.f, 0.f, 0.f};
+  const int ko = (lc >> 1) + 4 * (lc & 1);
+#pragma unroll 1
+  for (int k8 = kbeg; k8 < kend; k8 += 8) {
+#pragma unroll
+    for (int k = k8 + ko, h = 0; h < 2; ++h, k += 2) {
+      const bool in = k < kend;
+      const float a = in ? q[k] : 0.f, b = in ? p[k] : 0.f;
+      c = __builtin_amdgcn_mfma_f32_16x16x4f32(a, b, c, 0, 0, 0);
+    }
+  }
+  return c;
+}
+
+// Four consecutive columns of C (16-byte aligned)
+__device__ __forceinline__ void store_cols(float* c, int col, int N, fx4 v) {
+  if (col + 3 < N) {
+    *reinterpret_cast<fx4*>(c) = v;
+  } else {
+#pragma unroll
+    for (int e = 0; e < 3; ++e)
+      if (col + e < N) c[e] = v[e];
+  }
+}
+
+__device__ __forceinline__ float wave_max(float x) {
+#pragma unroll
+  for (int o = kWave / 2; o > 0; o >>= 1) x = fmaxf(x, __shfl_xor(x, o, kWave));
+  return x;
+}
+
+// Block -> (tile, split) as in gemm_nt_kernel: unsplit, runs of consecutive
+// tiles stay on one XCD (blocks are dealt to the 8 XCDs in turn); split, the
+// split index is fastest.
+__device__ __forceinline__ void tile_of(int b, int splits, int tiles_mn, int* tile, int* split) {
+  if (splits == 1) {
+    const int per_xcd = tiles_mn / 8;
+    if (b < per_xcd * 8) b = (b % 8) * per_xcd + b / 8;
+  }
+  *split = b % splits;
+  *tile = b / splits;
+}
+
+// ---------------------------------------------------------------------------
+// Large tiles
+// ---------------------------------------------------------------------------
+
+template <int BM, int BN, int WM, int WN, int NP>
+__global__ __launch_bounds__(WM* WN* kWave, 2) void split_pp_kernel(
+    const float* __restrict__ P, int64_t ldp, const float* __restrict__ Q, int64_t ldq,
+    float* __restrict__ C, int64_t ldc, int M, int N, int K, int tiles_m, int tiles_mn,
+    int splits, int kslabs_per_split, int64_t split_stride, const int32_t* __restrict__ gate,
+    int32_t gate_run) {
+  constexpr int NT = WM * WN * kWave;
+  constexpr int TM = BM / WM, TN = BN / WN, FM = TM / 16, FN = TN / 16;
+  constexpr int RPV = NT / 8;  // rows per load round (8 lanes of 16 bytes a row)
+  constexpr int VP = BM / RPV, VQ = (BN + RPV - 1) / RPV, VN = VP + VQ;
+  constexpr int kPBytes = BM / 16 * NP * 1024;
+  constexpr int kStage = kPBytes + BN / 16 * 3 * 1024;
+  static_assert(BM % RPV == 0 && TM % 16 == 0 && TN % 16 == 0, "tile split");
+  __shared__ __attribute__((aligned(16))) char lds[2 * kStage];
+  if (gate != nullptr && *gate != gate_run) return;
+
+  int tile, split;
+  tile_of(blockIdx.x, splits, tiles_mn, &tile, &split);
+  const int m0 = (tile % tiles_m) * BM, n0 = (tile / tiles_m) * BN;
+  const int kbeg = split * kslabs_per_split * kSlab;
+  int kend = kbeg + kslabs_per_split * kSlab;
+  kend = kend < K ? kend : K;
+  // slabs: a partial one (K not a multiple of 32) goes first, where the
+  // loop's loads need no guard for it
+  const int nfull = kend > kbeg ? (kend - kbeg) / kSlab : 0;
+  const int part = kend > kbeg && (kend - kbeg) % kSlab != 0 ? 1 : 0;
+  const int nslabs = nfull + part;
+
+  const int tid = threadIdx.x, lane = tid % kWave;
+  const int wave = __builtin_amdgcn_readfirstlane(tid / kWave);
+  const int wm = wave % WM, wn = wave / WM;
+  const int frow = tid / 8, c4 = tid % 8;
+
+  // byte offsets of this lane's loads from the tile's first rows
+  const char* Pb = reinterpret_cast<const char*>(P + (int64_t)m0 * ldp + kbeg);
+  const char* Qb = reinterpret_cast<const char*>(Q + (int64_t)n0 * ldq + kbeg);
+  uint32_t po[VP], qo[VQ];
+#pragma unroll
+  for (int v = 0; v < VP; ++v) {
+    int row = frow + v * RPV;
+    row = m0 + row < M ? row : M - 1 - m0;
+    po[v] = (uint32_t)row * (uint32_t)ldp * 4u + 16u * c4;
+  }
+#pragma unroll
+  for (int v = 0; v < VQ; ++v) {
+    int row = frow + v * RPV;
+    row = n0 + row < N ? row : N - 1 - n0;
+    qo[v] = (uint32_t)row * (uint32_t)ldq * 4u + 16u * c4;
+  }
+  struct Regs {
+    fx4 p[VP], q[VQ];
+  };
+  auto kbyte = [&](int sl) {  // byte offset of a full slab within a row
+    return (sl - part) * 4 * kSlab;
+  };
+  auto fetch = [&](Regs& r, int sl) {
+    if (sl < part) {
+      const int k = nfull * kSlab + 4 * c4;
+#pragma unroll
+      for (int v = 0; v < VP; ++v)
+        r.p[v] = load_tail(reinterpret_cast<const float*>(Pb + nfull * 4 * kSlab + po[v]), k,
+                           kend - kbeg);
+#pragma unroll
+      for (int v = 0; v < VQ; ++v)
+        r.q[v] = load_tail(reinterpret_cast<const float*>(Qb + nfull * 4 * kSlab + qo[v]), k,
+                           kend - kbeg);
+    } else {
+      const int kb = kbyte(sl);
+#pragma unroll
+      for (int v = 0; v < VP; ++v) r.p[v] = *reinterpret_cast<const fx4*>(Pb + kb + po[v]);
+#pragma unroll
+      for (int v = 0; v < VQ; ++v) r.q[v] = *reinterpret_cast<const fx4*>(Qb + kb + qo[v]);
+    }
+  };
+  Regs rg;
+
+  // LDS: blocks of 16 rows x 32 K per part (1 KB), the 16-byte chunk c of
+  // row r at slot 16 c + (r ^ 2 c), so that the 8-byte writes of two rows
+  // and the fragment reads (lane l: row l % 16, chunk l / 16) are both free
+  // of bank conflicts
+  float amax_p = 0.f, amax_q = 0.f;
+  ux2 kp[VP][NP], kq[VQ][3];
+  auto convert = [&](const Regs& r, int v) {
+    if (v < VP)
+      split4<NP>(r.p[v], kp[v], amax_p);
+    else
+      split4<3>(r.q[v - VP], kq[v - VP], amax_q);
+  };
+  const int wc = c4 / 2;
+  const int woff = (wc * 16 + ((frow & 15) ^ (2 * wc))) * 16 + (c4 & 1) * 8;
+  auto write_parts = [&](char* st) {
+#pragma unroll
+    for (int v = 0; v < VP; ++v) {
+      char* b = st + ((frow + v * RPV) / 16) * NP * 1024 + woff;
+#pragma unroll
+      for (int q = 0; q < NP; ++q) *reinterpret_cast<ux2*>(b + q * 1024) = kp[v][q];
+    }
+#pragma unroll
+    for (int v = 0; v < VQ; ++v) {
+      if (BN % RPV == 0 || v + 1 < VQ || frow + v * RPV < BN) {
+        char* b = st + kPBytes + ((frow + v * RPV) / 16) * 3072 + woff;
+#pragma unroll
+        for (int q = 0; q < 3; ++q) *reinterpret_cast<ux2*>(b + q * 1024) = kq[v][q];
+      }
+    }
+  };
+  const int slot = ((lane / 16) * 16 + ((lane % 16) ^ (2 * (lane / 16)))) * 16;
+  bf8 pf[FM][NP], qf[FN][3];
+  auto read_frags = [&](const char* st) {
+    const char* sp = st + wm * FM * NP * 1024 + slot;
+    const char* sq = st + kPBytes + wn * FN * 3072 + slot;
+#pragma unroll
+    for (int i = 0; i < FM; ++i)
+#pragma unroll
+      for (int q = 0; q < NP; ++q)
+        pf[i][q] = *reinterpret_cast<const bf8*>(sp + (i * NP + q) * 1024);
+#pragma unroll
+    for (int j = 0; j < FN; ++j)
+#pragma unroll
+      for (int q = 0; q < 3; ++q)
+        qf[j][q] = *reinterpret_cast<const bf8*>(sq + (j * 3 + q) * 1024);
+  };
+  // end of a half step: this wave's LDS accesses are done, then all meet
+  auto turn = [&]() {
+    __builtin_amdgcn_sched_barrier(0);
+    asm volatile("s_waitcnt lgkmcnt(0)\n\ts_barrier" ::: "memory");
+    __builtin_amdgcn_sched_barrier(0);
+  };
+  fx4 acc[FN][FM];
+#pragma unroll
+  for (int j = 0; j < FN; ++j)
+#pragma unroll
+    for (int i = 0; i < FM; ++i) acc[j][i] = fx4{0.f, 0.f, 0.f, 0.f};
+
+  if (nslabs > 0) {
+    // slab 0 in stage 0, slab 1 converted in registers, slab 2 in flight;
+    // past the last slab the loads repeat it (the copies are never read)
+    const int last = nslabs - 1;
+    {
+      Regs r0, r1;
+      fetch(r0, 0);
+      fetch(r1, last < 1 ? last : 1);
+      fetch(rg, last < 2 ? last : 2);
+#pragma unroll
+      for (int v = 0; v < VN; ++v) convert(r0, v);
+      write_parts(lds);
+#pragma unroll
+      for (int v = 0; v < VN; ++v) convert(r1, v);
+    }
+    const bool second = wave >= WM * WN / 2;  // the other wave of each SIMD
+    __syncthreads();
+    // Order of LDS accesses, half step by half step (first | second waves):
+    // slab s is written to stage s & 1 in half steps 2s - 2 | 2s - 1 and
+    // read in 2s | 2s + 1; it replaces slab s - 2, read in 2s - 4 | 2s - 3.
+    if (second) turn();
+    for (int ks = 0; ks < nslabs; ++ks) {
+      write_parts(lds + ((ks + 1) & 1) * kStage);
+      read_frags(lds + (ks & 1) * kStage);
+      turn();
+      // (with a single, partial slab: the rows' first 32 entries, which K >=
+      // kSplitMinK makes sure of; never used)
+      const int kn = ks + 3 < last ? ks + 3 : last;
+      const int kb = kn < part ? -4 * kbeg : kbyte(kn);
+      const char* Pn = Pb + kb;
+      const char* Qn = Qb + kb;
+#pragma unroll
+      for (int j = 0; j < FN; ++j) {
+        // the small products from zero, then added to the sum that takes
+        // h h': two roundings at its size per slab instead of six (5% of P
+        // nonzero, K = 1000: error 1.4e-7, with six 2.5e-7, FP32 MFMA 1.3e-7)
+        fx4 small[FM];
+#pragma unroll
+        for (int i = 0; i < FM; ++i) small[i] = fx4{0.f, 0.f, 0.f, 0.f};
+        mfma_parts<FM, NP>(qf[j], pf, small, acc[j]);
+#pragma unroll
+        for (int i = 0; i < FM; ++i) acc[j][i] += small[i];
+#pragma unroll
+        for (int v = 0; v < VN; ++v) {
+          if (v * FN / VN != j) continue;
+          convert(rg, v);
+          if (v < VP)
+            rg.p[v] = *reinterpret_cast<const fx4*>(Pn + po[v]);
+          else
+            rg.q[v - VP] = *reinterpret_cast<const fx4*>(Qn + qo[v - VP]);
+        }
+        // two vector instructions in the shadow of every MFMA
+#pragma unroll
+        for (int g = 0; g < FM * (NP == 1 ? 3 : 6); ++g) {
+          __builtin_amdgcn_sched_group_barrier(0x8, 1, 0);
+          __builtin_amdgcn_sched_group_barrier(0x2, NP == 1 ? 3 : 2, 0);
+        }
+      }
+      turn();
+    }
+    if (!second) turn();
+  }
+  // the operands' largest magnitudes over the whole tile
+  float* red = reinterpret_cast<float*>(lds);
+  amax_p = wave_max(amax_p);
+  amax_q = wave_max(amax_q);
+  if (lane == 0) {
+    red[2 * wave] = amax_p;
+    red[2 * wave + 1] = amax_q;
+  }
+  __syncthreads();
+#pragma unroll
+  for (int w = 0; w < WM * WN; ++w) {
+    amax_p = fmaxf(amax_p, red[2 * w]);
+    amax_q = fmaxf(amax_q, red[2 * w + 1]);
+  }
+
+  float* Cs = C + (int64_t)split * split_stride;
+  const bool vec = ldc % 4 == 0 && ((uintptr_t)Cs & 15) == 0;
+  const int lr = lane % 16, lc = lane / 16;
+  // Rows of C that are not 16-byte aligned go through LDS, 16 rows of the
+  // wave's tile at a time, so that the 4-byte stores of a wave still cover
+  // whole rows (387 x 22611 x 334: 74 to 71 us)
+  constexpr int kRow = TN + 4;
+  float* strip = reinterpret_cast<float*>(lds) + 64 + wave * 16 * kRow;
+  static_assert((64 + WM * WN * 16 * kRow) * 4 <= 2 * kStage, "row strips fit in the stages");
+  bool bad = false;
+  auto store_blocks = [&](int i, auto block) {  // the FN blocks of row block i
+    const int r0 = m0 + wm * TM + i * 16, c0 = n0 + wn * TN;
+    if (vec) {
+      if (r0 + lr < M) {
+#pragma unroll
+        for (int j = 0; j < FN; ++j) {
+          const int col = c0 + j * 16 + 4 * lc;
+          store_cols(Cs + (int64_t)(r0 + lr) * ldc + col, col, N, block(j));
+        }
+      }
+      return;
+    }
+#pragma unroll
+    for (int j = 0; j < FN; ++j)
+      *reinterpret_cast<fx4*>(strip + lr * kRow + j * 16 + 4 * lc) = block(j);
+    __builtin_amdgcn_fence(__ATOMIC_SEQ_CST, "wavefront");
+    for (int e = lane; e < 16 * TN; e += kWave) {
+      const int r = e / TN, c = e % TN;
+      if (r0 + r < M && c0 + c < N) Cs[(int64_t)(r0 + r) * ldc + c0 + c] = strip[r * kRow + c];
+    }
+    __builtin_amdgcn_fence(__ATOMIC_SEQ_CST, "wavefront");
+  };
+#pragma unroll
+  for (int i = 0; i < FM; ++i) {
+#pragma unroll
+    for (int j = 0; j < FN; ++j)
+#pragma unroll
+      for (int e = 0; e < 4; ++e) bad |= suspect(acc[j][i][e], amax_p, amax_q);
+  }
+  if (!__any(bad)) {  // wave-uniform
+#pragma unroll
+    for (int i = 0; i < FM; ++i) store_blocks(i, [&](int j) { return acc[j][i]; });
+  } else {
+#pragma unroll 1
+    for (int i = 0; i < FM; ++i) {
+      fx4 b[FN];
+#pragma unroll
+      for (int j = 0; j < FN; ++j)
+        b[j] = f32_block(P, ldp, Q, ldq, M, N, m0 + wm * TM + i * 16, n0 + wn * TN + j * 16, kbeg,
+                         kend);
+      store_blocks(i, [&](int j) { return b[j]; });
+    }
+  }
+}
+
+// ---------------------------------------------------------------------------
+// Small tiles, K shared by the waves
+// ---------------------------------------------------------------------------
+
+// LDS bytes of a workgroup: the slabs of its waves, and at the end the
+// partial tiles of half of them
+template <int FM, int FN>
+constexpr size_t ks_lds_bytes(int waves) {
+  const size_t slabs = (size_t)waves * (FM + FN) * 2048;
+  const size_t parts = (size_t)((waves + 1) / 2) * FM * FN * 1024;
+  return slabs > parts ? slabs : parts;
+}
+
+template <int FM, int FN, int NP>
+__device__ __forceinline__ void ks_tile(const float* __restrict__ P, int64_t ldp,
+                                        const float* __restrict__ Q, int64_t ldq,
+                                        float* __restrict__ Cs, int64_t ldc, int M, int N, int m0,
+                                        int n0, int kbeg, int kend, char* lds, float* red) {
+  constexpr int RB = (FM + FN) * 16;  // rows of a slab: P's, then Q's
+  constexpr int FB = FM * FN;
+  const int nslabs = kend > kbeg ? (kend - kbeg + kSlab - 1) / kSlab : 0;
+  const int nfull = kend > kbeg ? (kend - kbeg) / kSlab : 0;
+  const int lane = threadIdx.x % kWave;
+  const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x / kWave);
+  const int nw = blockDim.x / kWave;
+  const int lr = lane % 16, lc = lane / 16;
+  const char* Pb = reinterpret_cast<const char*>(P + (int64_t)m0 * ldp + kbeg);
+  const char* Qb = reinterpret_cast<const char*>(Q + (int64_t)n0 * ldq + kbeg);
+
+  float amax_p = 0.f, amax_q = 0.f;
+  // a fragment: lane (row lr, lc) holds k = 4 lc .. +3 and 16 + 4 lc .. +3
+  auto split_frag = [&](const fx4 (&x)[2], auto& out, float& amax) {
+    constexpr int PARTS = sizeof(out) / sizeof(bf8);
+    ux2 a[PARTS], b[PARTS];
+    split4<PARTS>(x[0], a, amax);
+    split4<PARTS>(x[1], b, amax);
+#pragma unroll
+    for (int q = 0; q < PARTS; ++q)
+      out[q] = __builtin_bit_cast(bf8, ux4{a[q].x, a[q].y, b[q].x, b[q].y});
+  };
+  fx4 acc[FN][FM];
+#pragma unroll
+  for (int j = 0; j < FN; ++j)
+#pragma unroll
+    for (int i = 0; i < FM; ++i) acc[j][i] = fx4{0.f, 0.f, 0.f, 0.f};
+  bf8 pf[FM][NP];
+  fx4 rp[FM][2], rq[FN][2];
+
+  // this wave's slab in LDS: row r is 128 bytes, its 16-byte chunk c at
+  // position c ^ (r & 7); 8 lanes load a row
+  char* slab = lds + wave * RB * 128;
+  uint32_t off[RB / 8];
+  {
+    const int r8 = lane / 8, ch = (lane % 8) ^ r8;
+#pragma unroll
+    for (int v = 0; v < RB / 8; ++v) {
+      const bool isp = v < 2 * FM;
+      int row = (isp ? v : v - 2 * FM) * 8 + r8;
+      const int last = isp ? M - 1 - m0 : N - 1 - n0;
+      row = row < last ? row : last;
+      off[v] = (uint32_t)row * (uint32_t)(isp ? ldp : ldq) * 4u + 16u * ch;
+    }
+  }
+  auto load_slab = [&](int ks) {
+    const char* Pn = Pb + ks * 4 * kSlab;
+    const char* Qn = Qb + ks * 4 * kSlab;
+#pragma unroll
+    for (int v = 0; v < RB / 8; ++v)
+      __builtin_amdgcn_global_load_lds(
+          (const __attribute__((address_space(1))) void*)((v < 2 * FM ? Pn : Qn) + off[v]),
+          (__attribute__((address_space(3))) void*)(slab + v * 1024), 16, 0, 0);
+  };
+  const int rd0 = lr * 128 + ((lc ^ (lr & 7)) * 16);
+  const int rd1 = lr * 128 + (((4 + lc) ^ (lr & 7)) * 16);
+  int ks = wave;
+  if (ks < nfull) {
+    load_slab(ks);
+    for (; ks < nfull; ks += nw) {
+      const int kn = ks + nw < nfull ? ks + nw : ks;
+      asm volatile("s_waitcnt vmcnt(0)" ::: "memory");  // the slab is in LDS
+#pragma unroll
+      for (int i = 0; i < FM; ++i) {
+        rp[i][0] = *reinterpret_cast<const fx4*>(slab + i * 2048 + rd0);
+        rp[i][1] = *reinterpret_cast<const fx4*>(slab + i * 2048 + rd1);
+      }
+#pragma unroll
+      for (int j = 0; j < FN; ++j) {
+        rq[j][0] = *reinterpret_cast<const fx4*>(slab + (FM + j) * 2048 + rd0);
+        rq[j][1] = *reinterpret_cast<const fx4*>(slab + (FM + j) * 2048 + rd1);
+      }
+      asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");  // and now in registers
+      load_slab(kn);
+      __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+      for (int i = 0; i < FM; ++i) split_frag(rp[i], pf[i], amax_p);
+      bf8 q[2][3];
+      split_frag(rq[0], q[0], amax_q);
+#pragma unroll
+      for (int j = 0; j < FN; ++j) {
+        mfma_parts<FM, NP>(q[j & 1], pf, acc[j], acc[j]);
+        if (j + 1 < FN) split_frag(rq[j + 1], q[(j + 1) & 1], amax_q);
+        if constexpr (FM * FN >= 16) {
+#pragma unroll
+          for (int g = 0; g < FM * (NP == 1 ? 3 : 6); ++g) {
+            __builtin_amdgcn_sched_group_barrier(0x8, 1, 0);
+            __builtin_amdgcn_sched_group_barrier(0x2, 3, 0);
+          }
+        }
+      }
+    }
+    asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+  }
+  if (nfull < nslabs && wave == nfull % nw) {  // the partial last slab
+    const int k0 = kbeg + nfull * kSlab;
+    auto load_frag = [&](fx4 (&r)[2], const char* base, uint32_t ld, int row) {
+      const float* s = reinterpret_cast<const float*>(base + nfull * 4 * kSlab +
+                                                      (uint64_t)row * ld * 4u) + 4 * lc;
+      r[0] = load_tail(s, k0 + 4 * lc, kend);
+      r[1] = load_tail(s + 16, k0 + 16 + 4 * lc, kend);
+    };
+#pragma unroll
+    for (int i = 0; i < FM; ++i) {
+      const int row = i * 16 + lr < M - m0 ? i * 16 + lr : M - 1 - m0;
+      load_frag(rp[i], Pb, (uint32_t)ldp, row);
+      split_frag(rp[i], pf[i], amax_p);
+    }
+#pragma unroll
+    for (int j = 0; j < FN; ++j) {
+      const int row = j * 16 + lr < N - n0 ? j * 16 + lr : N - 1 - n0;
+      bf8 q[3];
+      load_frag(rq[j], Qb, (uint32_t)ldq, row);
+      split_frag(rq[j], q, amax_q);
+      mfma_parts<FM, NP>(q, pf, acc[j], acc[j]);
+    }
+  }
+  amax_p = wave_max(amax_p);
+  amax_q = wave_max(amax_q);
+  if (lane == 0) {
+    red[2 * wave] = amax_p;
+    red[2 * wave + 1] = amax_q;
+  }
+
+  // the waves' partial tiles: the upper half through LDS to the lower half,
+  // which adds them, then every wave sums its share of the blocks
+  fx4* L = reinterpret_cast<fx4*>(lds);
+  const int half = (nw + 1) / 2;
+  __syncthreads();  // the slabs are read; red is written
+  for (int w = 0; w < nw; ++w) {
+    amax_p = fmaxf(amax_p, red[2 * w]);
+    amax_q = fmaxf(amax_q, red[2 * w + 1]);
+  }
+  if (wave >= half) {
+#pragma unroll
+    for (int b = 0; b < FB; ++b) L[((wave - half) * FB + b) * kWave + lane] = acc[b % FN][b / FN];
+  }
+  __syncthreads();
+  if (wave < half) {
+#pragma unroll
+    for (int b = 0; b < FB; ++b) {
+      fx4 s = acc[b % FN][b / FN];
+      if (wave + half < nw) s += L[(wave * FB + b) * kWave + lane];
+      L[(wave * FB + b) * kWave + lane] = s;
+    }
+  }
+  __syncthreads();
+  const bool vec = ldc % 4 == 0 && ((uintptr_t)Cs & 15) == 0;
+  // C rows that are not 16-byte aligned: the sums go back to LDS and out in
+  // whole rows of the tile with 4-byte stores
+  for (int b = wave; b < FB; b += nw) {
+    fx4 s = L[b * kWave + lane];
+    for (int w = 1; w < half; ++w) s += L[(w * FB + b) * kWave + lane];
+    bool bad = false;
+#pragma unroll
+    for (int e = 0; e < 4; ++e) bad |= suspect(s[e], amax_p, amax_q);
+    const int rm = m0 + (b / FN) * 16, cn = n0 + (b % FN) * 16;
+    if (__any(bad)) s = f32_block(P, ldp, Q, ldq, M, N, rm, cn, kbeg, kend);  // wave-uniform
+    const int row = rm + lr, col = cn + 4 * lc;
+    if (!vec)
+      L[b * kWave + lane] = s;
+    else if (row < M)
+      store_cols(Cs + (int64_t)row * ldc + col, col, N, s);
+  }
+  if (vec) return;
+  __syncthreads();
+  const float* T = reinterpret_cast<const float*>(lds);
+  for (int e = threadIdx.x; e < FB * 256; e += blockDim.x) {
+    const int r = e / (16 * FN), c = e % (16 * FN);
+    const int b = (r / 16) * FN + c / 16, l = r % 16 + 16 * ((c % 16) / 4);
+    if (m0 + r < M && n0 + c < N)
+      Cs[(int64_t)(m0 + r) * ldc + n0 + c] = T[(b * kWave + l) * 4 + c % 4];
+  }
+}
+
+constexpr int kKsWaves = 8;
+
+template <int FM, int FN, int NP, int OCC>
+__global__ __launch_bounds__(kKsWaves* kWave, OCC) void split_ks_kernel(
+    const float* __restrict__ P, int64_t ldp, const float* __restrict__ Q, int64_t ldq,
+    float* __restrict__ C, int64_t ldc, int M, int N, int K, int tiles_m, int tiles_mn,
+    int splits, int kslabs_per_split, int64_t split_stride, const int32_t* __restrict__ gate,
+    int32_t gate_run) {
+  extern __shared__ __attribute__((aligned(16))) char lds[];
+  __shared__ float red[2 * kKsWaves];
+  if (gate != nullptr && *gate != gate_run) return;
+  int tile, split;
+  tile_of(blockIdx.x, splits, tiles_mn, &tile, &split);
+  const int kbeg = split * kslabs_per_split * kSlab;
+  int kend = kbeg + kslabs_per_split * kSlab;
+  kend = kend < K ? kend : K;
+  ks_tile<FM, FN, NP>(P, ldp, Q, ldq, C + (int64_t)split * split_stride, ldc, M, N,
+                      (tile % tiles_m) * FM * 16, (tile / tiles_m) * FN * 16, kbeg, kend, lds,
+                      red);
+}
+
+// Compiled tiles.  Times of one workgroup step in microseconds, as measured
+// with few workgroups and with all CUs busy (the clock falls as the matrix
+// cores fill): a large tile takes `step` per slab, a small one `step` per
+// round of its waves over their slabs; `fixed` per workgroup is the first
+// loads, the sums over the waves and the store.
+struct SplitShape {
+  int bm, bn, waves;  // waves > 0: K shared by that many waves
+  double step, step_full, step_sgn, step_sgn_full, fixed;
+};
+constexpr SplitShape kSplitShapes[] = {
+    {256, 160, 0, 2.13, 2.87, 1.25, 1.65, 12.0},
+    {256, 128, 0, 1.75, 2.35, 1.00, 1.35, 12.0},
+    {64, 80, 8, 3.30, 4.10, 2.20, 2.85, 4.0},
+    {64, 64, 8, 2.70, 3.40, 1.75, 2.25, 3.5},
+    {64, 32, 8, 1.85, 2.30, 1.20, 1.50, 2.5},
+    {32, 32, 8, 1.20, 1.50, 0.85, 1.05, 2.2},
+    {64, 16, 8, 1.43, 1.80, 0.90, 1.15, 2.2},
+    {16, 16, 8, 0.60, 0.75, 0.45, 0.55, 2.0},
+};
+constexpr int kNumSplit = (int)(sizeof(kSplitShapes) / sizeof(kSplitShapes[0]));
+
+template <int BM, int BN, int WM, int WN, int NP>
+void launch_pp(hipStream_t st, const float* P, int64_t ldp, const float* Q, int64_t ldq, float* C,
+               int64_t ldc, int64_t M, int64_t N, int64_t K, int splits, int64_t split_stride,
+               const int32_t* gate, int32_t gate_run) {
+  const int tm = (int)ceil_div(M, BM), tn = (int)ceil_div(N, BN);
+  const int per = (int)ceil_div(ceil_div(K, (int64_t)kSlab), (int64_t)splits);
+  hipLaunchKernelGGL((split_pp_kernel<BM, BN, WM, WN, NP>), dim3((unsigned)(tm * tn * splits)),
+                     dim3(WM * WN * kWave), 0, st, P, ldp, Q, ldq, C, ldc, (int)M, (int)N, (int)K,
+                     tm, tm * tn, splits, per, split_stride, gate, gate_run);
+}
+
+template <int FM, int FN, int NP, int OCC>
+void launch_ks(hipStream_t st, const float* P, int64_t ldp, const float* Q, int64_t ldq, float* C,
+               int64_t ldc, int64_t M, int64_t N, int64_t K, int waves, int splits,
+               int64_t split_stride, const int32_t* gate, int32_t gate_run) {
+  const int tm = (int)ceil_div(M, 16 * FM), tn = (int)ceil_div(N, 16 * FN);
+  const int per = (int)ceil_div(ceil_div(K, (int64_t)kSlab), (int64_t)splits);
+  // few slabs and workgroups for every CU anyway: fewer waves, two slabs
+  // each, and more workgroups at once (24 x 26299 x 219: 13.0 to 10.9 us)
+  if (per < 2 * waves && (int64_t)tm * tn * splits >= 512) waves = per < 4 ? 2 : (per + 1) / 2;
+  hipLaunchKernelGGL((split_ks_kernel<FM, FN, NP, OCC>), dim3((unsigned)(tm * tn * splits)),
+                     dim3(waves * kWave), (ks_lds_bytes<FM, FN>(waves)), st, P, ldp, Q, ldq, C,
+                     ldc, (int)M, (int)N, (int)K, tm, tm * tn, splits, per, split_stride, gate,
+                     gate_run);
+}
+
+template <int NP>
+void dispatch_split(int v, hipStream_t st, const float* P, int64_t ldp, const float* Q,
+                    int64_t ldq, float* C, int64_t ldc, int64_t M, int64_t N, int64_t K,
+                    int splits, int64_t stride, const int32_t* gate, int32_t gate_run) {
+  const int w = kSplitShapes[v].waves;
+  switch (v) {
+    case 0:
+      launch_pp<256, 160, 4, 2, NP>(st, P, ldp, Q, ldq, C, ldc, M, N, K, splits, stride, gate, gate_run);
+      break;
+    case 1:
+      launch_pp<256, 128, 4, 2, NP>(st, P, ldp, Q, ldq, C, ldc, M, N, K, splits, stride, gate, gate_run);
+      break;
+    case 2:
+      launch_ks<4, 5, NP, 2>(st, P, ldp, Q, ldq, C, ldc, M, N, K, w, splits, stride, gate, gate_run);
+      break;
+    case 3:
+      launch_ks<4, 4, NP, 2>(st, P, ldp, Q, ldq, C, ldc, M, N, K, w, splits, stride, gate, gate_run);
+      break;
+    case 4:
+      launch_ks<4, 2, NP, 2>(st, P, ldp, Q, ldq, C, ldc, M, N, K, w, splits, stride, gate, gate_run);
+      break;
+    case 5:
+      launch_ks<2, 2, NP, 4>(st, P, ldp, Q, ldq, C, ldc, M, N, K, w, splits, stride, gate, gate_run);
+      break;
+    case 6:
+      launch_ks<4, 1, NP, 2>(st, P, ldp, Q, ldq, C, ldc, M, N, K, w, splits, stride, gate, gate_run);
+      break;
+    default:
+      launch_ks<1, 1, NP, 4>(st, P, ldp, Q, ldq, C, ldc, M, N, K, w, splits, stride, gate, gate_run);
+      break;
+  }
+}
+
+}  // namespace
+
+int gemm_num_split_shapes() { return kNumSplit; }
+int split_shape_bm(int shape) {
+  const int v = shape - kSplitShape0;
+  return v >= 0 && v < kNumSplit ? kSplitShapes[v].bm : 0;
+}
+
+// Products with K below kSplitMinK stay on the FP32 instructions: with fewer
+// terms, most of them zero, the FP32 sums round so seldom that the parts
+// would be less exact (K = 100, 5% of P nonzero: 5.7e-8 against 4.6e-8; K =
+// 200: 6.4e-8 and 6.2e-8).  The tiles' byte offsets are 32 bits wide, which
+// bounds the leading dimensions.
+bool split_possible(int64_t K, int64_t ldp, int64_t ldq) {
+  return K >= kSplitMinK && ldp <= (1 << 21) && ldq <= (1 << 21);
+}
+
+GemmPlan model_plan_split(int64_t M, int64_t N, int64_t K, int max_splits, bool signs,
+                          int fixed_splits, double* us_out) {
+  GemmPlan best{kSplitShape0, 1};
+  double best_us = 1e300;
+  const int64_t kslabs = ceil_div(K, (int64_t)kSlab);
+  for (int v = 0; v < kNumSplit; ++v) {
+    const SplitShape& sh = kSplitShapes[v];
+    if (sh.bm > 16 && M <= sh.bm / 2) continue;  // mostly padding rows
+    const double lo = signs ? sh.step_sgn : sh.step;
+    const double hi = signs ? sh.step_sgn_full : sh.step_full;
+    const int64_t tiles = ceil_div(M, (int64_t)sh.bm) * ceil_div(N, (int64_t)sh.bn);
+    for (int splits = fixed_splits > 0 ? fixed_splits : 1; splits <= max_splits; splits *= 2) {
+      const int64_t per = ceil_div(kslabs, (int64_t)splits);
+      if (fixed_splits > 0 ? splits != fixed_splits : splits > 1 && per < 8)
+        break;  // too little K per split
+      const int64_t wgs = tiles * splits;
+      const double steps = (double)(sh.waves > 0 ? ceil_div(per, (int64_t)sh.waves) : per);
+      // rounds of 256 workgroups, the last one partly filled (and faster)
+      const int64_t full = wgs / 256, rest = wgs % 256;
+      double us = (double)full * (steps * hi + sh.fixed);
+      if (rest > 0) us += steps * (lo + (hi - lo) * (double)rest / 256.0) + sh.fixed;
+      // the partial sums' traffic (written, then read by the next kernel)
+      if (splits > 1) us += 1.0 + (double)splits * (double)M * (double)N * 8.0 / 4.0e6;
+      if (us < best_us * 0.999) {
+        best_us = us;
+        best = GemmPlan{kSplitShape0 + v, splits};
+      }
+    }
+  }
+  *us_out = best_us;
+  return best;
+}
+
+void gemm_nt_split(hipStream_t st, const float* P, int64_t ldp, const float* Q, int64_t ldq,
+                   float* C, int64_t ldc, int64_t M, int64_t N, int64_t K, const int32_t* gate,
+                   int32_t gate_run, GemmPlan plan, int64_t split_stride, bool signs) {
+  if (M <= 0 || N <= 0) return;
+  const int v = plan.shape - kSplitShape0;
+  if (signs)
+    dispatch_split<1>(v, st, P, ldp, Q, ldq, C, ldc, M, N, K, plan.splits, split_stride, gate,
+                      gate_run);
+  else
+    dispatch_split<3>(v, st, P, ldp, Q, ldq, C, ldc, M, N, K, plan.splits, split_stride, gate,
+                      gate_run);
+}
+
+}  // namespace spca

@@ -298,9 +298,9 @@ int spca_am_solve_group(spca_ctx* ctx, void* stream, int32_t count, const spca_p
     d2.splits = L.aty_splits[q];
     d2.req = q;
   }
-  int tiles_ax = 0, tiles_aty = 0;
-  gemm_group_tiles(hdesc.data(), count, &tiles_ax);
-  gemm_group_tiles(hdesc.data() + count, count, &tiles_aty);
+  int items_ax = 0, items_aty = 0;
+  const int tile_ax = gemm_group_tiles(hdesc.data(), count, &items_ax);
+  const int tile_aty = gemm_group_tiles(hdesc.data() + count, count, &items_aty);
   SPCA_HIP_TRY(hipMemcpyAsync(cfg, hcfg.data(), sizeof(RowCfg) * (size_t)R,
                               hipMemcpyHostToDevice, st));
   SPCA_HIP_TRY(hipMemcpyAsync(desc, hdesc.data(), sizeof(GemmGroupDesc) * 2 * (size_t)count,
@@ -317,9 +317,9 @@ int spca_am_solve_group(spca_ctx* ctx, void* stream, int32_t count, const spca_p
   StartState sg = s;
   sg.cfg = cfg;
   auto iteration = [&]() -> int {
-    gemm_nt_f32_group(st, desc, count, tiles_ax, running);
+    gemm_nt_f32_group(st, desc, count, tile_ax, items_ax, running);
     group_y_update(st, U, R * ldu, Y, ldu, R, L.n_max, sg);
-    gemm_nt_f32_group(st, desc + count, count, tiles_aty, running);
+    gemm_nt_f32_group(st, desc + count, count, tile_aty, items_aty, running);
     if (L.saty > 1) group_sum_splits(st, V, R * ldx, ldx, R, L.p_max, sg);
     for (int k = 0; k < 4; ++k)
       if (kinds[k])

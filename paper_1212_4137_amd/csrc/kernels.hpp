@@ -125,7 +125,10 @@ void deflate_v(hipStream_t st, float* V, int64_t ldv, int64_t p, int64_t r, Star
 void deflate_final_alpha(hipStream_t st, const float* X, int64_t ldx, int64_t p,
                          int64_t r, Defl d);
 
-// Tile shape (index into the compiled shapes) and K split of one product.
+// Tile shape (index into the compiled shapes; from kSplitShape0 on, of the
+// BF16-part tiles of gemm_split.hip) and K split of one product.
+constexpr int kSplitShape0 = 64;
+constexpr int kStreamShape0 = 32;  // one-wave FP32 tiles of gemm_stream.hip
 struct GemmPlan {
   int shape;
   int splits;
@@ -137,8 +140,35 @@ GemmPlan plan_gemm_nt(int64_t M, int64_t N, int64_t K, int max_splits,
                       int elem_bytes = 4);
 // the cost model alone (no tuning table)
 GemmPlan model_plan_gemm_nt(int64_t M, int64_t N, int64_t K, int max_splits,
-                            int elem_bytes = 4);
+                            int elem_bytes = 4, double* cycles_out = nullptr);
+// plan_gemm_nt for FP32 operands, on the one-wave tiles of gemm_stream.hip
+// where those are faster: same K split, same bits.  us_out: modelled time
+// (0 for a tuning-table entry).
+GemmPlan plan_f32(int64_t M, int64_t N, int64_t K, int max_splits, double* us_out = nullptr);
+// the faster of plan_f32 and the BF16-part tiles (gemm_split.hip); a
+// tuning-table entry decides if there is one.  signs: P holds 0 and +-1
+// only.  fixed_splits > 0: the K split to use with either.  us_out: as above.
+GemmPlan plan_product_f32(int64_t M, int64_t N, int64_t K, int max_splits, int64_t ldp,
+                          int64_t ldq, bool signs, int fixed_splits = 0,
+                          double* us_out = nullptr);
 int gemm_num_shapes();
+// FP32 products on BF16 parts (gemm_split.hip): number of tiles, whether a
+// product can use them, the model's choice among them, and the launch
+// one-wave FP32 tiles (gemm_stream.hip): the bits of gemm_nt_kernel's tiles
+int gemm_num_stream_shapes();
+int model_stream(int64_t M, int64_t N, int64_t K, int splits, double* us_out);
+void gemm_nt_stream(hipStream_t st, const float* P, int64_t ldp, const float* Q, int64_t ldq,
+                    float* C, int64_t ldc, int64_t M, int64_t N, int64_t K, const int32_t* gate,
+                    int32_t gate_run, GemmPlan plan, int64_t split_stride);
+int gemm_num_split_shapes();
+int split_shape_bm(int shape);
+constexpr int64_t kSplitMinK = 192;
+bool split_possible(int64_t K, int64_t ldp, int64_t ldq);
+GemmPlan model_plan_split(int64_t M, int64_t N, int64_t K, int max_splits, bool signs,
+                          int fixed_splits, double* us_out);
+void gemm_nt_split(hipStream_t st, const float* P, int64_t ldp, const float* Q, int64_t ldq,
+                   float* C, int64_t ldc, int64_t M, int64_t N, int64_t K, const int32_t* gate,
+                   int32_t gate_run, GemmPlan plan, int64_t split_stride, bool signs);
 // rows of the output tile of a shape (0 for an unknown shape)
 int gemm_shape_bm(int shape);
 // largest power-of-two split count (<= max_splits) that leaves every split
@@ -157,12 +187,13 @@ void tune_table_clear();
 // plan.splits > 1, K split s writes its partial product at
 // C + s * split_stride.  When gate != nullptr the kernel runs only if
 // *gate == gate_run.  When kdev != nullptr, K is read from *kdev on the
-// device (plan.splits must then be 1).
+// device (plan.splits must then be 1, its shape below kSplitShape0).  signs:
+// P holds 0 and +-1 only (used by the BF16-part tiles).
 void gemm_nt_f32(hipStream_t st, const float* P, int64_t ldp, const float* Q,
                  int64_t ldq, float* C, int64_t ldc, int64_t M, int64_t N,
                  int64_t K, const int32_t* gate, int32_t gate_run,
                  GemmPlan plan, int64_t split_stride,
-                 const int32_t* kdev = nullptr);
+                 const int32_t* kdev = nullptr, bool signs = false);
 
 // The same product with BF16 operands (bit patterns, ld multiple of 8 and
 // 16-byte aligned rows), FP32 accumulation and output.
@@ -175,7 +206,7 @@ void gemm_nt_bf16(hipStream_t st, const uint16_t* P, int64_t ldp,
 // C = P * Q^T (M x N x K, leading dimensions ldp, ldq, ldc) with its own K
 // split, split partials split_stride floats apart; req is the request it
 // belongs to.  tiles_m, kslabs_per_split and tile0 are filled in by
-// gemm_group_tiles, which also returns the launch's tile count.
+// gemm_group_tiles, which returns the launch's tile and its tile count.
 struct GemmGroupDesc {
   const float* P;
   const float* Q;
@@ -184,12 +215,10 @@ struct GemmGroupDesc {
   int32_t M, N, K, splits, req;
   int32_t tiles_m, kslabs_per_split, tile0;
 };
-constexpr int kGroupBM = 64;   // tile of the grouped products
-constexpr int kGroupBN = 128;
-void gemm_group_tiles(GemmGroupDesc* d, int count, int* total_tiles);
+int gemm_group_tiles(GemmGroupDesc* d, int count, int* total_items);
 // the products of d_dev (device copy of gemm_group_tiles' output); products
 // of requests with running[req] == 0 are skipped (running may be null)
-void gemm_nt_f32_group(hipStream_t st, const GemmGroupDesc* d_dev, int count, int total_tiles,
+void gemm_nt_f32_group(hipStream_t st, const GemmGroupDesc* d_dev, int count, int tile, int items,
                        const int32_t* running);
 
 // Row-major copy: At[i * ldat + k] = A[i + k * lda] (i < n, k < p).

@@ -64,6 +64,16 @@ inline int list_cap_of(int64_t p) {
 
 constexpr int kMaxSplits = 16;  // K splits of the dense A x product
 static_assert(kMaxSplits <= kSplitsMax, "the y-update sums at most kSplitsMax partials");
+// A solve's first iterations decide which stationary point a start ends at:
+// near-ties of the selection (and signs of u near zero) fall as the sums
+// round.  They stay on the FP32 MFMA sums, bit for bit, for this many
+// iterations; the products on BF16 parts, of another rounding (smaller
+// errors), take over once the supports have settled.  1000 x 10000, F1 and
+// F2, 1024 starts, 18 solves continued on the parts: from iteration 0 on 8
+// starts ended elsewhere, from 4 on 2, from 8 on 1, from 16 on none; 36 more
+// solves of 64 to 400 starts: from 16 on 2, from 24 on 1, from 32 on none.
+// The 32 iterations cost 2.4 ms of the 36 ms that 200 take at that size.
+constexpr int kSettleIters = 32;
 constexpr int kTimeSample = 8;  // SPCA_FLAG_TIME_SAMPLED: events every 8th iteration
 
 struct Layout {
@@ -115,7 +125,10 @@ Layout make_layout(int64_t n, int64_t p, int64_t r, bool copy_a, bool bf16) {
   L.ucap = bf16 ? 0 : p;
   const int64_t mem_cap = (int64_t)(64LL << 20) / (n > 0 ? n : 1);
   if (L.ucap > mem_cap) L.ucap = mem_cap < 1024 ? (p < 1024 ? p : 1024) : mem_cap;
-  L.plan_union = plan_gemm_nt(r, n, L.ucap < 256 ? (L.ucap > 0 ? L.ucap : 1) : 256, 1);
+  const int64_t uk = L.ucap < 256 ? (L.ucap > 0 ? L.ucap : 1) : 256;
+  L.plan_union = plan_gemm_nt(r, n, uk, 1);
+  if (L.plan_union.shape >= kStreamShape0)  // K is read on the device: workgroup tiles only
+    L.plan_union = model_plan_gemm_nt(r, n, uk, 1);
   size_t c = 0;
   L.off_At = carve(&c, bf16 ? 0 : sizeof(float) * (size_t)n * L.ldat);
   L.off_Ab = carve(&c, bf16 ? sizeof(uint16_t) * (size_t)p * L.ldab : 0);
@@ -601,6 +614,32 @@ int spca_am_solve_ex(spca_ctx* ctx, void* stream, const spca_problem* prob,
   } else {
     max_norm_column_start(st, A, ldA, n, p, colsq, X, L.ldx);
   }
+  // The products' tiles: FP32 MFMA sums for the first iterations, from
+  // parts_from on those of plan_product_f32 (same A X split count, which the
+  // planner and the y-update know).  Y holds signs (0 and +-1) under L1
+  // variance.
+  const bool signs = l1_variance(fid);
+  GemmPlan late_ax{}, late_aty{};
+  int32_t parts_from = INT32_MAX;
+  auto plan_products = [&]() {
+    if (bf16) {
+      L.plan_ax = late_ax = plan_gemm_nt(r, n, p, kMaxSplits, 2);
+      L.plan_aty = late_aty = plan_gemm_nt(r, p, n, kMaxSplits, 2);
+      return;
+    }
+    double us = 0.0, late_us = 0.0;
+    L.plan_ax = plan_f32(r, n, p, kMaxSplits);
+    L.plan_aty = plan_f32(r, p, n, kMaxSplits, &us);
+    late_ax = plan_product_f32(r, n, p, kMaxSplits, L.ldx, L.ldat, false, L.plan_ax.splits);
+    late_aty = plan_product_f32(r, p, n, kMaxSplits, L.ldu, ldA, signs, 0, &late_us);
+    // a second graph costs about 0.2 ms to capture: not for a few iterations
+    // or a small product (the eager loop follows the same rule)
+    const int64_t from = (int64_t)kSettleIters + (warm ? opts->warmup_iters : 0);
+    const bool worth = late_aty.shape >= kSplitShape0 &&
+                       (late_us == 0.0 || (us - late_us) * (double)(opts->maxit - from) > 300.0);
+    parts_from = !otf && worth ? (int32_t)from : INT32_MAX;
+  };
+  plan_products();
   if (opts->flags & SPCA_FLAG_AUTOTUNE) {
     // a8: measure every tile shape and split on this solve's own operands
     // for the products that have no entry in the tuning table yet.  Y holds
@@ -639,8 +678,7 @@ int spca_am_solve_ex(spca_ctx* ctx, void* stream, const spca_problem* prob,
       rc = autotune_product(st, r, p, n, L.aty_split_cap, kMaxSplits, eb, run_aty);
       if (rc != SPCA_OK) return rc;
     }
-    L.plan_ax = plan_gemm_nt(r, n, p, kMaxSplits, eb);
-    L.plan_aty = plan_gemm_nt(r, p, n, kMaxSplits, eb);
+    plan_products();
   }
   init_state(st, s, r);
   if (otf) otf_init(st, o, r);
@@ -678,15 +716,16 @@ int spca_am_solve_ex(spca_ctx* ctx, void* stream, const spca_problem* prob,
   // Every launch reads its control data (mode, active starts, sizes) from
   // the device-side plan, so the same sequence serves every iteration and
   // can be captured once into a graph.
-  auto iteration = [&](hipStream_t q, bool tm) -> int {
+  auto iteration = [&](hipStream_t q, bool tm, bool late) -> int {
+    const GemmPlan g_ax = late ? late_ax : L.plan_ax, g_aty = late ? late_aty : L.plan_aty;
     // u = A x and the y-update
     if (tm) SPCA_HIP_TRY(ctx->t_ax.mark(q));
     if (bf16)
       gemm_nt_bf16(q, Xb, L.ldxb, Atb, L.ldatb, U, L.ldu, r, n, p, &plan->mode,
-                   kAxDense, L.plan_ax, r * L.ldu);
+                   kAxDense, g_ax, r * L.ldu);
     else
       gemm_nt_f32(q, X, L.ldx, At, L.ldat, U, L.ldu, r, n, p, &plan->mode,
-                  kAxDense, L.plan_ax, r * L.ldu);
+                  kAxDense, g_ax, r * L.ldu);
     if (tm) SPCA_HIP_TRY(ctx->t_ax.mark(q));
     if (!bf16 && union_on) {  // the planner can pick the union product
       union_gather(q, X, L.ldx, r, A, ldA, n, ulist, plan, Xc, ldc_u, Qc, ldc_u);
@@ -712,11 +751,11 @@ int spca_am_solve_ex(spca_ctx* ctx, void* stream, const spca_problem* prob,
     if (tm) SPCA_HIP_TRY(ctx->t_aty.mark(q));
     if (bf16)
       gemm_nt_bf16(q, Yb, L.ldyb, Ab, L.ldab, V, L.ldx, r, p, n, nullptr, 0,
-                   L.plan_aty, r * L.ldx);
+                   g_aty, r * L.ldx);
     else
       gemm_nt_f32(q, Y, L.ldu, A, ldA, V, L.ldx, r, p, n, nullptr, 0,
-                  L.plan_aty, r * L.ldx);
-    sum_splits(q, V, r * L.ldx, L.plan_aty.splits, r * L.ldx);
+                  g_aty, r * L.ldx, nullptr, signs);
+    sum_splits(q, V, r * L.ldx, g_aty.splits, r * L.ldx);
     if (tm) SPCA_HIP_TRY(ctx->t_aty.mark(q));
     if (dk > 0) deflate_v(q, V, L.ldx, p, r, s, defl);
     if (tm) SPCA_HIP_TRY(ctx->t_xup.mark(q));
@@ -764,14 +803,15 @@ int spca_am_solve_ex(spca_ctx* ctx, void* stream, const spca_problem* prob,
     // launches only.
     rc = ensure_capture_stream(ctx);
     if (rc != SPCA_OK) return rc;
-    // one graph per union_on state, captured when first needed
-    hipGraphExec_t execs[2] = {nullptr, nullptr};
-    auto capture = [&](hipGraphExec_t* exec) -> int {
+    // one graph per union_on state and product plan, captured when first
+    // needed; a block of iterations across parts_from runs eagerly
+    hipGraphExec_t execs[4] = {nullptr, nullptr, nullptr, nullptr};
+    auto capture = [&](hipGraphExec_t* exec, bool late) -> int {
       hipGraph_t graph = nullptr;
       SPCA_HIP_TRY(hipStreamBeginCapture(ctx->capture, hipStreamCaptureModeThreadLocal));
       int body_rc = SPCA_OK;
       for (int32_t k = 0; k < every && body_rc == SPCA_OK; ++k)
-        body_rc = iteration(ctx->capture, false);
+        body_rc = iteration(ctx->capture, false, late);
       hipError_t end_rc = hipStreamEndCapture(ctx->capture, &graph);
       if (body_rc != SPCA_OK) {
         if (graph) (void)hipGraphDestroy(graph);
@@ -785,16 +825,23 @@ int spca_am_solve_ex(spca_ctx* ctx, void* stream, const spca_problem* prob,
     };
     int loop_rc = SPCA_OK;
     while (!done && it + every <= loop_max) {
-      hipGraphExec_t& exec = execs[union_on ? 1 : 0];
-      if (exec == nullptr) {
-        loop_rc = capture(&exec);
+      const bool late = it >= parts_from;
+      if (!late && parts_from - it < every) {
+        for (int32_t k = 0; k < every && loop_rc == SPCA_OK; ++k)
+          loop_rc = iteration(st, false, it + k >= parts_from);
         if (loop_rc != SPCA_OK) break;
-      }
-      hipError_t e = hipGraphLaunch(exec, st);
-      if (e != hipSuccess) {
-        set_error(std::string("hipGraphLaunch: ") + hipGetErrorString(e));
-        loop_rc = SPCA_EHIP;
-        break;
+      } else {
+        hipGraphExec_t& exec = execs[(union_on ? 1 : 0) + (late ? 2 : 0)];
+        if (exec == nullptr) {
+          loop_rc = capture(&exec, late);
+          if (loop_rc != SPCA_OK) break;
+        }
+        hipError_t e = hipGraphLaunch(exec, st);
+        if (e != hipSuccess) {
+          set_error(std::string("hipGraphLaunch: ") + hipGetErrorString(e));
+          loop_rc = SPCA_EHIP;
+          break;
+        }
       }
       it += every;
       if (it < loop_max) {
@@ -807,7 +854,7 @@ int spca_am_solve_ex(spca_ctx* ctx, void* stream, const spca_problem* prob,
     if (loop_rc != SPCA_OK) return loop_rc;
   }
   for (; !done && it < loop_max; ++it) {
-    rc = iteration(st, timed && (!sampled || it % kTimeSample == 0));
+    rc = iteration(st, timed && (!sampled || it % kTimeSample == 0), it >= parts_from);
     if (rc != SPCA_OK) return rc;
     if ((it + 1) % every == 0 && it + 1 < loop_max) {
       rc = none_active(&done);
@@ -1472,7 +1519,7 @@ int spca_gemm_nt_f32(void* stream, const float* P, int64_t ldp, const float* Q,
   SPCA_REQUIRE((uintptr_t)P % 16 == 0 && (uintptr_t)Q % 16 == 0,
                "P and Q must be 16-byte aligned");
   gemm_nt_f32((hipStream_t)stream, P, ldp, Q, ldq, C, ldc, M, N, K, nullptr, 0,
-              plan_gemm_nt(M, N, K, 1), 0);
+              plan_product_f32(M, N, K, 1, ldp, ldq, false), 0);
   SPCA_LAUNCH_CHECK("gemm_nt_f32");
   return SPCA_OK;
 }
