@@ -6,24 +6,19 @@
 //   L1 penalty     x = V_g(v) / ||V_g(v)||             phi = ||V_g(v)||
 // followed by the ratio stop test of Section 2.2.
 //
-// Selection without a full sort.  The bit pattern of a non-negative float
-// is monotone in its value, so thresholds are searched over the 31-bit keys
-// of |v_i|.  Counting searches test kNC thresholds per step with wave
-// ballots (one compare and one scalar popcount per element and threshold),
-// a 16-ary search that needs 8 steps for 31 bits.
+// Selection without a sort.  The bit pattern of a non-negative float is
+// monotone in its value, so thresholds are searched over the 31-bit keys of
+// |v_i| by counting passes over register-resident rows.
 //   T_s       largest key t with #{key >= t} >= s; ties at that key go to the
 //             lowest indices (a block-wide prefix count finds the cut index).
 //   lambda_s  the derivative of l sqrt(s) + ||V_l(v)|| is sqrt(s) - rho(l)
 //             with rho = ||V_l||_1 / ||V_l||_2 non-increasing, so lambda = 0
-//             when rho(0) <= sqrt(s), and otherwise the root lies in the
-//             first segment [c_{k+1}, c_k] (k > s, c sorted descending) whose
-//             lower end already has rho >= sqrt(s), with the closed form
+//             when rho(0) <= sqrt(s), and otherwise the root on the k
+//             largest entries, where it keeps exactly those, is
 //             l = (S1_k - sqrt(s (k S2_k - S1_k^2) / (k - s))) / k.
-//             Fast path: the M largest |v_i| (M from the previous support
-//             size) are gathered, sorted in LDS and scanned for that segment,
-//             after checking rho >= sqrt(s) at their smallest key (so the
-//             root cannot lie below them).  Otherwise a search over keys with
-//             FP64 sums of (|v| - t)_+ and its square finds the float interval
+//             Rounds of that formula rise to the root from below; rows they
+//             do not settle (rounding; k <= s) take a search over keys with
+//             FP64 sums of (|v| - t)_+ and its square for the float interval
 //             holding the root, on which the active set is fixed.
 // Comparisons that decide membership use FP64 on the FP32 inputs (squares
 // and differences of floats are exact or correctly rounded there).
@@ -34,31 +29,13 @@
 namespace spca {
 namespace {
 
-constexpr int kXT = 1024;  // threads per start
-constexpr int kNW = kXT / kWave;
-constexpr int kNC = 15;    // thresholds per counting step (ballots)
 constexpr int kNCd = 7;    // thresholds per FP64 search step
-constexpr int kMaxCand = 2048;        // lambda_s candidates sorted in LDS
-constexpr int64_t kStageMax = 12288;  // p staged in LDS up to this size
 
 __device__ __forceinline__ uint32_t key_of(float v) {
   return __float_as_uint(v) & 0x7fffffffu;
 }
 
-struct XSmem {
-  double dred[2 * kNCd * (kNW + 1)];
-  int32_t ired[kNC * (kNW + 1)];
-  uint32_t ured[kNW + 1];
-  int scan[kNW + 1];
-  double dscan[2 * (kNW + 1)];
-  float cand[kMaxCand];
-  int ncand;
-  int kbest;
-  int64_t cut;
-  double seg[4];  // S1, S2, lower end, upper end of the chosen segment
-};
-
-// Thresholds strictly inside (lo, hi), spread evenly; unused slots get hi.
+// NC thresholds that split (lo, hi) evenly; hi stands for none.
 template <int NC>
 __device__ __forceinline__ void spread(uint32_t lo, uint32_t hi, uint32_t (&t)[NC]) {
   const uint32_t span = hi - lo;
@@ -71,492 +48,33 @@ __device__ __forceinline__ void spread(uint32_t lo, uint32_t hi, uint32_t (&t)[N
   }
 }
 
-// #{i : key_i >= t} for kNC thresholds, every thread gets the totals.
-template <typename ValF>
-__device__ __forceinline__ void count_ge(ValF val, int p, const uint32_t (&t)[kNC],
-                                         int (&cnt)[kNC], int32_t* ired) {
-  const int lane = threadIdx.x % kWave;
-  const int wave = threadIdx.x / kWave;
-#pragma unroll
-  for (int c = 0; c < kNC; ++c) cnt[c] = 0;
-  for (int base = wave * kWave; base < p; base += kXT) {
-    const int i = base + lane;
-    const uint32_t k = i < p ? key_of(val(i)) : 0u;
-#pragma unroll
-    for (int c = 0; c < kNC; ++c) cnt[c] += __popcll(__ballot(k >= t[c]));
-  }
-  if (lane == 0) {
-#pragma unroll
-    for (int c = 0; c < kNC; ++c) ired[wave * kNC + c] = cnt[c];
-  }
-  __syncthreads();
-  if (threadIdx.x < kNC) {
-    int a = 0;
-    for (int w = 0; w < kNW; ++w) a += ired[w * kNC + threadIdx.x];
-    ired[kNW * kNC + threadIdx.x] = a;
-  }
-  __syncthreads();
-#pragma unroll
-  for (int c = 0; c < kNC; ++c) cnt[c] = ired[kNW * kNC + c];
-  __syncthreads();
-}
-
-// Largest key t in [lo, hi) with #{key >= t} >= need, given that this holds
-// at lo and fails at hi.
-template <typename ValF>
-__device__ uint32_t search_count(ValF val, int p, uint32_t lo, uint32_t hi,
-                                 int64_t need, int32_t* ired) {
-  while (hi - lo > 1) {
-    uint32_t t[kNC];
-    spread<kNC>(lo, hi, t);
-    int cnt[kNC];
-    count_ge(val, p, t, cnt, ired);
-    uint32_t nlo = lo, nhi = hi;
-#pragma unroll
-    for (int c = 0; c < kNC; ++c) {
-      if (t[c] >= hi) continue;
-      if (cnt[c] >= need)
-        nlo = t[c] > nlo ? t[c] : nlo;
-      else
-        nhi = t[c] < nhi ? t[c] : nhi;
-    }
-    lo = nlo;
-    hi = nhi;
-  }
-  return lo;
-}
-
-__device__ __forceinline__ int count_ge1(uint32_t t, int p, const float* vs,
-                                         const float* vg, bool staged,
-                                         int32_t* ired) {
-  uint32_t tt[kNC];
-#pragma unroll
-  for (int c = 0; c < kNC; ++c) tt[c] = t;
-  int cnt[kNC];
-  auto val = [&](int i) -> float { return staged ? vs[i] : vg[i]; };
-  count_ge(val, p, tt, cnt, ired);
-  return cnt[0];
-}
-
-// Exclusive prefix sums of two doubles per thread in thread order.
-__device__ __forceinline__ void block_exclusive_scan2(double (&v)[2], double* scratch,
-                                                     double (&total)[2]) {
-  const int lane = threadIdx.x % kWave;
-  const int wave = threadIdx.x / kWave;
-  double inc[2] = {v[0], v[1]};
-#pragma unroll
-  for (int off = 1; off < kWave; off <<= 1) {
-#pragma unroll
-    for (int c = 0; c < 2; ++c) {
-      double o = __shfl_up(inc[c], off, kWave);
-      if (lane >= off) inc[c] += o;
-    }
-  }
-  if (lane == kWave - 1) {
-    scratch[2 * wave] = inc[0];
-    scratch[2 * wave + 1] = inc[1];
-  }
-  __syncthreads();
-  if (threadIdx.x == 0) {
-    double r0 = 0.0, r1 = 0.0;
-    for (int w = 0; w < kNW; ++w) {
-      double a = scratch[2 * w], b = scratch[2 * w + 1];
-      scratch[2 * w] = r0;
-      scratch[2 * w + 1] = r1;
-      r0 += a;
-      r1 += b;
-    }
-    scratch[2 * kNW] = r0;
-    scratch[2 * kNW + 1] = r1;
-  }
-  __syncthreads();
-  const double b0 = scratch[2 * wave], b1 = scratch[2 * wave + 1];
-  total[0] = scratch[2 * kNW];
-  total[1] = scratch[2 * kNW + 1];
-  v[0] = b0 + inc[0] - v[0];
-  v[1] = b1 + inc[1] - v[1];
-  __syncthreads();
-}
-
-template <int KIND, bool STAGED>
-__global__ __launch_bounds__(kXT) void x_update_kernel(
-    const float* __restrict__ V, int64_t ldv, int p, double param,
-    float* __restrict__ X, int64_t ldx, int32_t* __restrict__ list_idx,
-    float* __restrict__ list_val, int64_t ldl, int list_cap, StartState s,
-    double tol, int maxit, int32_t* __restrict__ colmark, const Plan* plan) {
-  extern __shared__ __attribute__((aligned(16))) float vstage[];
-  __shared__ XSmem sm;
-  const int64_t j = blockIdx.x;
-  const bool full = s.status != nullptr;
-  if (full && s.status[j] != kRunning) return;
-  if (s.cfg != nullptr) {  // grouped solve: this start's request
-    if (s.cfg[j].kind != KIND) return;
-    param = s.cfg[j].param;
-    tol = s.cfg[j].tol;
-    maxit = s.cfg[j].maxit;
-  }
-  const int tid = threadIdx.x;
-  const int lane = tid % kWave;
-  const float* vg = V + j * ldv;
-  if (STAGED) {
-    for (int i = tid; i < p; i += kXT) vstage[i] = vg[i];
-    __syncthreads();
-  }
-  auto val = [&](int i) -> float { return STAGED ? vstage[i] : vg[i]; };
-
-  const int chunk = (int)ceil_div(p, kXT);
-  const int cb = tid * chunk < p ? tid * chunk : p;
-  const int ce = cb + chunk < p ? cb + chunk : p;
-
-  // ---------------- threshold ----------------
-  uint32_t thr_key = 0;   // T_s: keys above are kept; equal keys up to cut
-  int64_t cut = -1;
-  double lam = 0.0;       // V_l: kept iff |v| > lam;  U_g: kept iff v^2 > g
-  if (KIND == kTopS || KIND == kLambdaS) {
-    uint32_t mk = 0;
-    for (int i = tid; i < p; i += kXT) {
-      uint32_t k = key_of(val(i));
-      mk = k > mk ? k : mk;
-    }
-    mk = block_max(mk, sm.ured);
-    const double s_par = param;
-    const double rs = sqrt(s_par);
-    if (KIND == kTopS) {
-      const int64_t s_int = (int64_t)s_par < (int64_t)p ? (int64_t)s_par : (int64_t)p;
-      // #{key >= 0} = p >= s and #{key >= mk + 1} = 0 < s
-      thr_key = search_count(val, p, 0u, mk + 1, s_int, sm.ired);
-      // ties at thr_key: keep the first (s - #{key > thr_key}) in index order
-      if (tid == 0) sm.cut = -1;
-      const int gt = count_ge1(thr_key + 1, p, vstage, vg, STAGED, sm.ired);
-      int eq = 0;
-      for (int i = cb; i < ce; ++i) eq += key_of(val(i)) == thr_key;
-      int eq_total;
-      int eq_off = block_exclusive_scan(eq, sm.scan, &eq_total);
-      const int need = (int)s_int - gt;  // >= 1
-      if (eq_off < need && need <= eq_off + eq) {
-        int seen = eq_off;
-        for (int i = cb; i < ce; ++i) {
-          if (key_of(val(i)) == thr_key) {
-            ++seen;
-            if (seen == need) {
-              sm.cut = i;
-              break;
-            }
-          }
-        }
-      }
-      __syncthreads();
-      cut = sm.cut;
-    }
-    if (KIND == kLambdaS) {
-      // constraint inactive when ||v||_1 <= sqrt(s) ||v||_2: lambda = 0
-      double a0[2] = {0.0, 0.0};
-      for (int i = tid; i < p; i += kXT) {
-        double a = fabs((double)val(i));
-        a0[0] += a;
-        a0[1] += a * a;
-      }
-      block_sum_n<double, 2>(a0, sm.dred);
-      const bool active = a0[0] > rs * sqrt(a0[1]);
-      bool done = !active;
-      if (active) {
-        // ---- fast path: the M largest entries ----
-        int64_t m0 = full ? 2 * (int64_t)s.nnz[j] + 32 : 4 * (int64_t)ceil(s_par) + 64;
-        const int64_t smin = (int64_t)floor(s_par) + 2;
-        m0 = m0 < smin ? smin : m0;
-        m0 = m0 > kMaxCand ? kMaxCand : m0;
-        m0 = m0 > p ? p : m0;
-        uint32_t t0 = search_count(val, p, 0u, mk + 1, m0, sm.ired);
-        t0 = t0 < 1u ? 1u : t0;  // zeros never enter
-        const double t0f = (double)__uint_as_float(t0);
-        double a1[2] = {0.0, 0.0};
-        int mine = 0;
-        for (int i = tid; i < p; i += kXT) {
-          double a = fabs((double)val(i));
-          if (key_of(val(i)) >= t0) ++mine;
-          double d = a - t0f;
-          d = d > 0.0 ? d : 0.0;
-          a1[0] += d;
-          a1[1] += d * d;
-        }
-        block_sum_n<double, 2>(a1, sm.dred);
-        const int ncand = block_sum(mine, sm.ired);
-        // rho(t0) >= sqrt(s): the root is >= t0 and only candidates matter
-        const bool ok = ncand <= kMaxCand && a1[1] > 0.0 && a1[0] >= rs * sqrt(a1[1]);
-        if (ok) {
-          if (tid == 0) sm.ncand = 0;
-          __syncthreads();
-          for (int base = (tid / kWave) * kWave; base < p; base += kXT) {
-            const int i = base + lane;
-            const float v = i < p ? val(i) : 0.f;
-            const bool in = i < p && key_of(v) >= t0;
-            const unsigned long long mask = __ballot(in);
-            int wbase = 0;
-            if (lane == 0 && mask) wbase = atomicAdd(&sm.ncand, (int)__popcll(mask));
-            wbase = __shfl(wbase, 0, kWave);
-            if (in) {
-              const unsigned long long below = mask & ((1ull << lane) - 1ull);
-              sm.cand[wbase + __popcll(below)] = fabsf(v);
-            }
-          }
-          __syncthreads();
-          int np2 = 2;
-          while (np2 < ncand) np2 <<= 1;
-          for (int i = ncand + tid; i < np2; i += kXT) sm.cand[i] = -1.f;
-          // bitonic sort, descending
-          for (int size = 2; size <= np2; size <<= 1) {
-            for (int stride = size >> 1; stride > 0; stride >>= 1) {
-              __syncthreads();
-              for (int t = tid; t < np2 / 2; t += kXT) {
-                const int pos = 2 * stride * (t / stride) + (t % stride);
-                const int partner = pos + stride;
-                const bool desc = (pos & size) == 0;
-                const float x0 = sm.cand[pos], x1 = sm.cand[partner];
-                if ((x0 < x1) == desc) {
-                  sm.cand[pos] = x1;
-                  sm.cand[partner] = x0;
-                }
-              }
-            }
-          }
-          __syncthreads();
-          // prefix sums of c and c^2; thread t owns sorted positions 2t, 2t+1
-          const int q0 = 2 * tid, q1 = 2 * tid + 1;
-          const double c0 = q0 < ncand ? (double)sm.cand[q0] : 0.0;
-          const double c1 = q1 < ncand ? (double)sm.cand[q1] : 0.0;
-          double pre[2] = {c0 + c1, c0 * c0 + c1 * c1};
-          double tot[2];
-          block_exclusive_scan2(pre, sm.dscan, tot);
-          if (tid == 0) sm.kbest = INT32_MAX;
-          __syncthreads();
-          double S1 = pre[0], S2 = pre[1];
-          int myk = INT32_MAX;
-          double seg[4] = {0, 0, 0, 0};
-          for (int e = 0; e < 2; ++e) {
-            const int q = q0 + e;
-            if (q >= ncand) break;
-            const double c = e == 0 ? c0 : c1;
-            S1 += c;
-            S2 += c * c;
-            const int k = q + 1;  // top-k prefix
-            if ((double)k <= s_par) continue;
-            const double lo = k < ncand ? (double)sm.cand[k] : t0f;
-            const double l1 = S1 - (double)k * lo;
-            const double l2 = S2 - 2.0 * lo * S1 + (double)k * lo * lo;
-            if (l2 > 0.0 && l1 >= rs * sqrt(l2) && k < myk) {
-              myk = k;
-              seg[0] = S1;
-              seg[1] = S2;
-              seg[2] = lo;
-              seg[3] = c;
-            }
-          }
-          if (myk != INT32_MAX) atomicMin(&sm.kbest, myk);
-          __syncthreads();
-          const int kb = sm.kbest;
-          if (myk == kb && kb != INT32_MAX) {
-            sm.seg[0] = seg[0];
-            sm.seg[1] = seg[1];
-            sm.seg[2] = seg[2];
-            sm.seg[3] = seg[3];
-          }
-          __syncthreads();
-          if (kb != INT32_MAX) {
-            const double k = (double)kb, S1b = sm.seg[0], S2b = sm.seg[1];
-            double disc = k * S2b - S1b * S1b;
-            disc = disc > 0.0 ? disc : 0.0;
-            double l = (S1b - sqrt(s_par * disc / (k - s_par))) / k;
-            l = l < sm.seg[2] ? sm.seg[2] : l;
-            l = l > sm.seg[3] ? sm.seg[3] : l;
-            lam = l;
-            done = true;
-          }
-          __syncthreads();
-        }
-      }
-      if (!done) {
-        // ---- fallback: FP64 search of the float interval holding the root ----
-        uint32_t lo = 0, hi = mk;  // rho(0) > sqrt(s); nothing exceeds mk
-        while (hi - lo > 1) {
-          uint32_t t[kNCd];
-          spread<kNCd>(lo, hi, t);
-          double acc[2 * kNCd];
-#pragma unroll
-          for (int c = 0; c < 2 * kNCd; ++c) acc[c] = 0.0;
-          double tf[kNCd];
-#pragma unroll
-          for (int c = 0; c < kNCd; ++c) tf[c] = (double)__uint_as_float(t[c]);
-          for (int i = tid; i < p; i += kXT) {
-            double a = fabs((double)val(i));
-#pragma unroll
-            for (int c = 0; c < kNCd; ++c) {
-              double d = a - tf[c];
-              d = d > 0.0 ? d : 0.0;
-              acc[2 * c] += d;
-              acc[2 * c + 1] += d * d;
-            }
-          }
-          block_sum_n<double, 2 * kNCd>(acc, sm.dred);
-          uint32_t nlo = lo, nhi = hi;
-#pragma unroll
-          for (int c = 0; c < kNCd; ++c) {
-            if (t[c] >= hi) continue;
-            bool pred = acc[2 * c + 1] > 0.0 && acc[2 * c] >= rs * sqrt(acc[2 * c + 1]);
-            if (pred)
-              nlo = t[c] > nlo ? t[c] : nlo;
-            else
-              nhi = t[c] < nhi ? t[c] : nhi;
-          }
-          lo = nlo;
-          hi = nhi;
-        }
-        const double tl = (double)__uint_as_float(lo);
-        const double th = (double)__uint_as_float(hi);
-        double ks[3] = {0.0, 0.0, 0.0};
-        for (int i = tid; i < p; i += kXT) {
-          double a = fabs((double)val(i));
-          if (a > tl) {
-            ks[0] += 1.0;
-            ks[1] += a;
-            ks[2] += a * a;
-          }
-        }
-        block_sum_n<double, 3>(ks, sm.dred);
-        const double k = ks[0], S1 = ks[1], S2 = ks[2];
-        double l = tl;
-        if (k > s_par) {
-          double disc = k * S2 - S1 * S1;
-          disc = disc > 0.0 ? disc : 0.0;
-          l = (S1 - sqrt(s_par * disc / (k - s_par))) / k;
-        }
-        l = l < tl ? tl : l;
-        l = l > th ? th : l;
-        lam = l;
-      }
-    }
-  } else {
-    lam = param;  // gamma
-  }
-
-  // keep test and kept value w_i for entry i
-  auto kept = [&](int i, float v, double* w) -> bool {
-    if (KIND == kTopS) {
-      uint32_t k = key_of(v);
-      *w = (double)v;
-      return k != 0 && (k > thr_key || (k == thr_key && (int64_t)i <= cut));
-    } else if (KIND == kHardGamma) {
-      *w = (double)v;
-      return (double)v * (double)v > lam;
-    } else {
-      double a = fabs((double)v);
-      *w = v > 0.f ? a - lam : lam - a;
-      return a > lam;
-    }
-  };
-
-  // ---------------- norms, phi and counts ----------------
-  int cnt = 0;
-  double acc[2] = {0.0, 0.0};  // sum w^2, sum (v^2 - g) over kept
-  for (int i = cb; i < ce; ++i) {
-    float v = val(i);
-    double w;
-    if (kept(i, v, &w)) {
-      ++cnt;
-      acc[0] += w * w;
-      if (KIND == kHardGamma) acc[1] += w * w - lam;
-    }
-  }
-  block_sum_n<double, 2>(acc, sm.dred);
-  int total;
-  int off = block_exclusive_scan(cnt, sm.scan, &total);
-  const double nrm = sqrt(acc[0]);
-  double phi;
-  if (KIND == kHardGamma)
-    phi = acc[1];
-  else if (KIND == kLambdaS)
-    phi = lam * sqrt(param) + nrm;
-  else
-    phi = nrm;
-  const bool zero = !(nrm > 0.0);
-  const double inv = zero ? 0.0 : 1.0 / nrm;
-
-  // ---------------- write x (list and dense row) ----------------
-  if (list_idx != nullptr && !zero && total <= list_cap) {
-    int32_t* li = list_idx + j * ldl;
-    float* lv = list_val + j * ldl;
-    for (int i = cb; i < ce; ++i) {
-      float v = val(i);
-      double w;
-      if (kept(i, v, &w)) {
-        li[off] = i;
-        lv[off] = (float)(w * inv);
-        ++off;
-      }
-    }
-  }
-  float* x = X + j * ldx;
-  const bool marking = colmark != nullptr && !zero && plan->mark != 0;
-  const int32_t epoch = marking ? plan->epoch : 0;
-  for (int i = tid; i < p; i += kXT) {
-    float v = val(i);
-    double w;
-    bool k = kept(i, v, &w);
-    x[i] = (k && !zero) ? (float)(w * inv) : 0.f;
-    if (k && marking) colmark[i] = epoch;
-  }
-
-  // ---------------- state and stop test (Section 2.2) ----------------
-  if (tid == 0) {
-    if (!full) {
-      // operator-only mode: phi and nnz are plain outputs in s.phi / s.nnz
-      s.phi[j] = phi;
-      s.nnz[j] = zero ? 0 : total;
-    } else {
-      const int it = s.iters[j] + 1;
-      const double prev = s.phi[j];
-      s.iters[j] = it;
-      s.phi_prev[j] = prev;
-      s.phi[j] = phi;
-      s.nnz[j] = zero ? 0 : total;
-      if (zero)
-        s.status[j] = SPCA_ZERO;
-      else if (it >= 2 && tol >= 0.0 && phi <= (1.0 + tol) * prev)
-        s.status[j] = SPCA_CONVERGED;
-      else if (it >= maxit)
-        s.status[j] = SPCA_MAXIT;
-    }
-  }
-}
-
-
 // ---------------------------------------------------------------------------
-// Register-resident variant for p <= 256 * NPT.  A 256-thread block per
-// start, thread t holding the contiguous entries [t NPT, (t+1) NPT) of the
-// row (16-byte loads), so that every pass is register arithmetic, index
-// order is thread order for the prefix counts, and all starts of a batch
-// are resident on the chip at once.  Keys are selected by radix select:
-// three histogram passes over 11, 11 and 9 bits of the 31-bit key with
-// integer LDS atomics (exact and order-independent).
+// Register-resident rows, p <= 256 * NPT: a 256-thread block per start, so
+// that every pass is register arithmetic and all starts of a batch are
+// resident on the chip at once (1024 x 10000: 4 blocks a CU).  Reading V and
+// writing X, 82 MB there, takes 18 us of the 42 us of T_s and 53 us of
+// lambda_s; the rest is the passes and their barriers, which all blocks go
+// through in step.  Before, with three LDS histograms a selection and a sort
+// of lambda_s candidates, 53 and 232 us.
 // ---------------------------------------------------------------------------
-typedef float floatx4 __attribute__((ext_vector_type(4)));
+// Four floats of a row, loaded and stored with one 16-byte instruction: global
+// memory asks for 4-byte alignment only, so rows of any leading dimension
+// and offset take it (900 x 12285: T_s 54 us, lambda_s 59, U_g 21; one
+// 1024-thread workgroup a row from LDS took 290, 712 and 28).
+typedef float floatx4 __attribute__((ext_vector_type(4), aligned(4)));
 
 constexpr int kRT = 256;  // threads per start
 constexpr int kRW = kRT / kWave;
-constexpr int kBins = 2048;
+constexpr int kSelPer = 4;
+constexpr int kSelCap = kSelPer * kRT;  // entries that a selection goes on with alone
+constexpr int kLamRoundsFull = 40;  // closed-form rounds of lambda_s from the whole row
 
 struct RSmem {
-  uint32_t hist[kBins];
   double dred[2 * kNCd * (kRW + 1)];
-  int32_t ired[16 * (kRW + 1)];
-  uint32_t ured[kRW + 1];
+  uint32_t ured[2 * kRW];
   int scan[kRW + 1];
-  double dscan[2 * (kRW + 1)];
-  float cand[kMaxCand];
-  int ncand;
-  int kbest;
+  float cand[kSelCap];
   int64_t cut;
-  uint32_t sel[2];  // selected bin, count above it
-  double seg[4];
   uint64_t pscan[3 * (kRW + 1)];  // packed per-row counts (rank_rows)
 };
 
@@ -644,74 +162,171 @@ __device__ __forceinline__ void rscan2(double (&v)[2], double* scratch) {
   __syncthreads();
 }
 
-// The need-th largest key (1 <= need <= number of entries) and the number of
-// keys strictly above it.  Entries beyond p are zero keys.
 // Marks a register value as changed, so that the compiler recomputes what
 // it derives from it (keys, bins) instead of holding copies across passes.
 __device__ __forceinline__ void reload(float& x) { asm volatile("" : "+v"(x)); }
 
-template <int NPT>
-__device__ void radix_select(float (&v)[NPT], uint32_t need, RSmem& sm,
-                             uint32_t* key_out, uint32_t* above_out) {
-  const int tid = threadIdx.x;
-  uint32_t prefix = 0;      // selected high bits so far
-  uint32_t above = 0;       // keys strictly above the selected prefix range
-  // (shift, bits) of the three passes over the 31-bit key
-  const int shifts[3] = {20, 9, 0};
-  const int widths[3] = {11, 11, 9};
-#pragma unroll 1
-  for (int pass = 0; pass < 3; ++pass) {
-    const int sh = shifts[pass];
-    const uint32_t nb = 1u << widths[pass];
-    const uint32_t hi_mask = pass == 0 ? 0u : (0x7fffffffu >> (sh + widths[pass])) << (sh + widths[pass]);
-    for (int i = tid; i < kBins; i += kRT) sm.hist[i] = 0u;
-    __syncthreads();
+// Number of the block's entries with |v| at or above the float of key t; one
+// compare an entry and one barrier a call (parity: consecutive calls alternate
+// it, so that a wave may write its count while another still reads the last).
+template <int N>
+__device__ __forceinline__ uint32_t count_from(float (&v)[N], uint32_t t, uint32_t parity,
+                                               uint32_t* scratch) {
+  const float f = __uint_as_float(t);
+  uint32_t n = 0;
 #pragma unroll
-    for (int k = 0; k < NPT; ++k) {
-      reload(v[k]);
-      const uint32_t key = key_of(v[k]);
-      if ((key & hi_mask) == prefix) atomicAdd(&sm.hist[(key >> sh) & (nb - 1)], 1u);
-    }
-    __syncthreads();
-    // bins from the top: thread t owns bins nb-1-8t .. nb-8-8t
-    constexpr int kPer = kBins / kRT;  // 8
-    uint32_t local = 0;
-    int first = (int)nb - 1 - kPer * tid;
-#pragma unroll
-    for (int q = 0; q < kPer; ++q) {
-      int bin = first - q;
-      local += bin >= 0 ? sm.hist[bin] : 0u;
-    }
-    int total;
-    const uint32_t before = (uint32_t)block_exclusive_scan((int)local, sm.scan, &total);
-    const uint32_t rem = need - above;
-    if (before < rem && rem <= before + local) {
-      uint32_t run = before;
-#pragma unroll
-      for (int q = 0; q < kPer; ++q) {
-        int bin = first - q;
-        uint32_t h = bin >= 0 ? sm.hist[bin] : 0u;
-        if (run < rem && rem <= run + h) {
-          sm.sel[0] = (uint32_t)bin;
-          sm.sel[1] = run;
-        }
-        run += h;
-      }
-    }
-    __syncthreads();
-    prefix |= sm.sel[0] << sh;
-    above += sm.sel[1];
-    __syncthreads();
+  for (int k = 0; k < N; ++k) {
+    reload(v[k]);
+    n += (uint32_t)__popcll(__ballot(fabsf(v[k]) >= f));
   }
-  *key_out = prefix;
-  *above_out = above;
+  uint32_t* c = scratch + kRW * parity;
+  if (threadIdx.x % kWave == 0) c[threadIdx.x / kWave] = n;
+  __syncthreads();
+  n = 0;
+#pragma unroll
+  for (int w = 0; w < kRW; ++w) n += c[w];
+  return n;
 }
 
-// Register budget: the top-s kernel keeps its keys live across the radix
-// passes and is left at 2 waves per SIMD; the others fit 4.
+// Compacts the entries with |v| >= f, at most kSelCap, into LDS in thread
+// order and deals them out again, kSelPer a thread (zeros beyond them).
+template <int NPT>
+__device__ __forceinline__ void compact(float (&v)[NPT], float f, RSmem& sm,
+                                        float (&c)[kSelPer]) {
+  int mine = 0;
+#pragma unroll
+  for (int k = 0; k < NPT; ++k) mine += fabsf(v[k]) >= f;
+  int n;
+  int off = block_exclusive_scan(mine, sm.scan, &n);
+#pragma unroll
+  for (int k = 0; k < NPT; ++k) {
+    reload(v[k]);  // compare again rather than hold the masks
+    if (fabsf(v[k]) >= f) sm.cand[off++] = fabsf(v[k]);
+  }
+  __syncthreads();
+#pragma unroll
+  for (int e = 0; e < kSelPer; ++e) {
+    const int i = threadIdx.x + e * kRT;
+    c[e] = i < n ? sm.cand[i] : 0.f;
+  }
+}
+
+// A threshold that about `want` of a row's p entries exceed if the row is
+// Gaussian with the sum of squares sq (asymptotic tail quantile): where the
+// searches below start.  Any value is a valid start.
+__device__ __forceinline__ float tail_guess(float sq, int p, float want) {
+  const float q = logf(fmaxf((float)p / want, 1.05f));
+  const float z = q > 1.f ? sqrtf(2.f * q - logf(3.f * q)) : 0.95f * q;
+  return sqrtf(sq / (float)p) * z;
+}
+
+// The need-th largest key (1 <= need <= p) and the number of keys from it on
+// and strictly above it: the bracket #{key >= lo} >= need > #{key >= hi} is halved in key
+// space (a float's bits are monotone and about logarithmic in it) by counting
+// passes over the registers, from a start by tail_guess; once at most kSelCap
+// entries lie above lo, over those alone.  Counting takes one compare an
+// entry, where a histogram of the key's bits takes an LDS atomic, most of
+// them on the few bins that hold most of a row.
+template <int NPT>
+__device__ void select_key(float (&v)[NPT], int p, uint32_t need, RSmem& sm,
+                           uint32_t* key_out, uint32_t* from_out, uint32_t* above_out) {
+  float sq = 0.f;
+  uint32_t mk = 0;
+#pragma unroll
+  for (int k = 0; k < NPT; ++k) {
+    const uint32_t key = key_of(v[k]);
+    mk = key > mk ? key : mk;
+    sq += v[k] * v[k];
+  }
+  sq = block_sum(sq, reinterpret_cast<float*>(sm.dred));
+  mk = block_max(mk, sm.ured);
+  uint32_t lo = 0u, hi = mk + 1u, nlo = (uint32_t)p, nhi = 0u, parity = 0u;
+  uint32_t t = key_of(tail_guess(sq, p, 1.4f * (float)need + 16.f));
+  uint32_t step = 1u << 21;  // a quarter of a binade: brackets a start that is nearly right
+  bool first = true, down = false;
+  while (hi - lo > 1u && nlo > (uint32_t)kSelCap) {
+    if (!(t > lo && t < hi)) t = lo + (hi - lo) / 2u;
+    const uint32_t n = count_from(v, t, parity, sm.ured);
+    parity ^= 1u;
+    const bool in = n >= need;
+    if (in) {
+      lo = t;
+      nlo = n;
+    } else {
+      hi = t;
+      nhi = n;
+    }
+    // steps in one direction double; the first turn brackets the threshold
+    const bool turned = !first && down == in;
+    first = false;
+    down = !in;
+    if (turned) step = 0u;
+    t = step == 0u ? 0u : (in ? t + step : (t > step ? t - step : 0u));
+    step *= 2u;
+  }
+  if (hi - lo > 1u && lo > 0u) {
+    float c[kSelPer];
+    compact(v, __uint_as_float(lo), sm, c);
+    while (hi - lo > 1u) {
+      t = lo + (hi - lo) / 2u;
+      const uint32_t n = count_from(c, t, parity, sm.ured);
+      parity ^= 1u;
+      if (n >= need) {
+        lo = t;
+        nlo = n;
+      } else {
+        hi = t;
+        nhi = n;
+      }
+    }
+  }
+  while (hi - lo > 1u) {  // rows of at most kSelCap entries
+    t = lo + (hi - lo) / 2u;
+    const uint32_t n = count_from(v, t, parity, sm.ured);
+    parity ^= 1u;
+    if (n >= need) {
+      lo = t;
+      nlo = n;
+    } else {
+      hi = t;
+      nhi = n;
+    }
+  }
+  *key_out = lo;
+  *from_out = nlo;
+  *above_out = nhi;
+}
+
+// The smallest float above l >= 0: |v| >= float_above(l) is |v| > l.
+__device__ __forceinline__ float float_above(double l) {
+  const float f = (float)l;
+  if (!((double)f <= l)) return f;
+  return f == 0.f ? __uint_as_float(1u) : __uint_as_float(__float_as_uint(f) + 1u);
+}
+
+// Count, sum and sum of squares of the entries with |v| >= f.
+template <int N>
+__device__ __forceinline__ void sums_from(float (&v)[N], float f, double (&b)[3],
+                                          double* scratch) {
+  int n = 0;
+  b[1] = b[2] = 0.0;
+#pragma unroll
+  for (int k = 0; k < N; ++k) {
+    if (k % 4 == 0) __builtin_amdgcn_sched_barrier(0);  // few conversions live at once
+    reload(v[k]);
+    const bool in = fabsf(v[k]) >= f;
+    n += in;
+    const double a = (double)(in ? fabsf(v[k]) : 0.f);
+    b[1] += a;
+    b[2] += a * a;
+  }
+  b[0] = (double)n;
+  block_sum_n<double, 3>(b, scratch);
+}
+
 // WARM: the sparsity-targeted warm-up (Section 4.1) of the parameter.
 template <int KIND, int NPT, bool WARM>
-__global__ __launch_bounds__(kRT, (KIND == kTopS || WARM) ? 2 : 4) void x_update_reg_kernel(
+__global__ __launch_bounds__(kRT, WARM ? 2 : 4) void x_update_reg_kernel(
     const float* __restrict__ V, int64_t ldv, int p, double param,
     float* __restrict__ X, int64_t ldx, int32_t* __restrict__ list_idx,
     float* __restrict__ list_val, int64_t ldl, int list_cap, StartState s,
@@ -760,171 +375,95 @@ __global__ __launch_bounds__(kRT, (KIND == kTopS || WARM) ? 2 : 4) void x_update
   const bool warming = WARM && itc <= wm.K;
   if (KIND == kTopS) {
     const uint32_t s_int = (uint32_t)((int64_t)param < (int64_t)p ? (int64_t)param : (int64_t)p);
-    uint32_t above;
-    radix_select<NPT>(v, s_int, sm, &thr_key, &above);
-    // ties at thr_key: keep the first (s - #{key > thr_key}) in index order
-    if (tid == 0) sm.cut = -1;
-    int eq[R], eq_base[R];
-#pragma unroll
-    for (int q = 0; q < R; ++q) {
-      eq[q] = 0;
-#pragma unroll
-      for (int e = 0; e < 4; ++e) {
-        reload(v[4 * q + e]);
-        eq[q] += key_of(v[4 * q + e]) == thr_key && gidx(4 * q + e) < p;
+    uint32_t from, above;
+    select_key<NPT>(v, p, s_int, sm, &thr_key, &from, &above);
+    cut = p;
+    if (thr_key != 0u && from > s_int) {
+      // ties at thr_key: keep the first (s - #{key > thr_key}) in index
+      // order; rare, so from memory, a run of the row a thread
+      const int need = (int)(s_int - above);
+      const int run = (p + kRT - 1) / kRT;
+      const int i0 = run * tid, i1 = i0 + run < p ? i0 + run : p;
+      int eq = 0, total_eq;
+#pragma unroll 1
+      for (int i = i0; i < i1; ++i) eq += key_of(vg[i]) == thr_key;
+      int seen = block_exclusive_scan(eq, sm.scan, &total_eq);
+      if (tid == 0) sm.cut = -1;
+      __syncthreads();
+      if (seen < need && need <= seen + eq) {
+#pragma unroll 1
+        for (int i = i0; i < i1; ++i)
+          if (key_of(vg[i]) == thr_key && ++seen == need) sm.cut = i;
       }
+      __syncthreads();
+      cut = sm.cut;
     }
-    rank_rows<R>(eq, eq_base, sm.pscan);
-    const int need = (int)s_int - (int)above;  // >= 1
-#pragma unroll
-    for (int q = 0; q < R; ++q) {
-      int seen = eq_base[q];
-#pragma unroll
-      for (int e = 0; e < 4; ++e) {
-        const int k = 4 * q + e;
-        if (key_of(v[k]) == thr_key && gidx(k) < p) {
-          ++seen;
-          if (seen == need) sm.cut = gidx(k);
-        }
-      }
-    }
-    __syncthreads();
-    cut = sm.cut;
   } else if (KIND == kLambdaS && WARM && !warming) {
     lam = wm.gam[j];  // frozen after the warm-up
   } else if (KIND == kLambdaS) {
+    // The root on a set S of entries, l = (S1 - sqrt(s (k S2 - S1^2) /
+    // (k - s))) / k with k = |S|, S1 = sum |v|, S2 = sum v^2 over S, lies at
+    // or below the row's while S holds every entry above that one (entries
+    // below l only lower the sum and raise the norm).  So each round takes S
+    // to {|v| > l}, and l rises to the row's root, reached when S no longer
+    // changes.  S begins as {|v| >= t} if rho(t) > sqrt(s) there, which
+    // places the root above t (t: about 6 s entries of a Gaussian row; 2 s
+    // are kept), else as all nonzero entries; from kSelCap entries on the
+    // rounds run over those alone, about eight of them.
     const double s_par = param;
     const double rs = sqrt(s_par);
-    double a0[2] = {0.0, 0.0};
+    float sq = 0.f;
     uint32_t mk = 0;
 #pragma unroll
     for (int k = 0; k < NPT; ++k) {
-      double a = fabs((double)v[k]);
-      a0[0] += a;
-      a0[1] += a * a;
-      uint32_t key = key_of(v[k]);
+      const uint32_t key = key_of(v[k]);
       mk = key > mk ? key : mk;
+      sq += v[k] * v[k];
     }
-    block_sum_n<double, 2>(a0, sm.dred);
-    const bool active = a0[0] > rs * sqrt(a0[1]);
+    sq = block_sum(sq, reinterpret_cast<float*>(sm.dred));
+    mk = block_max(mk, sm.ured);
+    float f = tail_guess(sq, p, (float)(6.0 * s_par));
+    double set3[3] = {0.0, 0.0, 0.0};
+    bool active = false;
+    if (f > 0.f && 12.0 * s_par < (double)p) {
+      sums_from<NPT>(v, f, set3, sm.dred);
+      lam = (double)f;
+      const double l1 = set3[1] - set3[0] * lam;
+      const double l2 = set3[2] - 2.0 * lam * set3[1] + set3[0] * lam * lam;
+      active = l2 > 1e-12 * set3[2] && l1 > (1.0 + 1e-9) * rs * sqrt(l2);
+    }
+    if (!active) {
+      lam = 0.0;
+      f = __uint_as_float(1u);
+      sums_from<NPT>(v, f, set3, sm.dred);
+      active = set3[1] > rs * sqrt(set3[2]);
+    }
     bool done = !active;
     if (active) {
-      mk = block_max(mk, sm.ured);
-      int64_t m0 = full ? 2 * (int64_t)s.nnz[j] + 32 : 4 * (int64_t)ceil(s_par) + 64;
-      const int64_t smin = (int64_t)floor(s_par) + 2;
-      m0 = m0 < smin ? smin : m0;
-      m0 = m0 > kMaxCand ? kMaxCand : m0;
-      m0 = m0 > p ? p : m0;
-      uint32_t t0, above0;
-      radix_select<NPT>(v, (uint32_t)m0, sm, &t0, &above0);
-      t0 = t0 < 1u ? 1u : t0;  // zeros never enter
-      const double t0f = (double)__uint_as_float(t0);
-      double a1[2] = {0.0, 0.0};
-      int mine = 0;
-#pragma unroll
-      for (int k = 0; k < NPT; ++k) {
-        mine += key_of(v[k]) >= t0;
-        double d = fabs((double)v[k]) - t0f;
-        d = d > 0.0 ? d : 0.0;
-        a1[0] += d;
-        a1[1] += d * d;
-      }
-      block_sum_n<double, 2>(a1, sm.dred);
-      const int ncand = block_sum(mine, sm.ired);
-      // rho(t0) >= sqrt(s): the root is >= t0 and only candidates matter
-      const bool ok = ncand <= kMaxCand && a1[1] > 0.0 && a1[0] >= rs * sqrt(a1[1]);
-      if (ok) {
-        if (tid == 0) sm.ncand = 0;
-        __syncthreads();
-#pragma unroll
-        for (int k = 0; k < NPT; ++k) {
-          const bool in = key_of(v[k]) >= t0;
-          const unsigned long long mask = __ballot(in);
-          int wbase = 0;
-          if (lane == 0 && mask) wbase = atomicAdd(&sm.ncand, (int)__popcll(mask));
-          wbase = __shfl(wbase, 0, kWave);
-          if (in) {
-            const unsigned long long below = mask & ((1ull << lane) - 1ull);
-            sm.cand[wbase + __popcll(below)] = fabsf(v[k]);
-          }
+      float c[kSelPer];
+      bool few = false;
+#pragma unroll 1
+      for (int round = 0; round < kLamRoundsFull; ++round) {
+        const double kk = set3[0];
+        if (!(kk > s_par)) break;
+        double disc = kk * set3[2] - set3[1] * set3[1];
+        disc = disc > 0.0 ? disc : 0.0;
+        const double l = (set3[1] - sqrt(s_par * disc / (kk - s_par))) / kk;
+        if (!(l > lam)) break;  // rounding: left to the search below
+        if (!few && kk <= (double)kSelCap) {
+          compact(v, f, sm, c);
+          few = true;
         }
-        __syncthreads();
-        int np2 = 2;
-        while (np2 < ncand) np2 <<= 1;
-        for (int i = ncand + tid; i < np2; i += kRT) sm.cand[i] = -1.f;
-        // bitonic sort, descending
-        for (int size = 2; size <= np2; size <<= 1) {
-          for (int stride = size >> 1; stride > 0; stride >>= 1) {
-            __syncthreads();
-            for (int t = tid; t < np2 / 2; t += kRT) {
-              const int pos = 2 * stride * (t / stride) + (t % stride);
-              const int partner = pos + stride;
-              const bool desc = (pos & size) == 0;
-              const float x0 = sm.cand[pos], x1 = sm.cand[partner];
-              if ((x0 < x1) == desc) {
-                sm.cand[pos] = x1;
-                sm.cand[partner] = x0;
-              }
-            }
-          }
-        }
-        __syncthreads();
-        // prefix sums of c and c^2; thread t owns sorted positions [8t, 8t+8)
-        constexpr int kCP = kMaxCand / kRT;
-        double cv[kCP];
-        double pre[2] = {0.0, 0.0};
-#pragma unroll
-        for (int e = 0; e < kCP; ++e) {
-          const int q = kCP * tid + e;
-          cv[e] = q < ncand ? (double)sm.cand[q] : 0.0;
-          pre[0] += cv[e];
-          pre[1] += cv[e] * cv[e];
-        }
-        rscan2(pre, sm.dscan);
-        if (tid == 0) sm.kbest = INT32_MAX;
-        __syncthreads();
-        double S1 = pre[0], S2 = pre[1];
-        int myk = INT32_MAX;
-        double seg[4] = {0, 0, 0, 0};
-#pragma unroll
-        for (int e = 0; e < kCP; ++e) {
-          const int q = kCP * tid + e;
-          S1 += cv[e];
-          S2 += cv[e] * cv[e];
-          const int k = q + 1;  // top-k prefix
-          if (q >= ncand || (double)k <= s_par || myk != INT32_MAX) continue;
-          const double lo = k < ncand ? (double)sm.cand[k] : t0f;
-          const double l1 = S1 - (double)k * lo;
-          const double l2 = S2 - 2.0 * lo * S1 + (double)k * lo * lo;
-          if (l2 > 0.0 && l1 >= rs * sqrt(l2)) {
-            myk = k;
-            seg[0] = S1;
-            seg[1] = S2;
-            seg[2] = lo;
-            seg[3] = cv[e];
-          }
-        }
-        if (myk != INT32_MAX) atomicMin(&sm.kbest, myk);
-        __syncthreads();
-        const int kb = sm.kbest;
-        if (myk == kb && kb != INT32_MAX) {
-          sm.seg[0] = seg[0];
-          sm.seg[1] = seg[1];
-          sm.seg[2] = seg[2];
-          sm.seg[3] = seg[3];
-        }
-        __syncthreads();
-        if (kb != INT32_MAX) {
-          const double k = (double)kb, S1b = sm.seg[0], S2b = sm.seg[1];
-          double disc = k * S2b - S1b * S1b;
-          disc = disc > 0.0 ? disc : 0.0;
-          double l = (S1b - sqrt(s_par * disc / (k - s_par))) / k;
-          l = l < sm.seg[2] ? sm.seg[2] : l;
-          l = l > sm.seg[3] ? sm.seg[3] : l;
-          lam = l;
+        f = float_above(l);
+        if (few)
+          sums_from<kSelPer>(c, f, set3, sm.dred);
+        else
+          sums_from<NPT>(v, f, set3, sm.dred);
+        lam = l;
+        if (set3[0] == kk) {  // nested sets of equal size: unchanged
           done = true;
+          break;
         }
-        __syncthreads();
       }
     }
     if (!done) {
@@ -995,8 +534,8 @@ __global__ __launch_bounds__(kRT, (KIND == kTopS || WARM) ? 2 : 4) void x_update
     if ((int64_t)wm.target >= (int64_t)p) {
       lam = 0.0;
     } else {
-      uint32_t tk, above;
-      radix_select<NPT>(v, (uint32_t)wm.target + 1u, sm, &tk, &above);
+      uint32_t tk, from, above;
+      select_key<NPT>(v, p, (uint32_t)wm.target + 1u, sm, &tk, &from, &above);
       const double t = (double)__uint_as_float(tk);
       lam = KIND == kHardGamma ? t * t : t;
     }
@@ -1006,6 +545,7 @@ __global__ __launch_bounds__(kRT, (KIND == kTopS || WARM) ? 2 : 4) void x_update
     lam = param;
   }
 
+  const float lamf = float_above(lam);
   auto kept = [&](int i, float vv, double* w) -> bool {
     if (KIND == kTopS) {
       uint32_t k = key_of(vv);
@@ -1017,7 +557,7 @@ __global__ __launch_bounds__(kRT, (KIND == kTopS || WARM) ? 2 : 4) void x_update
     } else {
       double a = fabs((double)vv);
       *w = vv > 0.f ? a - lam : lam - a;
-      return a > lam;
+      return fabsf(vv) >= lamf;
     }
   };
 
@@ -1026,6 +566,7 @@ __global__ __launch_bounds__(kRT, (KIND == kTopS || WARM) ? 2 : 4) void x_update
 #pragma unroll
   for (int q = 0; q < R; ++q) {
     cnt[q] = 0;
+    if (q % 2 == 0) __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
     for (int e = 0; e < 4; ++e) {
       const int k = 4 * q + e;
@@ -1717,34 +1258,19 @@ void launch_kind(hipStream_t st, double param, const float* V, int64_t ldv,
                  int64_t r, int64_t p, float* X, int64_t ldx, int32_t* li,
                  float* lv, int64_t ldl, int list_cap, StartState s, double tol,
                  int maxit, int32_t* colmark, const Plan* plan, Warm wm) {
-  const bool aligned = ldv % 4 == 0 && ldx % 4 == 0 &&
-                       (uintptr_t)V % 16 == 0 && (uintptr_t)X % 16 == 0;
   const int64_t per = ceil_div(p, kRT);
-  if (aligned && per <= 48) {
-    if (per <= 8)
-      launch_reg<KIND, 8>(st, param, V, ldv, r, p, X, ldx, li, lv, ldl, list_cap, s, tol, maxit, colmark, plan, wm);
-    else if (per <= 16)
-      launch_reg<KIND, 16>(st, param, V, ldv, r, p, X, ldx, li, lv, ldl, list_cap, s, tol, maxit, colmark, plan, wm);
-    else if (per <= 24)
-      launch_reg<KIND, 24>(st, param, V, ldv, r, p, X, ldx, li, lv, ldl, list_cap, s, tol, maxit, colmark, plan, wm);
-    else if (per <= 32)
-      launch_reg<KIND, 32>(st, param, V, ldv, r, p, X, ldx, li, lv, ldl, list_cap, s, tol, maxit, colmark, plan, wm);
-    else if (per <= 40)
-      launch_reg<KIND, 40>(st, param, V, ldv, r, p, X, ldx, li, lv, ldl, list_cap, s, tol, maxit, colmark, plan, wm);
-    else
-      launch_reg<KIND, 48>(st, param, V, ldv, r, p, X, ldx, li, lv, ldl, list_cap, s, tol, maxit, colmark, plan, wm);
-    return;
-  }
-  if (p <= kStageMax) {
-    size_t shm = (size_t)p * sizeof(float);
-    hipLaunchKernelGGL((x_update_kernel<KIND, true>), dim3((unsigned)r),
-                       dim3(kXT), shm, st, V, ldv, (int)p, param, X, ldx, li,
-                       lv, ldl, list_cap, s, tol, maxit, colmark, plan);
-  } else {
-    hipLaunchKernelGGL((x_update_kernel<KIND, false>), dim3((unsigned)r),
-                       dim3(kXT), 0, st, V, ldv, (int)p, param, X, ldx, li, lv,
-                       ldl, list_cap, s, tol, maxit, colmark, plan);
-  }
+  if (per <= 8)
+    launch_reg<KIND, 8>(st, param, V, ldv, r, p, X, ldx, li, lv, ldl, list_cap, s, tol, maxit, colmark, plan, wm);
+  else if (per <= 16)
+    launch_reg<KIND, 16>(st, param, V, ldv, r, p, X, ldx, li, lv, ldl, list_cap, s, tol, maxit, colmark, plan, wm);
+  else if (per <= 24)
+    launch_reg<KIND, 24>(st, param, V, ldv, r, p, X, ldx, li, lv, ldl, list_cap, s, tol, maxit, colmark, plan, wm);
+  else if (per <= 32)
+    launch_reg<KIND, 32>(st, param, V, ldv, r, p, X, ldx, li, lv, ldl, list_cap, s, tol, maxit, colmark, plan, wm);
+  else if (per <= 40)
+    launch_reg<KIND, 40>(st, param, V, ldv, r, p, X, ldx, li, lv, ldl, list_cap, s, tol, maxit, colmark, plan, wm);
+  else if (per <= 48)
+    launch_reg<KIND, 48>(st, param, V, ldv, r, p, X, ldx, li, lv, ldl, list_cap, s, tol, maxit, colmark, plan, wm);
 }
 
 }  // namespace

@@ -40,7 +40,8 @@ constexpr int kNWv = kWT / kWave;
 constexpr int kMaxCandW = 2048;       // lambda_s candidates sorted per row
 constexpr int kNCdW = 7;              // thresholds per FP64 search step
 
-typedef float floatx4 __attribute__((ext_vector_type(4)));
+// rows of any leading dimension: 16-byte accesses need 4-byte alignment only
+typedef float floatx4 __attribute__((ext_vector_type(4), aligned(4)));
 
 struct WRow {
   uint32_t prefix;   // key bits fixed so far (the full key after pass 3)
@@ -138,13 +139,14 @@ __global__ __launch_bounds__(kWT) void wide_hist_kernel(
     const float* __restrict__ V, int64_t ldv, int p, StartState s, Wide w) {
   using D = Digit<PASS>;
   __shared__ uint32_t lh[D::kBins];
-  const int64_t j = blockIdx.y;
+  const int64_t j = blockIdx.x / w.nch;
+  const int chunk = blockIdx.x % w.nch;
   if (!row_live(s, j)) return;
   const int tid = threadIdx.x;
   for (int b = tid; b < D::kBins; b += kWT) lh[b] = 0u;
   const uint32_t prefix = PASS == 0 ? 0u : w.rows[j].prefix;
   __syncthreads();
-  const int base = blockIdx.x * kWCH + tid * kWN;
+  const int base = chunk * kWCH + tid * kWN;
   float v[kWN];
   load_chunk(V + j * ldv, p, base, v);
 #pragma unroll
@@ -220,17 +222,18 @@ __global__ __launch_bounds__(kWT) void wide_decide_kernel(StartState s, Wide w,
 __global__ __launch_bounds__(kWT) void wide_eqcount_kernel(
     const float* __restrict__ V, int64_t ldv, int p, StartState s, Wide w) {
   __shared__ int red[kNWv + 1];
-  const int64_t j = blockIdx.y;
+  const int64_t j = blockIdx.x / w.nch;
+  const int chunk = blockIdx.x % w.nch;
   if (!row_live(s, j) || !w.rows[j].straddle) return;
   const uint32_t t = w.rows[j].prefix;
-  const int base = blockIdx.x * kWCH + threadIdx.x * kWN;
+  const int base = chunk * kWCH + threadIdx.x * kWN;
   float v[kWN];
   load_chunk(V + j * ldv, p, base, v);
   int eq = 0;
 #pragma unroll
   for (int k = 0; k < kWN; ++k) eq += base + k < p && wkey(v[k]) == t;
   eq = block_sum(eq, red);
-  if (threadIdx.x == 0) w.eqcnt[j * w.nch + blockIdx.x] = eq;
+  if (threadIdx.x == 0) w.eqcnt[j * w.nch + chunk] = eq;
 }
 
 // Membership and value of each element of the thread's slice.  For T_s the
@@ -252,7 +255,7 @@ struct Keep {
       need = R.need;
       if (straddle) {
         int before = 0;
-        for (int c = threadIdx.x; c < (int)blockIdx.x; c += kWT)
+        for (int c = threadIdx.x; c < (int)(blockIdx.x % w.nch); c += kWT)
           before += w.eqcnt[j * w.nch + c];
         before = block_sum(before, red);
         int eq = 0;
@@ -295,9 +298,10 @@ __global__ __launch_bounds__(kWT) void wide_partial_kernel(
   __shared__ int scan[kNWv + 1];
   __shared__ int red[kNWv + 1];
   __shared__ double dred[2 * (kNWv + 1)];
-  const int64_t j = blockIdx.y;
+  const int64_t j = blockIdx.x / w.nch;
+  const int chunk = blockIdx.x % w.nch;
   if (!row_live(s, j)) return;
-  const int base = blockIdx.x * kWCH + threadIdx.x * kWN;
+  const int base = chunk * kWCH + threadIdx.x * kWN;
   float v[kWN];
   load_chunk(V + j * ldv, p, base, v);
   Keep<KIND> keep;
@@ -316,7 +320,7 @@ __global__ __launch_bounds__(kWT) void wide_partial_kernel(
   block_sum_n<double, 2>(acc, dred);
   cnt = block_sum(cnt, red);
   if (threadIdx.x == 0) {
-    const int64_t c = j * w.nch + blockIdx.x;
+    const int64_t c = j * w.nch + chunk;
     w.cnt[c] = cnt;
     w.part[2 * c] = acc[0];
     w.part[2 * c + 1] = acc[1];
@@ -384,10 +388,11 @@ __global__ __launch_bounds__(kWT) void wide_emit_kernel(
     Wide w) {
   __shared__ int scan[kNWv + 1];
   __shared__ int red[kNWv + 1];
-  const int64_t j = blockIdx.y;
+  const int64_t j = blockIdx.x / w.nch;
+  const int chunk = blockIdx.x % w.nch;
   const WRow R = w.rows[j];
   if (!R.live) return;
-  const int base = blockIdx.x * kWCH + threadIdx.x * kWN;
+  const int base = chunk * kWCH + threadIdx.x * kWN;
   float v[kWN];
   load_chunk(V + j * ldv, p, base, v);
   Keep<KIND> keep;
@@ -404,7 +409,7 @@ __global__ __launch_bounds__(kWT) void wide_emit_kernel(
   }
   if (R.listed) {
     int tot;
-    int off = w.cnt[j * w.nch + blockIdx.x] + block_exclusive_scan(cnt, scan, &tot);
+    int off = w.cnt[j * w.nch + chunk] + block_exclusive_scan(cnt, scan, &tot);
     int32_t* li = list_idx + j * ldl;
     float* lv = list_val + j * ldl;
 #pragma unroll
@@ -448,11 +453,12 @@ __global__ __launch_bounds__(kWT) void lam_stats_kernel(
   __shared__ double dred[4 * (kNWv + 1)];
   __shared__ int red[kNWv + 1];
   __shared__ uint32_t ured[kNWv + 1];
-  const int64_t j = blockIdx.y;
+  const int64_t j = blockIdx.x / w.nch;
+  const int chunk = blockIdx.x % w.nch;
   if (!row_live(s, j)) return;
   const uint32_t t0 = w.rows[j].prefix > 1u ? w.rows[j].prefix : 1u;
   const double t0f = (double)__uint_as_float(t0);
-  const int base = blockIdx.x * kWCH + threadIdx.x * kWN;
+  const int base = chunk * kWCH + threadIdx.x * kWN;
   float v[kWN];
   load_chunk(V + j * ldv, p, base, v);
   double acc[4] = {0.0, 0.0, 0.0, 0.0};
@@ -476,7 +482,7 @@ __global__ __launch_bounds__(kWT) void lam_stats_kernel(
   c = block_sum(c, red);
   mk = block_max(mk, ured);
   if (threadIdx.x == 0) {
-    const int64_t q = j * w.nch + blockIdx.x;
+    const int64_t q = j * w.nch + chunk;
     w.lpart[4 * q] = acc[0];
     w.lpart[4 * q + 1] = acc[1];
     w.lpart[4 * q + 2] = acc[2];
@@ -525,17 +531,18 @@ __global__ __launch_bounds__(64) void lam_row_kernel(int64_t r, StartState s, Wi
 __global__ __launch_bounds__(kWT) void lam_gather_kernel(
     const float* __restrict__ V, int64_t ldv, int p, StartState s, Wide w) {
   __shared__ int scan[kNWv + 1];
-  const int64_t j = blockIdx.y;
+  const int64_t j = blockIdx.x / w.nch;
+  const int chunk = blockIdx.x % w.nch;
   if (!row_live(s, j) || w.rows[j].lmode != 1) return;
   const uint32_t t0 = w.rows[j].prefix > 1u ? w.rows[j].prefix : 1u;
-  const int base = blockIdx.x * kWCH + threadIdx.x * kWN;
+  const int base = chunk * kWCH + threadIdx.x * kWN;
   float v[kWN];
   load_chunk(V + j * ldv, p, base, v);
   int c = 0;
 #pragma unroll
   for (int k = 0; k < kWN; ++k) c += base + k < p && wkey(v[k]) >= t0;
   int tot;
-  int off = w.cnt[j * w.nch + blockIdx.x] + block_exclusive_scan(c, scan, &tot);
+  int off = w.cnt[j * w.nch + chunk] + block_exclusive_scan(c, scan, &tot);
   float* cd = w.cand + j * kMaxCandW;
 #pragma unroll
   for (int k = 0; k < kWN; ++k)
@@ -767,7 +774,7 @@ void launch_wide_kind(hipStream_t st, double param, const float* V,
                       int32_t* li, float* lv, int64_t ldl, int list_cap,
                       StartState s, double tol, int maxit, int32_t* colmark,
                       const Plan* plan, const Wide& w) {
-  const dim3 g2((unsigned)w.nch, (unsigned)r);
+  const dim3 g2((unsigned)(w.nch * r));  // chunk fastest
   const int ip = (int)p;
   const bool warm_gamma = (KIND == kHardGamma || KIND == kSoftGamma) && w.warm_K > 0;
   if (KIND == kTopS || KIND == kLambdaS || warm_gamma) {
@@ -828,10 +835,7 @@ bool x_update_wide(hipStream_t st, int fid, double s_or_gamma, const float* V,
                    int32_t* list_idx, float* list_val, int64_t ldl, int list_cap,
                    StartState s, double tol, int32_t maxit, int32_t* colmark,
                    const Plan* plan, void* scratch, Warm wm) {
-  const bool aligned = ldv % 4 == 0 && ldx % 4 == 0 && (uintptr_t)V % 16 == 0 &&
-                       (uintptr_t)X % 16 == 0;
-  if (scratch == nullptr || !aligned || x_update_wide_bytes(fid, r, p) == 0)
-    return false;
+  if (scratch == nullptr || x_update_wide_bytes(fid, r, p) == 0) return false;
   Wide w = carve_wide(scratch, r, p);
   w.warm_K = wm.K;
   w.warm_target = wm.target;
