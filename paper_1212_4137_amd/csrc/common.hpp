@@ -50,30 +50,119 @@ __host__ __device__ inline int64_t round_up(int64_t x, int64_t m) { return (x + 
 __host__ __device__ inline int64_t ceil_div(int64_t x, int64_t m) { return (x + m - 1) / m; }
 
 // ---------------------------------------------------------------------------
-// Deterministic reductions.  A wave reduces with a fixed xor butterfly and
-// lane 0's value is taken; waves are then summed in wave order by one thread.
-// The result does not depend on timing, only on the block size.
+// Exchanges between the lanes of a wave by DPP and row swaps, in registers: a
+// shuffle through LDS (ds_bpermute) takes 60 to 100 cycles until its value is
+// there, and the six steps of a reduction or a scan wait for one another.
+// All 64 lanes must be active.
+// ---------------------------------------------------------------------------
+template <typename T>
+struct Words {  // a 4- or 8-byte value as 32-bit words
+  static constexpr int N = sizeof(T) / 4;
+  static_assert(sizeof(T) == 4 || sizeof(T) == 8, "4- or 8-byte values");
+  int w[N];
+  __device__ __forceinline__ explicit Words(T v) { __builtin_memcpy(w, &v, sizeof(T)); }
+  __device__ __forceinline__ T value() const {
+    T v;
+    __builtin_memcpy(&v, w, sizeof(T));
+    return v;
+  }
+};
+
+// DPP move; lanes without a source, or outside the rows of ROWS, get 0.
+template <int CTRL, int ROWS = 0xf, typename T>
+__device__ __forceinline__ T dpp(T v) {
+  Words<T> a(v);
+#pragma unroll
+  for (int i = 0; i < Words<T>::N; ++i)
+    a.w[i] = __builtin_amdgcn_update_dpp(0, a.w[i], CTRL, ROWS, 0xf, false);
+  return a.value();
+}
+
+// For M = 16 or 32: *lo is the value of lane & ~M, *hi that of lane | M.
+template <int M, typename T>
+__device__ __forceinline__ void lane_pair(T v, T* lo, T* hi) {
+  static_assert(M == 16 || M == 32, "rows or halves");
+  Words<T> a(v), b(v);
+#pragma unroll
+  for (int i = 0; i < Words<T>::N; ++i) {
+    const auto r = M == 16 ? __builtin_amdgcn_permlane16_swap(a.w[i], b.w[i], false, false)
+                           : __builtin_amdgcn_permlane32_swap(a.w[i], b.w[i], false, false);
+    a.w[i] = (int)r[0];
+    b.w[i] = (int)r[1];
+  }
+  *lo = a.value();
+  *hi = b.value();
+}
+
+constexpr int kDppXor1 = 0xb1, kDppXor2 = 0x4e, kDppXor3 = 0x1b;  // within 4 lanes
+constexpr int kDppXor7 = 0x141;                                   // half row mirror
+constexpr int kDppRor = 0x120;                                    // rotate a row of 16
+constexpr int kDppShr = 0x110;                                    // shift a row up
+constexpr int kDppBcast15 = 0x142, kDppBcast31 = 0x143;
+
+// The value of lane ^ M.
+template <int M, typename T>
+__device__ __forceinline__ T lane_xor(T v) {
+  if constexpr (M == 1) {
+    return dpp<kDppXor1>(v);
+  } else if constexpr (M == 2) {
+    return dpp<kDppXor2>(v);
+  } else if constexpr (M == 4) {
+    return dpp<kDppXor7>(dpp<kDppXor3>(v));
+  } else if constexpr (M == 8) {
+    return dpp<kDppRor + 8>(v);
+  } else {
+    T lo, hi;
+    lane_pair<M>(v, &lo, &hi);
+    return (threadIdx.x & M) != 0 ? lo : hi;
+  }
+}
+
+// op over the wave by the butterfly lane ^ 32, 16, 8, 4, 2, 1 (op commutes;
+// from the third step on all rows of 16 agree, so a rotation serves as xor).
+template <typename T, typename Op>
+__device__ __forceinline__ T wave_all(T v, Op op) {
+  T lo, hi;
+  lane_pair<32>(v, &lo, &hi);
+  v = op(lo, hi);
+  lane_pair<16>(v, &lo, &hi);
+  v = op(lo, hi);
+  v = op(v, dpp<kDppRor + 8>(v));
+  v = op(v, dpp<kDppRor + 4>(v));
+  v = op(v, dpp<kDppXor2>(v));
+  return op(v, dpp<kDppXor1>(v));
+}
+
+// Inclusive prefix sum over the wave's lanes (integers).
+template <typename T>
+__device__ __forceinline__ T wave_scan(T v) {
+  v += dpp<kDppShr + 1>(v);
+  v += dpp<kDppShr + 2>(v);
+  v += dpp<kDppShr + 4>(v);
+  v += dpp<kDppShr + 8>(v);
+  v += dpp<kDppBcast15, 0xa>(v);  // rows 1 and 3: the sum of the row below
+  v += dpp<kDppBcast31, 0xc>(v);  // rows 2 and 3: the sum of the lower half
+  return v;
+}
+
+// ---------------------------------------------------------------------------
+// Deterministic reductions.  A wave reduces with a fixed xor butterfly; waves
+// are then summed in wave order.  The result does not depend on timing, only
+// on the block size.
 // ---------------------------------------------------------------------------
 
 template <typename T>
 __device__ __forceinline__ T wave_sum(T v) {
-#pragma unroll
-  for (int off = kWave / 2; off > 0; off >>= 1) v += __shfl_xor(v, off, kWave);
-  return v;
+  return wave_all(v, [](T a, T b) { return a + b; });
 }
 
 template <typename T>
 __device__ __forceinline__ T wave_max(T v) {
-#pragma unroll
-  for (int off = kWave / 2; off > 0; off >>= 1) {
-    T o = __shfl_xor(v, off, kWave);
-    v = o > v ? o : v;
-  }
-  return v;
+  return wave_all(v, [](T a, T b) { return b > a ? b : a; });
 }
 
 // Sums NV values per thread over the block; every thread receives the
-// totals.  scratch must hold NV * (blockDim/64 + 1) elements of T.
+// totals.  scratch must hold NV * (blockDim/64) elements of T.
 template <typename T, int NV>
 __device__ __forceinline__ void block_sum_n(T (&v)[NV], T* scratch) {
   const int lane = threadIdx.x % kWave;
@@ -86,14 +175,13 @@ __device__ __forceinline__ void block_sum_n(T (&v)[NV], T* scratch) {
     for (int c = 0; c < NV; ++c) scratch[wave * NV + c] = v[c];
   }
   __syncthreads();
-  if (threadIdx.x < NV) {
-    T acc = 0;
-    for (int w = 0; w < nwaves; ++w) acc += scratch[w * NV + threadIdx.x];
-    scratch[nwaves * NV + threadIdx.x] = acc;
-  }
-  __syncthreads();
 #pragma unroll
-  for (int c = 0; c < NV; ++c) v[c] = scratch[nwaves * NV + c];
+  for (int c = 0; c < NV; ++c) v[c] = 0;
+#pragma unroll 4
+  for (int w = 0; w < nwaves; ++w) {
+#pragma unroll
+    for (int c = 0; c < NV; ++c) v[c] += scratch[w * NV + c];
+  }
   __syncthreads();
 }
 
@@ -104,7 +192,7 @@ __device__ __forceinline__ T block_sum(T v, T* scratch) {
   return a[0];
 }
 
-// Block max; scratch holds blockDim/64 + 1 elements.
+// Block max; scratch holds blockDim/64 elements.
 template <typename T>
 __device__ __forceinline__ T block_max(T v, T* scratch) {
   const int lane = threadIdx.x % kWave;
@@ -113,47 +201,34 @@ __device__ __forceinline__ T block_max(T v, T* scratch) {
   v = wave_max(v);
   if (lane == 0) scratch[wave] = v;
   __syncthreads();
-  if (threadIdx.x == 0) {
-    T m = scratch[0];
-    for (int w = 1; w < nwaves; ++w) m = scratch[w] > m ? scratch[w] : m;
-    scratch[nwaves] = m;
-  }
-  __syncthreads();
-  v = scratch[nwaves];
+  v = scratch[0];
+#pragma unroll 4
+  for (int w = 1; w < nwaves; ++w) v = scratch[w] > v ? scratch[w] : v;
   __syncthreads();
   return v;
 }
 
-// Exclusive prefix sum of one value per thread in thread order; returns the
+// Exclusive prefix sum of one integer per thread in thread order; returns the
 // thread's offset and writes the block total to *total.  scratch holds
-// blockDim/64 + 1 values.
+// blockDim/64 values.
 template <typename T>
 __device__ __forceinline__ T block_exclusive_scan(T v, T* scratch, T* total) {
   const int lane = threadIdx.x % kWave;
   const int wave = threadIdx.x / kWave;
   const int nwaves = blockDim.x / kWave;
-  T incl = v;
-#pragma unroll
-  for (int off = 1; off < kWave; off <<= 1) {
-    T o = __shfl_up(incl, off, kWave);
-    if (lane >= off) incl += o;
-  }
+  const T incl = wave_scan(v);
   if (lane == kWave - 1) scratch[wave] = incl;
   __syncthreads();
-  if (threadIdx.x == 0) {
-    T run = 0;
-    for (int w = 0; w < nwaves; ++w) {
-      T t = scratch[w];
-      scratch[w] = run;
-      run += t;
-    }
-    scratch[nwaves] = run;
+  T before = 0, sum = 0;
+#pragma unroll 4
+  for (int w = 0; w < nwaves; ++w) {
+    const T t = scratch[w];
+    before += w < wave ? t : (T)0;
+    sum += t;
   }
   __syncthreads();
-  T res = scratch[wave] + incl - v;
-  *total = scratch[nwaves];
-  __syncthreads();
-  return res;
+  *total = sum;
+  return before + incl - v;
 }
 
 // FP32 -> BF16 bit pattern, round to nearest even (NaN stays NaN).

@@ -96,15 +96,7 @@ __device__ __forceinline__ int rank_rows(const int (&c)[R], int (&base)[R], uint
 #pragma unroll
   for (int q = 0; q < R; ++q) in[q / 4] |= (uint64_t)c[q] << (16 * (q % 4));
 #pragma unroll
-  for (int w = 0; w < W; ++w) inc[w] = in[w];
-#pragma unroll
-  for (int off = 1; off < kWave; off <<= 1) {
-#pragma unroll
-    for (int w = 0; w < W; ++w) {
-      const uint64_t o = __shfl_up(inc[w], off, kWave);
-      if (lane >= off) inc[w] += o;
-    }
-  }
+  for (int w = 0; w < W; ++w) inc[w] = wave_scan(in[w]);
   if (lane == kWave - 1) {
 #pragma unroll
     for (int w = 0; w < W; ++w) scratch[wave * W + w] = inc[w];
@@ -701,10 +693,16 @@ struct CSmem {
   double seg[4];
 };
 
+// The value of lane ^ m (m is a constant once the callers' loops are unrolled).
 __device__ __forceinline__ uint64_t shfl_xor_u64(uint64_t x, int m) {
-  const uint32_t lo = __shfl_xor((uint32_t)x, m, kWave);
-  const uint32_t hi = __shfl_xor((uint32_t)(x >> 32), m, kWave);
-  return ((uint64_t)hi << 32) | lo;
+  switch (m) {
+    case 1: return lane_xor<1>(x);
+    case 2: return lane_xor<2>(x);
+    case 4: return lane_xor<4>(x);
+    case 8: return lane_xor<8>(x);
+    case 16: return lane_xor<16>(x);
+    default: return lane_xor<32>(x);
+  }
 }
 
 // Ascending bitonic sort of kRT E keys: x[e] is element tid + kRT e.
@@ -817,8 +815,7 @@ __device__ __forceinline__ double fixed_sum(int m, F f, double* slot) {
   if (threadIdx.x < kWave) {
     double a = 0.0;
     for (int q = threadIdx.x; q < m; q += kWave) a += f(q);
-#pragma unroll
-    for (int o = kWave / 2; o > 0; o >>= 1) a += __shfl_xor(a, o, kWave);
+    a = wave_sum(a);
     if (threadIdx.x == 0) *slot = a;
   }
   __syncthreads();
