@@ -52,14 +52,16 @@ __device__ __forceinline__ void spread(uint32_t lo, uint32_t hi, uint32_t (&t)[N
 // Register-resident rows, p <= 256 * NPT: a 256-thread block per start, so
 // that every pass is register arithmetic and all starts of a batch are
 // resident on the chip at once (1024 x 10000: 4 blocks a CU).  Reading V and
-// writing X, 82 MB there, takes 18 us of the 42 us of T_s and 53 us of
+// writing X, 82 MB there, takes 17 us of the 27 us of T_s and 32 us of
 // lambda_s; the rest is the passes and their barriers, which all blocks go
-// through in step.  Before, with three LDS histograms a selection and a sort
-// of lambda_s candidates, 53 and 232 us.
+// through in step.  Norm, count and rounds therefore run over the at most
+// 1024 entries that the search left, where there are such (over the whole
+// row: 40 and 50 us; with three LDS histograms a selection and a sort of
+// lambda_s candidates: 53 and 232 us).
 // ---------------------------------------------------------------------------
 // Four floats of a row, loaded and stored with one 16-byte instruction: global
 // memory asks for 4-byte alignment only, so rows of any leading dimension
-// and offset take it (900 x 12285: T_s 54 us, lambda_s 59, U_g 21; one
+// and offset take it (900 x 12285: T_s 31 us, lambda_s 50, U_g 19; one
 // 1024-thread workgroup a row from LDS took 290, 712 and 28).
 typedef float floatx4 __attribute__((ext_vector_type(4), aligned(4)));
 
@@ -74,7 +76,7 @@ struct RSmem {
   uint32_t ured[2 * kRW];
   int scan[kRW + 1];
   float cand[kSelCap];
-  int64_t cut;
+  int cut;
   uint64_t pscan[3 * (kRW + 1)];  // packed per-row counts (rank_rows)
 };
 
@@ -212,16 +214,23 @@ __device__ __forceinline__ float tail_guess(float sq, int p, float want) {
   return sqrtf(sq / (float)p) * z;
 }
 
-// The need-th largest key (1 <= need <= p) and the number of keys from it on
-// and strictly above it: the bracket #{key >= lo} >= need > #{key >= hi} is halved in key
-// space (a float's bits are monotone and about logarithmic in it) by counting
-// passes over the registers, from a start by tail_guess; once at most kSelCap
-// entries lie above lo, over those alone.  Counting takes one compare an
-// entry, where a histogram of the key's bits takes an LDS atomic, most of
-// them on the few bins that hold most of a row.
+// Search for the need-th largest key of a row (1 <= need <= p): the bracket
+// #{key >= lo} >= need > #{key >= hi} with those counts.
+struct Bracket {
+  uint32_t lo, hi, nlo, nhi, parity;
+  uint32_t mk;  // the largest key
+  bool nan;     // the row holds NaN
+};
+
+// Halves the bracket in key space (a float's bits are monotone and about
+// logarithmic in it) by counting passes over the registers, from a start by
+// tail_guess, until at most kSelCap entries lie above lo, and deals those out
+// in c as compact does; false if that needs lo = 0 or ties forbid it.
+// Counting takes one compare an entry, where a histogram of the key's bits
+// takes an LDS atomic, most of them on the few bins that hold most of a row.
 template <int NPT>
-__device__ void select_key(float (&v)[NPT], int p, uint32_t need, RSmem& sm,
-                           uint32_t* key_out, uint32_t* from_out, uint32_t* above_out) {
+__device__ __forceinline__ bool narrow(float (&v)[NPT], int p, uint32_t need, RSmem& sm,
+                                       float (&c)[kSelPer], Bracket& b) {
   float sq = 0.f;
   uint32_t mk = 0;
 #pragma unroll
@@ -232,61 +241,63 @@ __device__ void select_key(float (&v)[NPT], int p, uint32_t need, RSmem& sm,
   }
   sq = block_sum(sq, reinterpret_cast<float*>(sm.dred));
   mk = block_max(mk, sm.ured);
-  uint32_t lo = 0u, hi = mk + 1u, nlo = (uint32_t)p, nhi = 0u, parity = 0u;
+  b = Bracket{0u, mk + 1u, (uint32_t)p, 0u, 0u, mk, sq != sq};
   uint32_t t = key_of(tail_guess(sq, p, 1.4f * (float)need + 16.f));
   uint32_t step = 1u << 21;  // a quarter of a binade: brackets a start that is nearly right
   bool first = true, down = false;
-  while (hi - lo > 1u && nlo > (uint32_t)kSelCap) {
-    if (!(t > lo && t < hi)) t = lo + (hi - lo) / 2u;
-    const uint32_t n = count_from(v, t, parity, sm.ured);
-    parity ^= 1u;
+  while (b.hi - b.lo > 1u && b.nlo > (uint32_t)kSelCap) {
+    if (!(t > b.lo && t < b.hi)) t = b.lo + (b.hi - b.lo) / 2u;
+    const uint32_t n = count_from(v, t, b.parity, sm.ured);
+    b.parity ^= 1u;
     const bool in = n >= need;
     if (in) {
-      lo = t;
-      nlo = n;
+      b.lo = t;
+      b.nlo = n;
     } else {
-      hi = t;
-      nhi = n;
+      b.hi = t;
+      b.nhi = n;
     }
     // steps in one direction double; the first turn brackets the threshold
-    const bool turned = !first && down == in;
+    if (!first && down == in) step = 0u;
     first = false;
     down = !in;
-    if (turned) step = 0u;
     t = step == 0u ? 0u : (in ? t + step : (t > step ? t - step : 0u));
     step *= 2u;
   }
-  if (hi - lo > 1u && lo > 0u) {
-    float c[kSelPer];
-    compact(v, __uint_as_float(lo), sm, c);
-    while (hi - lo > 1u) {
-      t = lo + (hi - lo) / 2u;
-      const uint32_t n = count_from(c, t, parity, sm.ured);
-      parity ^= 1u;
-      if (n >= need) {
-        lo = t;
-        nlo = n;
-      } else {
-        hi = t;
-        nhi = n;
-      }
-    }
-  }
-  while (hi - lo > 1u) {  // rows of at most kSelCap entries
-    t = lo + (hi - lo) / 2u;
-    const uint32_t n = count_from(v, t, parity, sm.ured);
-    parity ^= 1u;
+  // a row with NaN takes the whole-row passes, which give its norm as NaN
+  const bool few = b.lo > 0u && b.nlo <= (uint32_t)kSelCap && !b.nan;
+  if (few) compact(v, __uint_as_float(b.lo), sm, c);
+  return few;
+}
+
+// Halves the bracket over v down to one key: the need-th largest.
+template <int N>
+__device__ __forceinline__ void settle(float (&v)[N], uint32_t need, RSmem& sm, Bracket& b) {
+  while (b.hi - b.lo > 1u) {
+    const uint32_t t = b.lo + (b.hi - b.lo) / 2u;
+    const uint32_t n = count_from(v, t, b.parity, sm.ured);
+    b.parity ^= 1u;
     if (n >= need) {
-      lo = t;
-      nlo = n;
+      b.lo = t;
+      b.nlo = n;
     } else {
-      hi = t;
-      nhi = n;
+      b.hi = t;
+      b.nhi = n;
     }
   }
-  *key_out = lo;
-  *from_out = nlo;
-  *above_out = nhi;
+}
+
+// The need-th largest key of the row is b.lo, with b.nlo keys from it on and
+// b.nhi above it; true if all of those are in c.
+template <int NPT>
+__device__ __forceinline__ bool select_key(float (&v)[NPT], int p, uint32_t need, RSmem& sm,
+                                           float (&c)[kSelPer], Bracket& b) {
+  const bool few = narrow<NPT>(v, p, need, sm, c, b);
+  if (few)
+    settle<kSelPer>(c, need, sm, b);
+  else
+    settle<NPT>(v, need, sm, b);
+  return few;
 }
 
 // The smallest float above l >= 0: |v| >= float_above(l) is |v| > l.
@@ -361,19 +372,24 @@ __global__ __launch_bounds__(kRT, WARM ? 2 : 4) void x_update_reg_kernel(
   }
 
   uint32_t thr_key = 0;
-  int64_t cut = -1;
+  int cut = -1;
+  int tied = 0;       // T_s: entries kept at the threshold itself
   double lam = 0.0;
+  float c[kSelPer];   // the magnitudes of all entries from the threshold on, if few
+  bool few = false;
+  Bracket br;
   const int itc = full ? s.iters[j] + 1 : 1;  // this x-update's number
   const bool warming = WARM && itc <= wm.K;
   if (KIND == kTopS) {
     const uint32_t s_int = (uint32_t)((int64_t)param < (int64_t)p ? (int64_t)param : (int64_t)p);
-    uint32_t from, above;
-    select_key<NPT>(v, p, s_int, sm, &thr_key, &from, &above);
+    few = select_key<NPT>(v, p, s_int, sm, c, br);
+    thr_key = br.lo;
     cut = p;
-    if (thr_key != 0u && from > s_int) {
+    tied = thr_key == 0u ? 0 : (int)((br.nlo < s_int ? br.nlo : s_int) - br.nhi);
+    if (thr_key != 0u && br.nlo > s_int) {
       // ties at thr_key: keep the first (s - #{key > thr_key}) in index
       // order; rare, so from memory, a run of the row a thread
-      const int need = (int)(s_int - above);
+      const int need = (int)(s_int - br.nhi);
       const int run = (p + kRT - 1) / kRT;
       const int i0 = run * tid, i1 = i0 + run < p ? i0 + run : p;
       int eq = 0, total_eq;
@@ -399,41 +415,34 @@ __global__ __launch_bounds__(kRT, WARM ? 2 : 4) void x_update_reg_kernel(
     // below l only lower the sum and raise the norm).  So each round takes S
     // to {|v| > l}, and l rises to the row's root, reached when S no longer
     // changes.  S begins as {|v| >= t} if rho(t) > sqrt(s) there, which
-    // places the root above t (t: about 6 s entries of a Gaussian row; 2 s
-    // are kept), else as all nonzero entries; from kSelCap entries on the
-    // rounds run over those alone, about eight of them.
+    // places the root above t, else as all nonzero entries.  t has the 8 s
+    // largest entries or more above it (a row of noise and s larger entries
+    // keeps about 5 s) and at most kSelCap, and the rounds run over those
+    // alone; S from the whole row does so once it has come down to that.
     const double s_par = param;
     const double rs = sqrt(s_par);
-    float sq = 0.f;
-    uint32_t mk = 0;
-#pragma unroll
-    for (int k = 0; k < NPT; ++k) {
-      const uint32_t key = key_of(v[k]);
-      mk = key > mk ? key : mk;
-      sq += v[k] * v[k];
-    }
-    sq = block_sum(sq, reinterpret_cast<float*>(sm.dred));
-    mk = block_max(mk, sm.ured);
-    float f = tail_guess(sq, p, (float)(6.0 * s_par));
     double set3[3] = {0.0, 0.0, 0.0};
     bool active = false;
-    if (f > 0.f && 12.0 * s_par < (double)p) {
-      sums_from<NPT>(v, f, set3, sm.dred);
+    float f = 0.f;
+    const double want = 8.0 * s_par < 800.0 ? 8.0 * s_par : 800.0;
+    if (narrow<NPT>(v, p, want < (double)p ? (uint32_t)want : (uint32_t)p, sm, c, br)) {
+      f = __uint_as_float(br.lo);
       lam = (double)f;
+      sums_from<kSelPer>(c, f, set3, sm.dred);
       const double l1 = set3[1] - set3[0] * lam;
       const double l2 = set3[2] - 2.0 * lam * set3[1] + set3[0] * lam * lam;
       active = l2 > 1e-12 * set3[2] && l1 > (1.0 + 1e-9) * rs * sqrt(l2);
     }
+    few = active;
+    const uint32_t mk = br.mk;
     if (!active) {
       lam = 0.0;
       f = __uint_as_float(1u);
       sums_from<NPT>(v, f, set3, sm.dred);
-      active = set3[1] > rs * sqrt(set3[2]);
+      active = !br.nan && set3[1] > rs * sqrt(set3[2]);  // NaN: lambda = 0
     }
     bool done = !active;
     if (active) {
-      float c[kSelPer];
-      bool few = false;
 #pragma unroll 1
       for (int round = 0; round < kLamRoundsFull; ++round) {
         const double kk = set3[0];
@@ -461,6 +470,7 @@ __global__ __launch_bounds__(kRT, WARM ? 2 : 4) void x_update_reg_kernel(
     if (!done) {
       // fallback: FP64 search of the float interval holding the root; reads
       // the row from memory so that the fast path keeps its registers
+      few = false;
       uint32_t lo = 0, hi = mk;
       while (hi - lo > 1) {
         uint32_t t[kNCd];
@@ -526,9 +536,8 @@ __global__ __launch_bounds__(kRT, WARM ? 2 : 4) void x_update_reg_kernel(
     if ((int64_t)wm.target >= (int64_t)p) {
       lam = 0.0;
     } else {
-      uint32_t tk, from, above;
-      select_key<NPT>(v, p, (uint32_t)wm.target + 1u, sm, &tk, &from, &above);
-      const double t = (double)__uint_as_float(tk);
+      select_key<NPT>(v, p, (uint32_t)wm.target + 1u, sm, c, br);
+      const double t = (double)__uint_as_float(br.lo);
       lam = KIND == kHardGamma ? t * t : t;
     }
   } else if (WARM) {
@@ -542,7 +551,7 @@ __global__ __launch_bounds__(kRT, WARM ? 2 : 4) void x_update_reg_kernel(
     if (KIND == kTopS) {
       uint32_t k = key_of(vv);
       *w = (double)vv;
-      return k != 0 && (k > thr_key || (k == thr_key && (int64_t)i <= cut));
+      return k != 0 && (k > thr_key || (k == thr_key && i <= cut));
     } else if (KIND == kHardGamma) {
       *w = (double)vv;
       return (double)vv * (double)vv > lam;
@@ -553,26 +562,57 @@ __global__ __launch_bounds__(kRT, WARM ? 2 : 4) void x_update_reg_kernel(
     }
   };
 
-  int cnt[R], off[R];
-  double acc[2] = {0.0, 0.0};
+  // the kept entries' number and squares, from the candidates where there are
+  // such, and their offsets in the list if one is written
+  double acc[3] = {0.0, 0.0, 0.0};
+  auto add = [&](float vv) {
+    bool in;
+    double w;
+    if (KIND == kTopS) {
+      in = key_of(vv) > thr_key;
+      w = (double)vv;
+    } else {
+      in = kept(0, vv, &w);
+    }
+    if (in) {
+      acc[0] += w * w;
+      if (KIND == kHardGamma) acc[1] += w * w - lam;
+      acc[2] += 1.0;
+    }
+  };
+  if (few) {
 #pragma unroll
-  for (int q = 0; q < R; ++q) {
-    cnt[q] = 0;
-    if (q % 2 == 0) __builtin_amdgcn_sched_barrier(0);
+    for (int e = 0; e < kSelPer; ++e) add(c[e]);
+  } else {
 #pragma unroll
-    for (int e = 0; e < 4; ++e) {
-      const int k = 4 * q + e;
-      double w;
+    for (int k = 0; k < NPT; ++k) {
+      if (k % 8 == 0) __builtin_amdgcn_sched_barrier(0);
       reload(v[k]);
-      if (kept(gidx(k), v[k], &w)) {
-        ++cnt[q];
-        acc[0] += w * w;
-        if (KIND == kHardGamma) acc[1] += w * w - lam;
-      }
+      add(v[k]);
     }
   }
-  block_sum_n<double, 2>(acc, sm.dred);
-  const int total = rank_rows<R>(cnt, off, sm.pscan);
+  block_sum_n<double, 3>(acc, sm.dred);
+  if (KIND == kTopS && tied > 0) {
+    const double w = (double)__uint_as_float(thr_key);
+    acc[0] += (double)tied * (w * w);
+    acc[2] += (double)tied;
+  }
+  const int total = (int)acc[2];
+  int cnt[R], off[R];
+  if (list_idx != nullptr) {
+#pragma unroll
+    for (int q = 0; q < R; ++q) {
+      cnt[q] = 0;
+#pragma unroll
+      for (int e = 0; e < 4; ++e) {
+        const int k = 4 * q + e;
+        double w;
+        reload(v[k]);
+        cnt[q] += kept(gidx(k), v[k], &w);
+      }
+    }
+    rank_rows<R>(cnt, off, sm.pscan);
+  }
   const double nrm = sqrt(acc[0]);
   double phi;
   if (KIND == kHardGamma)
@@ -594,7 +634,7 @@ __global__ __launch_bounds__(kRT, WARM ? 2 : 4) void x_update_reg_kernel(
 #pragma unroll
   for (int q = 0; q < NPT; q += 4) {
     float xo[4];
-    int o = off[q / 4];
+    int o = li != nullptr ? off[q / 4] : 0;
 #pragma unroll
     for (int e = 0; e < 4; ++e) {
       double w;
