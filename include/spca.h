@@ -408,9 +408,10 @@ int spca_gemm_nt_f32_plan(int64_t M, int64_t N, int64_t K, int max_splits,
  * T_s, V_{lambda_s}, U_gamma or V_gamma (Table 3, rows S3-S6).  Writes X
  * (r x p, ldx >= p, device), phi (r doubles, device: the subproblem optimum
  * of Table 3) and nnz (r int32, device).  A zero image gives X_j = 0.
- * Same parameter checks as spca_am_solve.  For p > 12288 (except the L1
- * constraint) the chunked kernels run on scratch that this call allocates
- * and frees, so the call then synchronizes the stream before returning.   */
+ * Same parameter checks as spca_am_solve.  For p > 12288 the call
+ * synchronizes the stream before returning; the chunked kernels of those
+ * rows may run on scratch that the call allocates and frees (T_s of a large
+ * s, or X overlapping V).                                                 */
 int spca_x_update(void* stream, int formulation, const float* V, int64_t ldv,
                   int64_t r, int64_t p, double s_or_gamma, float* X,
                   int64_t ldx, double* phi, int32_t* nnz);

@@ -360,9 +360,13 @@ void x_update(hipStream_t st, int fid, double s_or_gamma, const float* V,
               const Plan* plan, void* wide = nullptr, Warm wm = Warm{});
 
 constexpr int64_t kWideMinP = 12288;
-// scratch of the chunked x-update (0 when it does not apply: lambda_s, or
-// p <= kWideMinP); the size is the same for every other formulation
+// scratch of the chunked x-update (0 for p <= kWideMinP); the size is the same
+// for every formulation
 size_t x_update_wide_bytes(int fid, int64_t r, int64_t p);
+// true when spca_x_update has to hold that scratch: lambda_s and T_s of a small
+// s need none
+bool x_update_wide_scratch(int fid, double s_or_gamma, const float* V, int64_t ldv, int64_t r,
+                           int64_t p, const float* X, int64_t ldx);
 hipError_t x_update_wide_reset(hipStream_t st, void* scratch, int64_t r);
 // 32-bit words at the start of that scratch which x_update_wide_reset clears
 int64_t x_update_wide_clear_words(int64_t r);

@@ -78,6 +78,9 @@ extern "C" int spca_x_update_noalloc(void* stream, int formulation, const float*
   if (wb) {
     rc = scratch_on_current_device(&wide);
     if (rc != SPCA_OK) return rc;
+    if (!x_update_wide_scratch(formulation, s_or_gamma, V, ldv, r, p, X, ldx)) wide = nullptr;
+  }
+  if (wide) {
     // the digit histograms must start at zero (the kernels leave them
     // zero, but an earlier call's state is not relied on)
     const int64_t words = x_update_wide_clear_words(r);

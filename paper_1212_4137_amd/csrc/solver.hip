@@ -1627,8 +1627,11 @@ int spca_x_update(void* stream, int formulation, const float* V, int64_t ldv,
   SPCA_REQUIRE(ldv >= p && ldx >= p, "leading dimensions too small");
   StartState s{phi, nullptr, nnz, nullptr, nullptr};
   hipStream_t st = (hipStream_t)stream;
-  // long rows: the chunked kernels need scratch, held for this call only
-  const size_t wb = x_update_wide_bytes(formulation, r, p);
+  // long rows: where the chunked kernels need scratch, it is held for this call
+  // only; without it the call still synchronizes, as documented
+  const size_t wb = x_update_wide_scratch(formulation, s_or_gamma, V, ldv, r, p, X, ldx)
+                        ? x_update_wide_bytes(formulation, r, p)
+                        : 0;
   void* wide = nullptr;
   if (wb) {
     SPCA_HIP_TRY(hipMalloc(&wide, wb));
@@ -1641,9 +1644,9 @@ int spca_x_update(void* stream, int formulation, const float* V, int64_t ldv,
   x_update(st, formulation, s_or_gamma, V, ldv, r, p, X, ldx, nullptr, nullptr, 0,
            0, s, -1.0, 1, nullptr, nullptr, wide);
   hipError_t le = hipGetLastError();
-  if (wide) {
+  if (p > kWideMinP) {
     hipError_t se = hipStreamSynchronize(st);
-    (void)hipFree(wide);
+    if (wide) (void)hipFree(wide);
     if (le == hipSuccess) le = se;
   }
   if (le != hipSuccess) {

@@ -25,108 +25,10 @@
 #include "../../include/spca.h"
 #include "common.hpp"
 #include "kernels.hpp"
+#include "select.hpp"
 
 namespace spca {
 namespace {
-
-constexpr int kNCd = 7;    // thresholds per FP64 search step
-
-__device__ __forceinline__ uint32_t key_of(float v) {
-  return __float_as_uint(v) & 0x7fffffffu;
-}
-
-// NC thresholds that split (lo, hi) evenly; hi stands for none.
-template <int NC>
-__device__ __forceinline__ void spread(uint32_t lo, uint32_t hi, uint32_t (&t)[NC]) {
-  const uint32_t span = hi - lo;
-#pragma unroll
-  for (int c = 0; c < NC; ++c) {
-    uint32_t d = span > NC + 1
-                     ? (uint32_t)(((uint64_t)span * (uint64_t)(c + 1)) / (NC + 1))
-                     : (uint32_t)(c + 1);
-    t[c] = d < span ? lo + d : hi;
-  }
-}
-
-// ---------------------------------------------------------------------------
-// Register-resident rows, p <= 256 * NPT: a 256-thread block per start, so
-// that every pass is register arithmetic and all starts of a batch are
-// resident on the chip at once (1024 x 10000: 4 blocks a CU).  Reading V and
-// writing X, 82 MB there, takes 17 us of the 27 us of T_s and 32 us of
-// lambda_s; the rest is the passes and their barriers, which all blocks go
-// through in step.  Norm, count and rounds therefore run over the at most
-// 1024 entries that the search left, where there are such (over the whole
-// row: 40 and 50 us; with three LDS histograms a selection and a sort of
-// lambda_s candidates: 53 and 232 us).
-// ---------------------------------------------------------------------------
-// Four floats of a row, loaded and stored with one 16-byte instruction: global
-// memory asks for 4-byte alignment only, so rows of any leading dimension
-// and offset take it (900 x 12285: T_s 31 us, lambda_s 50, U_g 19; one
-// 1024-thread workgroup a row from LDS took 290, 712 and 28).
-typedef float floatx4 __attribute__((ext_vector_type(4), aligned(4)));
-
-constexpr int kRT = 256;  // threads per start
-constexpr int kRW = kRT / kWave;
-constexpr int kSelPer = 4;
-constexpr int kSelCap = kSelPer * kRT;  // entries that a selection goes on with alone
-constexpr int kLamRoundsFull = 40;  // closed-form rounds of lambda_s from the whole row
-
-struct RSmem {
-  double dred[2 * kNCd * (kRW + 1)];
-  uint32_t ured[2 * kRW];
-  int scan[kRW + 1];
-  float cand[kSelCap];
-  int cut;
-  uint64_t pscan[3 * (kRW + 1)];  // packed per-row counts (rank_rows)
-};
-
-// Index-order ranks over the striped row layout of the one-workgroup
-// x-update: thread t holds elements 4 (q kRT + t) + e, e < 4, for rows q <
-// R.  Given per-thread counts c[q] <= 4 of the elements that satisfy a
-// predicate, returns in base[q] the number of such elements at a lower
-// index than this thread's row-q group (earlier rows of the whole block,
-// then lower threads of the same row), and the block total.  Four 16-bit
-// fields per 64-bit word hold row counts up to 4 kRT without carries.
-template <int R>
-__device__ __forceinline__ int rank_rows(const int (&c)[R], int (&base)[R], uint64_t* scratch) {
-  constexpr int W = (R + 3) / 4;
-  const int lane = threadIdx.x % kWave;
-  const int wave = threadIdx.x / kWave;
-  uint64_t in[W], inc[W];
-#pragma unroll
-  for (int w = 0; w < W; ++w) in[w] = 0;
-#pragma unroll
-  for (int q = 0; q < R; ++q) in[q / 4] |= (uint64_t)c[q] << (16 * (q % 4));
-#pragma unroll
-  for (int w = 0; w < W; ++w) inc[w] = wave_scan(in[w]);
-  if (lane == kWave - 1) {
-#pragma unroll
-    for (int w = 0; w < W; ++w) scratch[wave * W + w] = inc[w];
-  }
-  __syncthreads();
-  uint64_t before[W], tot[W];
-#pragma unroll
-  for (int w = 0; w < W; ++w) before[w] = tot[w] = 0;
-#pragma unroll
-  for (int u = 0; u < kRW; ++u) {
-#pragma unroll
-    for (int w = 0; w < W; ++w) {
-      const uint64_t x = scratch[u * W + w];
-      if (u < wave) before[w] += x;
-      tot[w] += x;
-    }
-  }
-  __syncthreads();
-  int run = 0;
-#pragma unroll
-  for (int q = 0; q < R; ++q) {
-    const int sh = 16 * (q % 4);
-    const int mine = (int)(((before[q / 4] + inc[q / 4] - in[q / 4]) >> sh) & 0xffffu);
-    base[q] = run + mine;
-    run += (int)((tot[q / 4] >> sh) & 0xffffu);
-  }
-  return run;
-}
 
 // Exclusive prefix sums of two doubles per thread in thread order (kRT).
 __device__ __forceinline__ void rscan2(double (&v)[2], double* scratch) {
@@ -156,177 +58,17 @@ __device__ __forceinline__ void rscan2(double (&v)[2], double* scratch) {
   __syncthreads();
 }
 
-// Marks a register value as changed, so that the compiler recomputes what
-// it derives from it (keys, bins) instead of holding copies across passes.
-__device__ __forceinline__ void reload(float& x) { asm volatile("" : "+v"(x)); }
-
-// Number of the block's entries with |v| at or above the float of key t; one
-// compare an entry and one barrier a call (parity: consecutive calls alternate
-// it, so that a wave may write its count while another still reads the last).
-template <int N>
-__device__ __forceinline__ uint32_t count_from(float (&v)[N], uint32_t t, uint32_t parity,
-                                               uint32_t* scratch) {
-  const float f = __uint_as_float(t);
-  uint32_t n = 0;
-#pragma unroll
-  for (int k = 0; k < N; ++k) {
-    reload(v[k]);
-    n += (uint32_t)__popcll(__ballot(fabsf(v[k]) >= f));
-  }
-  uint32_t* c = scratch + kRW * parity;
-  if (threadIdx.x % kWave == 0) c[threadIdx.x / kWave] = n;
-  __syncthreads();
-  n = 0;
-#pragma unroll
-  for (int w = 0; w < kRW; ++w) n += c[w];
-  return n;
-}
-
-// Compacts the entries with |v| >= f, at most kSelCap, into LDS in thread
-// order and deals them out again, kSelPer a thread (zeros beyond them).
-template <int NPT>
-__device__ __forceinline__ void compact(float (&v)[NPT], float f, RSmem& sm,
-                                        float (&c)[kSelPer]) {
-  int mine = 0;
-#pragma unroll
-  for (int k = 0; k < NPT; ++k) mine += fabsf(v[k]) >= f;
-  int n;
-  int off = block_exclusive_scan(mine, sm.scan, &n);
-#pragma unroll
-  for (int k = 0; k < NPT; ++k) {
-    reload(v[k]);  // compare again rather than hold the masks
-    if (fabsf(v[k]) >= f) sm.cand[off++] = fabsf(v[k]);
-  }
-  __syncthreads();
-#pragma unroll
-  for (int e = 0; e < kSelPer; ++e) {
-    const int i = threadIdx.x + e * kRT;
-    c[e] = i < n ? sm.cand[i] : 0.f;
-  }
-}
-
-// A threshold that about `want` of a row's p entries exceed if the row is
-// Gaussian with the sum of squares sq (asymptotic tail quantile): where the
-// searches below start.  Any value is a valid start.
-__device__ __forceinline__ float tail_guess(float sq, int p, float want) {
-  const float q = logf(fmaxf((float)p / want, 1.05f));
-  const float z = q > 1.f ? sqrtf(2.f * q - logf(3.f * q)) : 0.95f * q;
-  return sqrtf(sq / (float)p) * z;
-}
-
-// Search for the need-th largest key of a row (1 <= need <= p): the bracket
-// #{key >= lo} >= need > #{key >= hi} with those counts.
-struct Bracket {
-  uint32_t lo, hi, nlo, nhi, parity;
-  uint32_t mk;  // the largest key
-  bool nan;     // the row holds NaN
-};
-
-// Halves the bracket in key space (a float's bits are monotone and about
-// logarithmic in it) by counting passes over the registers, from a start by
-// tail_guess, until at most kSelCap entries lie above lo, and deals those out
-// in c as compact does; false if that needs lo = 0 or ties forbid it.
-// Counting takes one compare an entry, where a histogram of the key's bits
-// takes an LDS atomic, most of them on the few bins that hold most of a row.
-template <int NPT>
-__device__ __forceinline__ bool narrow(float (&v)[NPT], int p, uint32_t need, RSmem& sm,
-                                       float (&c)[kSelPer], Bracket& b) {
-  float sq = 0.f;
-  uint32_t mk = 0;
-#pragma unroll
-  for (int k = 0; k < NPT; ++k) {
-    const uint32_t key = key_of(v[k]);
-    mk = key > mk ? key : mk;
-    sq += v[k] * v[k];
-  }
-  sq = block_sum(sq, reinterpret_cast<float*>(sm.dred));
-  mk = block_max(mk, sm.ured);
-  b = Bracket{0u, mk + 1u, (uint32_t)p, 0u, 0u, mk, sq != sq};
-  uint32_t t = key_of(tail_guess(sq, p, 1.4f * (float)need + 16.f));
-  uint32_t step = 1u << 21;  // a quarter of a binade: brackets a start that is nearly right
-  bool first = true, down = false;
-  while (b.hi - b.lo > 1u && b.nlo > (uint32_t)kSelCap) {
-    if (!(t > b.lo && t < b.hi)) t = b.lo + (b.hi - b.lo) / 2u;
-    const uint32_t n = count_from(v, t, b.parity, sm.ured);
-    b.parity ^= 1u;
-    const bool in = n >= need;
-    if (in) {
-      b.lo = t;
-      b.nlo = n;
-    } else {
-      b.hi = t;
-      b.nhi = n;
-    }
-    // steps in one direction double; the first turn brackets the threshold
-    if (!first && down == in) step = 0u;
-    first = false;
-    down = !in;
-    t = step == 0u ? 0u : (in ? t + step : (t > step ? t - step : 0u));
-    step *= 2u;
-  }
-  // a row with NaN takes the whole-row passes, which give its norm as NaN
-  const bool few = b.lo > 0u && b.nlo <= (uint32_t)kSelCap && !b.nan;
-  if (few) compact(v, __uint_as_float(b.lo), sm, c);
-  return few;
-}
-
-// Halves the bracket over v down to one key: the need-th largest.
-template <int N>
-__device__ __forceinline__ void settle(float (&v)[N], uint32_t need, RSmem& sm, Bracket& b) {
-  while (b.hi - b.lo > 1u) {
-    const uint32_t t = b.lo + (b.hi - b.lo) / 2u;
-    const uint32_t n = count_from(v, t, b.parity, sm.ured);
-    b.parity ^= 1u;
-    if (n >= need) {
-      b.lo = t;
-      b.nlo = n;
-    } else {
-      b.hi = t;
-      b.nhi = n;
-    }
-  }
-}
-
-// The need-th largest key of the row is b.lo, with b.nlo keys from it on and
-// b.nhi above it; true if all of those are in c.
-template <int NPT>
-__device__ __forceinline__ bool select_key(float (&v)[NPT], int p, uint32_t need, RSmem& sm,
-                                           float (&c)[kSelPer], Bracket& b) {
-  const bool few = narrow<NPT>(v, p, need, sm, c, b);
-  if (few)
-    settle<kSelPer>(c, need, sm, b);
-  else
-    settle<NPT>(v, need, sm, b);
-  return few;
-}
-
-// The smallest float above l >= 0: |v| >= float_above(l) is |v| > l.
-__device__ __forceinline__ float float_above(double l) {
-  const float f = (float)l;
-  if (!((double)f <= l)) return f;
-  return f == 0.f ? __uint_as_float(1u) : __uint_as_float(__float_as_uint(f) + 1u);
-}
-
-// Count, sum and sum of squares of the entries with |v| >= f.
-template <int N>
-__device__ __forceinline__ void sums_from(float (&v)[N], float f, double (&b)[3],
-                                          double* scratch) {
-  int n = 0;
-  b[1] = b[2] = 0.0;
-#pragma unroll
-  for (int k = 0; k < N; ++k) {
-    if (k % 4 == 0) __builtin_amdgcn_sched_barrier(0);  // few conversions live at once
-    reload(v[k]);
-    const bool in = fabsf(v[k]) >= f;
-    n += in;
-    const double a = (double)(in ? fabsf(v[k]) : 0.f);
-    b[1] += a;
-    b[2] += a * a;
-  }
-  b[0] = (double)n;
-  block_sum_n<double, 3>(b, scratch);
-}
-
+// ---------------------------------------------------------------------------
+// Register-resident rows, p <= 256 * NPT: a 256-thread block per start, so
+// that every pass is register arithmetic and all starts of a batch are
+// resident on the chip at once (1024 x 10000: 4 blocks a CU).  Reading V and
+// writing X, 82 MB there, takes 17 us of the 27 us of T_s and 32 us of
+// lambda_s; the rest is the passes and their barriers, which all blocks go
+// through in step.  Norm, count and rounds therefore run over the at most
+// 1024 entries that the search left, where there are such (over the whole
+// row: 40 and 50 us; with three LDS histograms a selection and a sort of
+// lambda_s candidates: 53 and 232 us).
+// ---------------------------------------------------------------------------
 // WARM: the sparsity-targeted warm-up (Section 4.1) of the parameter.
 template <int KIND, int NPT, bool WARM>
 __global__ __launch_bounds__(kRT, WARM ? 2 : 4) void x_update_reg_kernel(
@@ -409,68 +151,13 @@ __global__ __launch_bounds__(kRT, WARM ? 2 : 4) void x_update_reg_kernel(
   } else if (KIND == kLambdaS && WARM && !warming) {
     lam = wm.gam[j];  // frozen after the warm-up
   } else if (KIND == kLambdaS) {
-    // The root on a set S of entries, l = (S1 - sqrt(s (k S2 - S1^2) /
-    // (k - s))) / k with k = |S|, S1 = sum |v|, S2 = sum v^2 over S, lies at
-    // or below the row's while S holds every entry above that one (entries
-    // below l only lower the sum and raise the norm).  So each round takes S
-    // to {|v| > l}, and l rises to the row's root, reached when S no longer
-    // changes.  S begins as {|v| >= t} if rho(t) > sqrt(s) there, which
-    // places the root above t, else as all nonzero entries.  t has the 8 s
-    // largest entries or more above it (a row of noise and s larger entries
-    // keeps about 5 s) and at most kSelCap, and the rounds run over those
-    // alone; S from the whole row does so once it has come down to that.
     const double s_par = param;
     const double rs = sqrt(s_par);
-    double set3[3] = {0.0, 0.0, 0.0};
-    bool active = false;
-    float f = 0.f;
-    const double want = 8.0 * s_par < 800.0 ? 8.0 * s_par : 800.0;
-    if (narrow<NPT>(v, p, want < (double)p ? (uint32_t)want : (uint32_t)p, sm, c, br)) {
-      f = __uint_as_float(br.lo);
-      lam = (double)f;
-      sums_from<kSelPer>(c, f, set3, sm.dred);
-      const double l1 = set3[1] - set3[0] * lam;
-      const double l2 = set3[2] - 2.0 * lam * set3[1] + set3[0] * lam * lam;
-      active = l2 > 1e-12 * set3[2] && l1 > (1.0 + 1e-9) * rs * sqrt(l2);
-    }
-    few = active;
+    const bool done = lambda_root<NPT>(v, p, s_par, sm, c, few, br, lam);
     const uint32_t mk = br.mk;
-    if (!active) {
-      lam = 0.0;
-      f = __uint_as_float(1u);
-      sums_from<NPT>(v, f, set3, sm.dred);
-      active = !br.nan && set3[1] > rs * sqrt(set3[2]);  // NaN: lambda = 0
-    }
-    bool done = !active;
-    if (active) {
-#pragma unroll 1
-      for (int round = 0; round < kLamRoundsFull; ++round) {
-        const double kk = set3[0];
-        if (!(kk > s_par)) break;
-        double disc = kk * set3[2] - set3[1] * set3[1];
-        disc = disc > 0.0 ? disc : 0.0;
-        const double l = (set3[1] - sqrt(s_par * disc / (kk - s_par))) / kk;
-        if (!(l > lam)) break;  // rounding: left to the search below
-        if (!few && kk <= (double)kSelCap) {
-          compact(v, f, sm, c);
-          few = true;
-        }
-        f = float_above(l);
-        if (few)
-          sums_from<kSelPer>(c, f, set3, sm.dred);
-        else
-          sums_from<NPT>(v, f, set3, sm.dred);
-        lam = l;
-        if (set3[0] == kk) {  // nested sets of equal size: unchanged
-          done = true;
-          break;
-        }
-      }
-    }
     if (!done) {
       // fallback: FP64 search of the float interval holding the root; reads
       // the row from memory so that the fast path keeps its registers
-      few = false;
       uint32_t lo = 0, hi = mk;
       while (hi - lo > 1) {
         uint32_t t[kNCd];
@@ -536,7 +223,7 @@ __global__ __launch_bounds__(kRT, WARM ? 2 : 4) void x_update_reg_kernel(
     if ((int64_t)wm.target >= (int64_t)p) {
       lam = 0.0;
     } else {
-      select_key<NPT>(v, p, (uint32_t)wm.target + 1u, sm, c, br);
+      (void)select_key<NPT>(v, p, (uint32_t)wm.target + 1u, sm, c, br);
       const double t = (double)__uint_as_float(br.lo);
       lam = KIND == kHardGamma ? t * t : t;
     }
@@ -1306,7 +993,7 @@ void launch_kind(hipStream_t st, double param, const float* V, int64_t ldv,
     launch_reg<KIND, 32>(st, param, V, ldv, r, p, X, ldx, li, lv, ldl, list_cap, s, tol, maxit, colmark, plan, wm);
   else if (per <= 40)
     launch_reg<KIND, 40>(st, param, V, ldv, r, p, X, ldx, li, lv, ldl, list_cap, s, tol, maxit, colmark, plan, wm);
-  else if (per <= 48)
+  else
     launch_reg<KIND, 48>(st, param, V, ldv, r, p, X, ldx, li, lv, ldl, list_cap, s, tol, maxit, colmark, plan, wm);
 }
 
@@ -1317,10 +1004,11 @@ void x_update(hipStream_t st, int fid, double s_or_gamma, const float* V,
               int32_t* list_idx, float* list_val, int64_t ldl, int list_cap,
               StartState s, double tol, int32_t maxit, int32_t* colmark,
               const Plan* plan, void* wide, Warm wm) {
-  if (wide != nullptr &&
-      x_update_wide(st, fid, s_or_gamma, V, ldv, r, p, X, ldx, list_idx, list_val,
-                    ldl, list_cap, s, tol, maxit, colmark, plan, wide, wm))
+  if (p > kWideMinP) {
+    (void)x_update_wide(st, fid, s_or_gamma, V, ldv, r, p, X, ldx, list_idx, list_val,
+                        ldl, list_cap, s, tol, maxit, colmark, plan, wide, wm);
     return;
+  }
   switch (xkind_of(fid)) {
     case kTopS:
       launch_kind<kTopS>(st, s_or_gamma, V, ldv, r, p, X, ldx, list_idx,

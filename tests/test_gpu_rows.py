@@ -23,12 +23,13 @@ def spca():
 
 
 def _rows(p, rng):
-    """Five rows that start the searches at different places."""
-    V = rng.standard_normal((5, p)).astype(np.float32)
+    """Rows that start the searches at different places."""
+    V = rng.standard_normal((6, p)).astype(np.float32)
     V[1, rng.choice(p, min(p, 40), replace=False)] *= 50.0   # a few large entries
     V[2] = rng.integers(-3, 4, size=p)                       # ties everywhere
     V[3] = np.exp(3.0 * V[3]).astype(np.float32)             # heavy tail
     V[4, p // 3:] = 0.0
+    V[5, p // 4:p // 4 + p // 9] *= 20.0                     # large entries crowded together
     return V
 
 
