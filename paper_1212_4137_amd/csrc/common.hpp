@@ -118,6 +118,20 @@ __device__ __forceinline__ T lane_xor(T v) {
   }
 }
 
+// The same for a power of two m that is a constant once the caller's loop is
+// unrolled.
+template <typename T>
+__device__ __forceinline__ T lane_xor_by(T v, int m) {
+  switch (m) {
+    case 1: return lane_xor<1>(v);
+    case 2: return lane_xor<2>(v);
+    case 4: return lane_xor<4>(v);
+    case 8: return lane_xor<8>(v);
+    case 16: return lane_xor<16>(v);
+    default: return lane_xor<32>(v);
+  }
+}
+
 // op over the wave by the butterfly lane ^ 32, 16, 8, 4, 2, 1 (op commutes;
 // from the third step on all rows of 16 agree, so a rotation serves as xor).
 template <typename T, typename Op>

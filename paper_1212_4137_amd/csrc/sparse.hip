@@ -8,7 +8,7 @@
 // are balanced over the nonzeros, not over the columns or rows: word counts
 // follow Zipf's law, so a few columns hold a large share of all nonzeros and
 // a column-per-wave split leaves one wave with most of the work.  Each wave
-// takes a fixed chunk of kW consecutive nonzeros of the compressed layout;
+// takes a fixed chunk of consecutive nonzeros of the compressed layout;
 // every lane group of the wave takes one nonzero at a time and the lanes of a
 // group are the starts, so every stored entry of A meets one contiguous row
 // of the transposed operand.  A column (or row) that lies inside one chunk is
@@ -32,7 +32,15 @@
 namespace spca {
 namespace {
 
-constexpr int64_t kW = 2048;  // nonzeros per wave chunk
+// Nonzeros per wave chunk (kW in the kernels), as a power of two: 2048, and
+// down to 512 (one stage of sp_seg_kernel) where that leaves fewer than 2048
+// chunks, two waves per SIMD.  20000 x 6000 of 1.5 million words, 20 starts: A^T
+// Y 93 us in chunks of 2048, 29 us in chunks of 512.
+inline int chunk_log(int64_t nnz) {
+  int lw = 11;
+  while (lw > 9 && (nnz >> lw) < 2048) --lw;
+  return lw;
+}
 constexpr int kWPB = 4;       // waves per workgroup
 constexpr int kTT = 64;       // tile of the transposed-to-start-major copy
 constexpr int kRB = 8192;     // rows per block, FP32 list product (32 KB LDS)
@@ -71,7 +79,8 @@ __global__ __launch_bounds__(256) void sp_check_idx_kernel(const int32_t* __rest
 // first[w] = the nonempty major (column or row) holding nonzero w * kW
 __global__ __launch_bounds__(256) void sp_first_kernel(const int64_t* __restrict__ ptr,
                                                        int64_t m, int64_t nchunks,
-                                                       int32_t* __restrict__ first) {
+                                                       int32_t* __restrict__ first, int lw) {
+  const int64_t kW = (int64_t)1 << lw;
   const int64_t c = (int64_t)blockIdx.x * 256 + threadIdx.x;
   if (c >= m) return;
   const int64_t cb = ptr[c], ce = ptr[c + 1];
@@ -84,7 +93,8 @@ __global__ __launch_bounds__(256) void sp_first_kernel(const int64_t* __restrict
 // to be valid
 __global__ __launch_bounds__(256) void sp_check_sorted_kernel(
     const int64_t* __restrict__ ptr, const int32_t* __restrict__ idx, int64_t m,
-    int64_t nnz, const int32_t* __restrict__ first, int32_t* bad) {
+    int64_t nnz, const int32_t* __restrict__ first, int32_t* bad, int lw) {
+  const int64_t kW = (int64_t)1 << lw;
   const int lane = threadIdx.x % kWave;
   const int64_t w =
       (int64_t)blockIdx.x * kWPB + __builtin_amdgcn_readfirstlane(threadIdx.x / kWave);
@@ -190,7 +200,8 @@ __global__ __launch_bounds__(256) void sp_pan_copy_kernel(
     const int64_t* __restrict__ src, const int64_t* __restrict__ pptr, int64_t len,
     int64_t nnz, const int32_t* __restrict__ pfirst, const int32_t* __restrict__ row_idx,
     const float* __restrict__ col_val, int32_t* __restrict__ pidx,
-    float* __restrict__ pval) {
+    float* __restrict__ pval, int lw) {
+  const int64_t kW = (int64_t)1 << lw;
   const int lane = threadIdx.x % kWave;
   const int64_t w =
       (int64_t)blockIdx.x * kWPB + __builtin_amdgcn_readfirstlane(threadIdx.x / kWave);
@@ -242,7 +253,8 @@ __global__ __launch_bounds__(256) void sp_seg_kernel(
     const float* __restrict__ val, int64_t m, int64_t nnz,
     const int32_t* __restrict__ first, const float* __restrict__ BT, int64_t ldb, int64_t r,
     float* __restrict__ OT, int64_t ldo, float* __restrict__ carry, const Plan* plan,
-    int gate) {
+    int gate, int lw) {
+  const int64_t kW = (int64_t)1 << lw;
   constexpr int NPI = kWave / L;      // nonzeros per load instruction
   constexpr int NS = kU * NPI;        // nonzeros per step
   static_assert(kSS % NS == 0 && kU % 4 == 0, "a stage holds whole steps");
@@ -295,10 +307,10 @@ __global__ __launch_bounds__(256) void sp_seg_kernel(
   auto flush = [&](float4 a, int64_t c, int64_t cb, int64_t ce) {
 #pragma unroll
     for (int off = L; off < kWave; off <<= 1) {
-      a.x += __shfl_xor(a.x, off, kWave);
-      a.y += __shfl_xor(a.y, off, kWave);
-      a.z += __shfl_xor(a.z, off, kWave);
-      a.w += __shfl_xor(a.w, off, kWave);
+      a.x += lane_xor_by(a.x, off);
+      a.y += lane_xor_by(a.y, off);
+      a.z += lane_xor_by(a.z, off);
+      a.w += lane_xor_by(a.w, off);
     }
     if (slot == 0 && j0 < r) {
       const bool whole = cb >= lo && ce <= hi;
@@ -400,7 +412,8 @@ __global__ __launch_bounds__(256) void sp_fix_kernel(const int64_t* __restrict__
                                                      int64_t nsplit,
                                                      const float* __restrict__ carry,
                                                      int64_t r, float* __restrict__ OT,
-                                                     int64_t ldo, const Plan* plan, int gate) {
+                                                     int64_t ldo, const Plan* plan, int gate,
+                                                     int lw) {
   if ((gate & kGateDense) && plan->mode != kAxDense) return;
   if ((gate & kGateActive) && plan->active == 0) return;
   const int64_t k =
@@ -409,8 +422,8 @@ __global__ __launch_bounds__(256) void sp_fix_kernel(const int64_t* __restrict__
   const int lane = threadIdx.x % kWave;
   const int64_t c = split[k];
   const int64_t cb = ptr[c], ce = ptr[c + 1];
-  const int64_t w0 = cb / kW, w1 = (ce - 1) / kW;
-  const int64_t s0 = cb == w0 * kW ? 0 : 1;
+  const int64_t w0 = cb >> lw, w1 = (ce - 1) >> lw;
+  const int64_t s0 = cb == w0 << lw ? 0 : 1;
   for (int64_t j = lane; j < r; j += kWave) {
     float acc = carry[(w0 * 2 + s0) * ldo + j];
 #pragma unroll 8
@@ -422,11 +435,11 @@ __global__ __launch_bounds__(256) void sp_fix_kernel(const int64_t* __restrict__
 // the nonempty majors crossing a chunk boundary, in any order
 __global__ __launch_bounds__(256) void sp_split_list_kernel(const int64_t* __restrict__ ptr,
                                                             int64_t m, int32_t* split,
-                                                            int32_t* count) {
+                                                            int32_t* count, int lw) {
   const int64_t c = (int64_t)blockIdx.x * 256 + threadIdx.x;
   if (c >= m) return;
   const int64_t cb = ptr[c], ce = ptr[c + 1];
-  if (cb < ce && cb / kW != (ce - 1) / kW) split[atomicAdd(count, 1)] = (int32_t)c;
+  if (cb < ce && cb >> lw != (ce - 1) >> lw) split[atomicAdd(count, 1)] = (int32_t)c;
 }
 
 // O[j][c] = sum over the npan panels of OT[P m + c][j] (in panel order),
@@ -558,39 +571,74 @@ __device__ __forceinline__ int64_t wave_lower_bound(const int32_t* __restrict__ 
   return lo + cnt;
 }
 
-// rows [b0, b1) of the running start j's u = sum over its support columns
-__global__ __launch_bounds__(256) void sp_list_rows_kernel(
+// rows [b0, b1) of the running start j's u = sum over its support columns,
+// column by column.  A column's share is a few hundred nonzeros, so the time
+// is latency: the searches of a tile of columns run side by side, a wave each,
+// and the next column's first nonzeros are loaded while one is added (20000 x
+// 6000, supports of 8, 20 starts: 68 us with both in line, 22 us so).
+constexpr int kLT = 1024;      // threads
+constexpr int kListTile = 64;  // columns searched at a time
+
+__global__ __launch_bounds__(kLT) void sp_list_rows_kernel(
     const int64_t* __restrict__ col_ptr, const int32_t* __restrict__ row_idx,
     const float* __restrict__ val, int64_t n, const int32_t* __restrict__ list_idx,
     const float* __restrict__ list_val, int64_t ldl, float* __restrict__ U, int64_t ldu,
     StartState s, const Plan* plan) {
   __shared__ float ub[kRB];
-  __shared__ int64_t bnd[2];
+  __shared__ int64_t bnd[2 * kListTile];
+  __shared__ float xs[kListTile];
   if (plan->mode != kAxListRows) return;
   const int64_t j = blockIdx.y;
   if (s.status[j] != kRunning) return;
   const int64_t b0 = (int64_t)blockIdx.x * kRB;
   const int64_t b1 = b0 + kRB < n ? b0 + kRB : n;
-  const int wave = threadIdx.x / kWave;
-  for (int i = threadIdx.x; i < kRB; i += 256) ub[i] = 0.f;
+  const int tid = threadIdx.x;
+  const int wave = __builtin_amdgcn_readfirstlane(tid / kWave);
+  for (int i = tid; i < kRB; i += kLT) ub[i] = 0.f;
   const int32_t cnt = s.nnz[j];
-  for (int32_t t = 0; t < cnt; ++t) {
-    const int32_t c = list_idx[j * ldl + t];
-    const float x = list_val[j * ldl + t];
-    const int64_t cb = col_ptr[c], ce = col_ptr[c + 1];
-    if (wave < 2) {
-      const int64_t pos = wave_lower_bound(row_idx, cb, ce, wave == 0 ? b0 : b1);
-      if (threadIdx.x % kWave == 0) bnd[wave] = pos;
+  for (int32_t t0 = 0; t0 < cnt; t0 += kListTile) {
+    const int m = cnt - t0 < kListTile ? cnt - t0 : kListTile;
+    for (int q = wave; q < 2 * m; q += kLT / kWave) {
+      const int32_t c = list_idx[j * ldl + t0 + q / 2];
+      const int64_t cb = col_ptr[c], ce = col_ptr[c + 1];
+      int64_t pos;
+      if (q % 2 == 0)
+        pos = b0 == 0 ? cb : wave_lower_bound(row_idx, cb, ce, b0);
+      else
+        pos = b1 == n ? ce : wave_lower_bound(row_idx, cb, ce, b1);
+      if (tid % kWave == 0) bnd[q] = pos;
     }
+    if (tid < m) xs[tid] = list_val[j * ldl + t0 + tid];
     __syncthreads();
-    const int64_t kb = bnd[0], ke = bnd[1];
-    for (int64_t k = kb + threadIdx.x; k < ke; k += 256) {
-      const int64_t i = row_idx[k];
-      if (i >= b0 && i < b1) ub[i - b0] += val[k] * x;
+    int64_t k = bnd[0] + tid;
+    int32_t i = k < bnd[1] ? row_idx[k] : -1;
+    float v = k < bnd[1] ? val[k] : 0.f;
+    for (int t = 0; t < m; ++t) {
+      const int64_t ke = bnd[2 * t + 1];
+      const float x = xs[t];
+      int64_t kn = 0;
+      int32_t in = -1;
+      float vn = 0.f;
+      if (t + 1 < m) {
+        kn = bnd[2 * t + 2] + tid;
+        if (kn < bnd[2 * t + 3]) {
+          in = row_idx[kn];
+          vn = val[kn];
+        }
+      }
+      if (k < ke && i >= b0 && i < b1) ub[i - b0] += v * x;
+      for (k += kLT; k < ke; k += kLT) {
+        i = row_idx[k];
+        if (i >= b0 && i < b1) ub[i - b0] += val[k] * x;
+      }
+      __syncthreads();
+      k = kn;
+      i = in;
+      v = vn;
     }
-    __syncthreads();
   }
-  for (int64_t i = threadIdx.x; b0 + i < b1; i += 256) U[j * ldu + b0 + i] = ub[i];
+  __syncthreads();
+  for (int64_t i = tid; b0 + i < b1; i += kLT) U[j * ldu + b0 + i] = ub[i];
 }
 
 // FP64 evaluation: rows [b0, b1) of u = A x / ||x||_2, then the block's
@@ -687,16 +735,17 @@ void launch_seg(hipStream_t st, const int64_t* ptr, const int32_t* idx, const fl
                 int64_t m, int64_t nnz, const int32_t* first, const float* BT, int64_t ldb,
                 int64_t minor, int64_t r, float* OT, int64_t ldo, float* carry,
                 const Plan* plan, int gate) {
-  const int64_t nchunks = ceil_div(nnz, kW);
+  const int64_t nchunks = sparse_chunks(nnz);
+  const int lw = chunk_log(nnz);
   if (nchunks == 0) return;
   const dim3 g((unsigned)ceil_div(nchunks, (int64_t)kWPB), (unsigned)seg_blocks(r));
   // BT (minor rows of ldb floats) within 4 GiB: 32-bit address arithmetic
   if (minor * ldb * (int64_t)sizeof(float) <= (int64_t)UINT32_MAX)
     hipLaunchKernelGGL((sp_seg_kernel<L, true>), g, dim3(256), 0, st, ptr, idx, val, m, nnz,
-                       first, BT, ldb, r, OT, ldo, carry, plan, gate);
+                       first, BT, ldb, r, OT, ldo, carry, plan, gate, lw);
   else
     hipLaunchKernelGGL((sp_seg_kernel<L, false>), g, dim3(256), 0, st, ptr, idx, val, m, nnz,
-                       first, BT, ldb, r, OT, ldo, carry, plan, gate);
+                       first, BT, ldb, r, OT, ldo, carry, plan, gate, lw);
 }
 
 // O (r x mo, start-major, ld) = the product of A's compressed layout (ptr,
@@ -727,7 +776,8 @@ void seg_product(hipStream_t st, const int64_t* ptr, const int32_t* idx, const f
   }
   if (nsplit > 0)
     hipLaunchKernelGGL(sp_fix_kernel, dim3((unsigned)ceil_div(nsplit, (int64_t)kWPB)),
-                       dim3(256), 0, st, ptr, split, nsplit, carry, r, OT, ldo, plan, gate);
+                       dim3(256), 0, st, ptr, split, nsplit, carry, r, OT, ldo, plan, gate,
+                       chunk_log(nnz));
   const dim3 g((unsigned)ceil_div(mo, (int64_t)kTT), (unsigned)ceil_div(r, (int64_t)kTT));
   hipLaunchKernelGGL(sp_to_starts_kernel, g, dim3(256), 0, st, OT, ldo, mo, r,
                      npan > 0 ? npan : 1, O, ld, plan, gate);
@@ -735,7 +785,7 @@ void seg_product(hipStream_t st, const int64_t* ptr, const int32_t* idx, const f
 
 }  // namespace
 
-int64_t sparse_chunks(int64_t nnz) { return ceil_div(nnz, kW); }
+int64_t sparse_chunks(int64_t nnz) { return ceil_div(nnz, (int64_t)1 << chunk_log(nnz)); }
 // rows of the transposed operands: a power of two of at least 8 floats up to
 // 64 starts (one 128-byte line for 17 .. 32), then whole blocks of 64
 int64_t sparse_ld(int64_t r) { return seg_blocks(r) * 4 * seg_lanes(r); }
@@ -757,11 +807,11 @@ int64_t sparse_panel_tmp(int32_t npan, int64_t p) {
 void sparse_split_lists(hipStream_t st, const SparseA& a, int32_t* counts) {
   if (a.nnz == 0) return;
   hipLaunchKernelGGL(sp_split_list_kernel, dim3((unsigned)ceil_div(a.n, (int64_t)256)),
-                     dim3(256), 0, st, a.row_ptr, a.n, a.row_split, counts);
+                     dim3(256), 0, st, a.row_ptr, a.n, a.row_split, counts, chunk_log(a.nnz));
   const int64_t mc = a.npan > 0 ? a.npan * a.p : a.p;
   hipLaunchKernelGGL(sp_split_list_kernel, dim3((unsigned)ceil_div(mc, (int64_t)256)),
                      dim3(256), 0, st, a.npan > 0 ? a.pptr : a.col_ptr, mc, a.col_split,
-                     counts + 1);
+                     counts + 1, chunk_log(a.nnz));
 }
 
 void sparse_build_panels(hipStream_t st, SparseA& a) {
@@ -779,10 +829,10 @@ void sparse_build_panels(hipStream_t st, SparseA& a) {
   const int64_t nch = sparse_chunks(a.nnz);
   (void)hipMemsetAsync(a.pfirst, 0, sizeof(int32_t) * nch, st);
   hipLaunchKernelGGL(sp_first_kernel, dim3((unsigned)ceil_div(len, (int64_t)256)), dim3(256),
-                     0, st, a.pptr, len, nch, a.pfirst);
+                     0, st, a.pptr, len, nch, a.pfirst, chunk_log(a.nnz));
   hipLaunchKernelGGL(sp_pan_copy_kernel, dim3((unsigned)ceil_div(nch, (int64_t)kWPB)),
                      dim3(256), 0, st, src, a.pptr, len, a.nnz, a.pfirst, a.row_idx,
-                     a.col_val, a.pidx, a.pval);
+                     a.col_val, a.pidx, a.pval, chunk_log(a.nnz));
 }
 
 int64_t sparse_final_parts(int64_t n) { return ceil_div(n, (int64_t)kRB64); }
@@ -804,11 +854,12 @@ void sparse_prepare(hipStream_t st, const SparseA& a, int32_t* bad) {
   (void)hipMemsetAsync(a.col_first, 0, sizeof(int32_t) * nch, st);
   (void)hipMemsetAsync(a.row_first, 0, sizeof(int32_t) * nch, st);
   hipLaunchKernelGGL(sp_first_kernel, dim3((unsigned)ceil_div(a.p, (int64_t)256)), dim3(256),
-                     0, st, a.col_ptr, a.p, nch, a.col_first);
+                     0, st, a.col_ptr, a.p, nch, a.col_first, chunk_log(a.nnz));
   hipLaunchKernelGGL(sp_first_kernel, dim3((unsigned)ceil_div(a.n, (int64_t)256)), dim3(256),
-                     0, st, a.row_ptr, a.n, nch, a.row_first);
+                     0, st, a.row_ptr, a.n, nch, a.row_first, chunk_log(a.nnz));
   hipLaunchKernelGGL(sp_check_sorted_kernel, dim3((unsigned)ceil_div(nch, (int64_t)kWPB)),
-                     dim3(256), 0, st, a.col_ptr, a.row_idx, a.p, a.nnz, a.col_first, bad);
+                     dim3(256), 0, st, a.col_ptr, a.row_idx, a.p, a.nnz, a.col_first, bad,
+                     chunk_log(a.nnz));
 }
 
 void sparse_ax_dense(hipStream_t st, const SparseA& a, const float* XT, int64_t ldxt,
@@ -852,7 +903,7 @@ void sparse_ax_list(hipStream_t st, const SparseA& a, const int32_t* list_idx,
                     StartState s, const Plan* plan) {
   if (a.n == 0) return;
   const dim3 g((unsigned)ceil_div(a.n, (int64_t)kRB), (unsigned)r);
-  hipLaunchKernelGGL(sp_list_rows_kernel, g, dim3(256), 0, st, a.col_ptr, a.row_idx,
+  hipLaunchKernelGGL(sp_list_rows_kernel, g, dim3(kLT), 0, st, a.col_ptr, a.row_idx,
                      a.col_val, a.n, list_idx, list_val, ldl, U, ldu, s, plan);
 }
 

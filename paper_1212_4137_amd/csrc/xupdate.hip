@@ -420,18 +420,6 @@ struct CSmem {
   double seg[4];
 };
 
-// The value of lane ^ m (m is a constant once the callers' loops are unrolled).
-__device__ __forceinline__ uint64_t shfl_xor_u64(uint64_t x, int m) {
-  switch (m) {
-    case 1: return lane_xor<1>(x);
-    case 2: return lane_xor<2>(x);
-    case 4: return lane_xor<4>(x);
-    case 8: return lane_xor<8>(x);
-    case 16: return lane_xor<16>(x);
-    default: return lane_xor<32>(x);
-  }
-}
-
 // Ascending bitonic sort of kRT E keys: x[e] is element tid + kRT e.
 // Partners fewer than 64 apart are in the same wave (shuffles), 64 and 128
 // apart in another wave (through buf, kRT E keys of LDS), kRT and more
@@ -466,7 +454,7 @@ __device__ __forceinline__ void block_sort_asc(uint64_t (&x)[E], uint64_t* buf) 
 #pragma unroll
         for (int e = 0; e < E; ++e) {
           const int i = tid + kRT * e;
-          const uint64_t b = stride >= kWave ? buf[i ^ stride] : shfl_xor_u64(x[e], stride);
+          const uint64_t b = stride >= kWave ? buf[i ^ stride] : lane_xor_by(x[e], stride);
           const bool lower = (i & stride) == 0;
           const bool asc = (i & size) == 0;
           const uint64_t mn = x[e] < b ? x[e] : b;
@@ -510,7 +498,7 @@ __device__ __forceinline__ void sort_wave_lds(uint64_t* arr, int n, uint64_t pad
     for (int size = 2; size <= kWave; size <<= 1) {
 #pragma unroll
       for (int stride = size >> 1; stride > 0; stride >>= 1) {
-        const uint64_t b = shfl_xor_u64(x, stride);
+        const uint64_t b = lane_xor_by(x, stride);
         const bool lower = (lane & stride) == 0;
         const bool asc = (lane & size) == 0;
         const uint64_t mn = x < b ? x : b;
