@@ -633,6 +633,21 @@ GemmPlan model_plan_gemm_nt(int64_t M, int64_t N, int64_t K, int max_splits,
   return best;
 }
 
+// Microseconds per slab of 64 K and round of workgroups, by shape, on a chip that
+// is less than full: a workgroup waits for each slab (measured over the same
+// products as the tiles of gemm_bf16.hip; long K costs up to half more, which
+// leaves the other side ahead there all the more).
+double gemm_bf16_us(int64_t M, int64_t N, int64_t K, int shape) {
+  constexpr double kStep[] = {1.5, 1.7, 1.15, 1.2, 1.5, 0.78, 1.5, 2.0, 2.6, 2.6, 2.6, 1.3};
+  static_assert(sizeof(kStep) / sizeof(kStep[0]) == kNumShapes, "one step per shape");
+  const Shape& sh = kShapes[shape];
+  const int64_t tiles = ceil_div(M, (int64_t)sh.bm) * ceil_div(N, (int64_t)sh.bn);
+  double step = kStep[shape];
+  if (sh.bm == 32) step += 0.3 * (tiles < 300 ? (double)tiles / 300.0 : 1.0);
+  return 3.0 + (double)ceil_div(tiles, (int64_t)256 * sh.occ) *
+                   (double)ceil_div(K, (int64_t)64) * step;
+}
+
 int gemm_num_shapes() { return kNumShapes; }
 int gemm_shape_bm(int shape) {
   if (shape >= kSplitShape0) return split_shape_bm(shape);

@@ -201,6 +201,13 @@ void gemm_nt_bf16(hipStream_t st, const uint16_t* P, int64_t ldp,
                   const uint16_t* Q, int64_t ldq, float* C, int64_t ldc,
                   int64_t M, int64_t N, int64_t K, const int32_t* gate,
                   int32_t gate_run, GemmPlan plan, int64_t split_stride);
+// The unsplit product with K shared by the waves of small tiles (gemm_bf16.hip);
+// false (nothing launched) where that takes longer than other_us.
+bool gemm_nt_bf16_ks(hipStream_t st, const uint16_t* P, int64_t ldp, const uint16_t* Q,
+                     int64_t ldq, float* C, int64_t ldc, int64_t M, int64_t N, int64_t K,
+                     double other_us);
+// Estimated microseconds of an unsplit product with a BF16 tile of gemm_nt_kernel.
+double gemm_bf16_us(int64_t M, int64_t N, int64_t K, int shape);
 
 // Grouped products (requests sharing one launch): product q computes
 // C = P * Q^T (M x N x K, leading dimensions ldp, ldq, ldc) with its own K

@@ -1576,8 +1576,12 @@ int spca_gemm_nt_bf16(void* stream, const uint16_t* P, int64_t ldp,
                "ldp and ldq must be multiples of 8");
   SPCA_REQUIRE((uintptr_t)P % 16 == 0 && (uintptr_t)Q % 16 == 0,
                "P and Q must be 16-byte aligned");
-  gemm_nt_bf16((hipStream_t)stream, P, ldp, Q, ldq, C, ldc, M, N, K, nullptr, 0,
-               plan_gemm_nt(M, N, K, 1, 2), 0);
+  const GemmPlan g = plan_gemm_nt(M, N, K, 1, 2);
+  GemmPlan tuned;  // a tuning table entry holds
+  if (tuned_plan(M, N, K, 1, 2, &tuned) ||
+      !gemm_nt_bf16_ks((hipStream_t)stream, P, ldp, Q, ldq, C, ldc, M, N, K,
+                       gemm_bf16_us(M, N, K, g.shape)))
+    gemm_nt_bf16((hipStream_t)stream, P, ldp, Q, ldq, C, ldc, M, N, K, nullptr, 0, g, 0);
   SPCA_LAUNCH_CHECK("gemm_nt_bf16");
   return SPCA_OK;
 }
