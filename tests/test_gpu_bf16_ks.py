@@ -38,3 +38,19 @@ def test_bf16_products_match_fp64(spca, M, N, K):
     # FP32 accumulation: one rounding a term at most
     bound = (np.abs(P64) @ np.abs(Q64).T) * (K * 2.0 ** -24) * 1.01 + 1e-30
     assert np.all(np.abs(C - P64 @ Q64.T) <= bound)
+
+
+@pytest.mark.parametrize("M,N,K", [(255, 50001, 3001), (511, 25003, 3007), (250, 52000, 2111),
+                                   (129, 50001, 3001), (256, 57344, 3072)])
+def test_large_bf16_tiles_match_fp64(spca, M, N, K):
+    print(f"bf16 M={M} N={N} K={K}", flush=True)
+    ld = (K + 7) // 8 * 8
+    g = torch.Generator(device="cuda").manual_seed(M + N + K)
+    P = torch.full((M, ld), float("nan"), dtype=torch.bfloat16, device="cuda")
+    Q = torch.full((N, ld), float("nan"), dtype=torch.bfloat16, device="cuda")
+    P[:, :K] = torch.randn(M, K, generator=g, device="cuda").bfloat16()
+    Q[:, :K] = torch.randn(N, K, generator=g, device="cuda").bfloat16()
+    C = spca.gemm_nt_bf16(P[:, :K], Q[:, :K]).double()
+    P64, Q64 = P[:, :K].double(), Q[:, :K].double()
+    bound = (P64.abs() @ Q64.abs().t()) * (K * 2.0 ** -24) * 1.01 + 1e-30
+    assert bool(torch.all((C - P64 @ Q64.t()).abs() <= bound))
