@@ -4,6 +4,8 @@
 // y = sgn(u) or u / ||u||_2 (Table 3, rows S1 and S2).
 #include <algorithm>
 
+#include <type_traits>
+
 #include "../../include/spca.h"
 #include "common.hpp"
 #include "kernels.hpp"
@@ -740,7 +742,11 @@ void launch_sparse(hipStream_t st, const TA* A, int64_t lda, int64_t n,
 
 // Row-block list product: workgroup (c, j) forms rows [1024 c, 1024 c + 1024)
 // of u_j = sum_t A[:, idx_t] val_t, each thread four consecutive rows with
-// 16-byte loads, in list order, in FP64.
+// 16-byte loads, in list order, in FP64.  Few starts leave a CU with a
+// workgroup or less, so the loads of kRowsAhead list entries are in flight at
+// once (2000 x 20000, 64 starts, 60 entries: 23 us one entry at a time,
+// 9 us so).
+constexpr int kRowsAhead = 16;
 constexpr int kRowsBlock = 4 * kSpThreads;
 static_assert(kRowsBlock == kRowsBlockN, "row-block height");
 
@@ -767,20 +773,34 @@ __global__ __launch_bounds__(kSpThreads) void sparse_ax_rows_kernel(
       sval[threadIdx.x] = list_val[j * ldl + t0 + threadIdx.x];
     }
     __syncthreads();
-    if (row < n) {
+    if (full) {
+      int32_t t = 0;
+      auto step = [&](auto ahead) {
+        constexpr int E = decltype(ahead)::value;
+        for (; t + E <= m; t += E) {
+          floatx4_t a[E];
+#pragma unroll
+          for (int e = 0; e < E; ++e) a[e] = load4(A + (int64_t)sidx[t + e] * lda, row);
+          __builtin_amdgcn_sched_barrier(0);  // all loads before the first sum
+#pragma unroll
+          for (int e = 0; e < E; ++e) {
+            const double w = (double)sval[t + e];
+            acc[0] += (double)a[e].x * w;
+            acc[1] += (double)a[e].y * w;
+            acc[2] += (double)a[e].z * w;
+            acc[3] += (double)a[e].w * w;
+          }
+        }
+      };
+      step(std::integral_constant<int, kRowsAhead>{});
+      step(std::integral_constant<int, 4>{});
+      step(std::integral_constant<int, 1>{});
+    } else if (row < n) {
       for (int32_t t = 0; t < m; ++t) {
         const TA* c = A + (int64_t)sidx[t] * lda;
         const double w = (double)sval[t];
-        if (full) {
-          const floatx4_t a = load4(c, row);
-          acc[0] += (double)a.x * w;
-          acc[1] += (double)a.y * w;
-          acc[2] += (double)a.z * w;
-          acc[3] += (double)a.w * w;
-        } else {
-          for (int e = 0; e < 4; ++e)
-            if (row + e < n) acc[e] += (double)load1(c, row + e) * w;
-        }
+        for (int e = 0; e < 4; ++e)
+          if (row + e < n) acc[e] += (double)load1(c, row + e) * w;
       }
     }
   }
