@@ -71,27 +71,16 @@ __device__ __forceinline__ void rscan2(double (&v)[2], double* scratch) {
 // ---------------------------------------------------------------------------
 // WARM: the sparsity-targeted warm-up (Section 4.1) of the parameter.
 template <int KIND, int NPT, bool WARM>
-__global__ __launch_bounds__(kRT, WARM ? 2 : 4) void x_update_reg_kernel(
+__device__ __forceinline__ void full_update(
     const float* __restrict__ V, int64_t ldv, int p, double param,
     float* __restrict__ X, int64_t ldx, int32_t* __restrict__ list_idx,
-    float* __restrict__ list_val, int64_t ldl, int list_cap, StartState s,
+    float* __restrict__ list_val, int64_t ldl, int list_cap, const StartState& s,
     double tol, int maxit, int32_t* __restrict__ colmark, const Plan* plan,
-    Warm wm) {
+    const Warm& wm, RSmem& sm) {
   static_assert(NPT % 4 == 0, "NPT must be a multiple of 4");
-  __shared__ RSmem sm;
   const int64_t j = blockIdx.x;
   const bool full = s.status != nullptr;
-  if (full && s.status[j] != kRunning) return;
-  if (s.cfg != nullptr) {  // grouped solve: this start's request
-    if (s.cfg[j].kind != KIND) return;
-    param = s.cfg[j].param;
-    tol = s.cfg[j].tol;
-    maxit = s.cfg[j].maxit;
-  }
-  // after the candidate kernel: only the rows it could not settle
-  if (s.redo != nullptr && s.redo[j] == 0) return;
   const int tid = threadIdx.x;
-  const int lane = tid % kWave;
   // Striped rows: element 4 (q kRT + tid) + e is v[4 q + e], so that each
   // 16-byte load and store instruction covers 1 KB of contiguous memory.
   constexpr int R = NPT / 4;
@@ -375,6 +364,35 @@ __global__ __launch_bounds__(kRT, WARM ? 2 : 4) void x_update_reg_kernel(
   }
 }
 
+// The request of a grouped solve's start (its settings replace the launch's);
+// false when it takes another operator.
+__device__ __forceinline__ bool start_settings(const StartState& s, int64_t j, int kind,
+                                               double& param, double& tol, int& maxit) {
+  if (s.cfg == nullptr) return true;
+  if (s.cfg[j].kind != kind) return false;
+  param = s.cfg[j].param;
+  tol = s.cfg[j].tol;
+  maxit = s.cfg[j].maxit;
+  return true;
+}
+
+template <int KIND, int NPT, bool WARM>
+__global__ __launch_bounds__(kRT, WARM ? 2 : 4) void x_update_reg_kernel(
+    const float* __restrict__ V, int64_t ldv, int p, double param,
+    float* __restrict__ X, int64_t ldx, int32_t* __restrict__ list_idx,
+    float* __restrict__ list_val, int64_t ldl, int list_cap, StartState s,
+    double tol, int maxit, int32_t* __restrict__ colmark, const Plan* plan,
+    Warm wm) {
+  __shared__ RSmem sm;
+  const int64_t j = blockIdx.x;
+  if (s.status != nullptr && s.status[j] != kRunning) return;
+  if (!start_settings(s, j, KIND, param, tol, maxit)) return;
+  // after the candidate kernel: only the rows it could not settle
+  if (s.redo != nullptr && s.redo[j] == 0) return;
+  full_update<KIND, NPT, WARM>(V, ldv, p, param, X, ldx, list_idx, list_val, ldl, list_cap, s,
+                               tol, maxit, colmark, plan, wm, sm);
+}
+
 // ---------------------------------------------------------------------------
 // Candidate x-update for T_s and V_{lambda_s} (register-resident rows,
 // inside a solve).  Near convergence the selection threshold moves little
@@ -539,28 +557,20 @@ __device__ __forceinline__ double fixed_sum(int m, F f, double* slot) {
   return r;
 }
 
+// False (nothing written) for a row it cannot settle.
 template <int KIND, int NPT>
-__global__ __launch_bounds__(kRT, 4) void x_update_cand_kernel(
+__device__ __forceinline__ bool cand_update(
     const float* __restrict__ V, int64_t ldv, int p, double param,
     float* __restrict__ X, int64_t ldx, int32_t* __restrict__ list_idx,
-    float* __restrict__ list_val, int64_t ldl, int list_cap, StartState s,
-    double tol, int maxit, int32_t* __restrict__ colmark, const Plan* plan) {
+    float* __restrict__ list_val, int64_t ldl, int list_cap, const StartState& s,
+    double tol, int maxit, int32_t* __restrict__ colmark, const Plan* plan, CSmem& sm) {
   static_assert(KIND == kTopS || KIND == kLambdaS, "T_s and lambda_s only");
   static_assert(kRT * NPT <= (int)kIdxMask + 1, "row indices must fit the sort key");
-  __shared__ CSmem sm;
   const int64_t j = blockIdx.x;
-  if (s.status[j] != kRunning) return;
-  if (s.cfg != nullptr) {  // grouped solve: this start's request
-    if (s.cfg[j].kind != KIND) return;
-    param = s.cfg[j].param;
-    tol = s.cfg[j].tol;
-    maxit = s.cfg[j].maxit;
-  }
   const int tid = threadIdx.x;
   const uint32_t t0 = key_of(s.thr[j] * kGuessLow);
   if (t0 == 0u) {  // no guess yet
-    if (tid == 0) s.redo[j] = 1;
-    return;
+    return false;
   }
   auto gidx = [&](int k) { return 4 * ((k / 4) * kRT + tid) + k % 4; };
   const float* vg = V + j * ldv;
@@ -685,7 +695,6 @@ __global__ __launch_bounds__(kRT, 4) void x_update_cand_kernel(
         }
       }
       if (tid == 0) {
-        s.redo[j] = 0;
         s.thr[j] = zero ? 0.f : (float)lam;
         const int it = s.iters[j] + 1;
         const double prev = s.phi[j];
@@ -700,7 +709,7 @@ __global__ __launch_bounds__(kRT, 4) void x_update_cand_kernel(
         else if (it >= maxit)
           s.status[j] = SPCA_MAXIT;
       }
-      return;
+      return true;
     }
   }
   // the candidate at sorted position q
@@ -755,8 +764,7 @@ __global__ __launch_bounds__(kRT, 4) void x_update_cand_kernel(
     }
   }
   if (!ok) {
-    if (tid == 0) s.redo[j] = 1;
-    return;
+    return false;
   }
   int nc;
   int off = block_exclusive_scan(mine, sm.scan, &nc);
@@ -828,8 +836,7 @@ __global__ __launch_bounds__(kRT, 4) void x_update_cand_kernel(
     }
     __syncthreads();
     if (kb == INT32_MAX) {  // rounding at the lower end: leave it to the full kernel
-      if (tid == 0) s.redo[j] = 1;
-      return;
+      return false;
     }
     const double k = (double)kb, S1b = sm.seg[0], S2b = sm.seg[1];
     double disc = k * S2b - S1b * S1b;
@@ -921,7 +928,6 @@ __global__ __launch_bounds__(kRT, 4) void x_update_cand_kernel(
     }
   }
   if (tid == 0) {
-    s.redo[j] = 0;
     s.thr[j] = zero ? 0.f : (KIND == kTopS ? __uint_as_float(thr_key) : (float)lam);
     const int it = s.iters[j] + 1;
     const double prev = s.phi[j];
@@ -936,6 +942,49 @@ __global__ __launch_bounds__(kRT, 4) void x_update_cand_kernel(
     else if (it >= maxit)
       s.status[j] = SPCA_MAXIT;
   }
+  return true;
+}
+
+template <int KIND, int NPT>
+__global__ __launch_bounds__(kRT, 4) void x_update_cand_kernel(
+    const float* __restrict__ V, int64_t ldv, int p, double param,
+    float* __restrict__ X, int64_t ldx, int32_t* __restrict__ list_idx,
+    float* __restrict__ list_val, int64_t ldl, int list_cap, StartState s,
+    double tol, int maxit, int32_t* __restrict__ colmark, const Plan* plan) {
+  __shared__ CSmem sm;
+  const int64_t j = blockIdx.x;
+  if (s.status[j] != kRunning) return;
+  if (!start_settings(s, j, KIND, param, tol, maxit)) return;
+  const bool done = cand_update<KIND, NPT>(V, ldv, p, param, X, ldx, list_idx, list_val, ldl,
+                                           list_cap, s, tol, maxit, colmark, plan, sm);
+  if (threadIdx.x == 0) s.redo[j] = !done;
+}
+
+// Both in one launch, for rows short enough that the registers of the two fit
+// together without spills: the launch after the candidates, mostly empty, costs
+// 2 to 5 us of an iteration of 40 to 60 (100 x 500 with one start; 8 requests
+// of 16 starts).
+constexpr int kBothMax = 24;  // floats a thread
+
+template <int KIND, int NPT>
+__global__ __launch_bounds__(kRT, 4) void x_update_both_kernel(
+    const float* __restrict__ V, int64_t ldv, int p, double param,
+    float* __restrict__ X, int64_t ldx, int32_t* __restrict__ list_idx,
+    float* __restrict__ list_val, int64_t ldl, int list_cap, StartState s,
+    double tol, int maxit, int32_t* __restrict__ colmark, const Plan* plan) {
+  __shared__ union {
+    CSmem cand;
+    RSmem full;
+  } sm;
+  const int64_t j = blockIdx.x;
+  if (s.status[j] != kRunning) return;
+  if (!start_settings(s, j, KIND, param, tol, maxit)) return;
+  if (cand_update<KIND, NPT>(V, ldv, p, param, X, ldx, list_idx, list_val, ldl, list_cap, s, tol,
+                             maxit, colmark, plan, sm.cand))
+    return;
+  __syncthreads();  // the shared memory changes hands
+  full_update<KIND, NPT, false>(V, ldv, p, param, X, ldx, list_idx, list_val, ldl, list_cap, s,
+                                tol, maxit, colmark, plan, Warm{}, sm.full);
 }
 
 template <int KIND, int NPT>
@@ -949,7 +998,14 @@ void launch_reg(hipStream_t st, double param, const float* V, int64_t ldv,
   const bool cand = kCand && wm.K == 0 && s.status != nullptr && s.thr != nullptr &&
                     s.redo != nullptr;
   if (!cand) s.redo = nullptr;
-  if constexpr (kCand) {
+  if constexpr (kCand && NPT <= kBothMax) {
+    if (cand) {
+      hipLaunchKernelGGL((x_update_both_kernel<KIND, NPT>), dim3((unsigned)r), dim3(kRT), 0, st, V,
+                         ldv, (int)p, param, X, ldx, li, lv, ldl, list_cap, s, tol, maxit, colmark,
+                         plan);
+      return;
+    }
+  } else if constexpr (kCand) {
     if (cand)
       hipLaunchKernelGGL((x_update_cand_kernel<KIND, NPT>), dim3((unsigned)r), dim3(kRT),
                          0, st, V, ldv, (int)p, param, X, ldx, li, lv, ldl, list_cap, s,
