@@ -344,8 +344,9 @@ const char* spca_last_error(void);
 /* ---------------------------------------------------------------------- */
 /* Building blocks of one AM iteration, exported for testing and tuning.   */
 
-/* C = P * Q^T in FP32 with FP32 accumulation (the two products of an AM
- * iteration, Section 4: U^T = X^T A^T and V^T = Y^T A).  From K = 192 on the
+/* C = P * Q^T in FP32 with FP32 accumulation (the shape of the two products
+ * of an AM iteration, Section 4: U^T = X^T A^T and V^T = Y^T A; solves form
+ * theirs on the FP32 matrix instructions throughout).  From K = 192 on the
  * product runs, where that is faster, on BF16 matrix instructions over three
  * BF16 parts of each operand, whose sum is the FP32 value: errors no larger
  * than those of the FP32 instructions, infinities, NaN and tiny operands as
@@ -392,10 +393,8 @@ int spca_gemm_nt_f32_shape(void* stream, const float* P, int64_t ldp,
  * line, and then nothing is imported); clear removes every entry.  Plans
  * (spca_gemm_nt_f32_plan and the solves) use an entry of their bucket
  * before the cost model.  Shapes 64 to 71 (elem_bytes 4) are the tiles on
- * BF16 parts: they hold for spca_gemm_nt_f32 and for the iterations of a
- * solve that may use such tiles (from the 33rd on, without total_starts >
- * r); a solve's earlier iterations stay on FP32 tiles, whose entries hold
- * for them.  Host-only: no device is touched.                             */
+ * BF16 parts, which hold for spca_gemm_nt_f32 alone: solves stay on FP32
+ * tiles.  Host-only: no device is touched.                                */
 int spca_tune_table_export(char* buf, size_t cap, size_t* len);
 int spca_tune_table_import(const char* text);
 int spca_tune_table_clear(void);

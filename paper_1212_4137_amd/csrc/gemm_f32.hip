@@ -564,18 +564,13 @@ GemmPlan plan_f32(int64_t M, int64_t N, int64_t K, int max_splits, double* us_ou
   return g;
 }
 
-GemmPlan plan_product_f32(int64_t M, int64_t N, int64_t K, int max_splits, int64_t ldp,
-                          int64_t ldq, bool signs, int fixed_splits, double* us_out) {
+GemmPlan plan_product_f32(int64_t M, int64_t N, int64_t K, int64_t ldp, int64_t ldq) {
   const bool split = split_possible(K, ldp, ldq);
   GemmPlan t;
-  if (us_out != nullptr) *us_out = 0.0;
-  if (tuned_plan(M, N, K, max_splits, 4, &t)) {
-    const bool parts = t.shape >= kSplitShape0;
+  if (tuned_plan(M, N, K, 1, 4, &t)) {
     // an entry covers a size bucket, in which K may be too small for it
-    if (parts && !split) return model_plan_gemm_nt(M, N, K, max_splits, 4);
-    t = plan_gemm_nt(M, N, K, max_splits, 4);
-    if (fixed_splits > 0) t.splits = fixed_splits;
-    return t;
+    if (t.shape >= kSplitShape0 && !split) return model_plan_gemm_nt(M, N, K, 1, 4);
+    return plan_gemm_nt(M, N, K, 1, 4);
   }
   // Both models in microseconds.  The FP32 tiles stay ahead only where K is
   // short and the large tiles are mostly padding: 300 x 45359 x 240 takes 83
@@ -584,14 +579,10 @@ GemmPlan plan_product_f32(int64_t M, int64_t N, int64_t K, int max_splits, int64
   // us on parts, 30.2 on FP32 tiles); over 100 sizes with 16 to 1024 rows, K
   // from 200 to 50000, they are up to 20 times faster otherwise.
   double us = 0.0, parts_us = 0.0;
-  const GemmPlan f32 = plan_f32(M, N, K, max_splits, &us);
-  if (us_out != nullptr) *us_out = us;
+  const GemmPlan f32 = plan_f32(M, N, K, 1, &us);
   if (!split) return f32;
-  const GemmPlan parts =
-      model_plan_split(M, N, K, max_splits, signs, fixed_splits, &parts_us);
-  if (parts_us + 3.0 >= 0.9 * us) return f32;
-  if (us_out != nullptr) *us_out = parts_us + 3.0;
-  return parts;
+  const int parts = model_plan_split(M, N, K, &parts_us);
+  return parts_us + 3.0 >= 0.9 * us ? f32 : GemmPlan{parts, 1};
 }
 
 GemmPlan model_plan_gemm_nt(int64_t M, int64_t N, int64_t K, int max_splits,
@@ -657,10 +648,10 @@ int gemm_shape_bm(int shape) {
 void gemm_nt_f32(hipStream_t st, const float* P, int64_t ldp, const float* Q,
                  int64_t ldq, float* C, int64_t ldc, int64_t M, int64_t N,
                  int64_t K, const int32_t* gate, int32_t gate_run,
-                 GemmPlan plan, int64_t split_stride, const int32_t* kdev, bool signs) {
+                 GemmPlan plan, int64_t split_stride, const int32_t* kdev) {
   if (M <= 0 || N <= 0) return;
   if (plan.shape >= kSplitShape0) {
-    gemm_nt_split(st, P, ldp, Q, ldq, C, ldc, M, N, K, gate, gate_run, plan, split_stride, signs);
+    gemm_nt_split(st, P, ldp, Q, ldq, C, ldc, M, N, K, plan.shape);
     return;
   }
   if (plan.shape >= kStreamShape0) {

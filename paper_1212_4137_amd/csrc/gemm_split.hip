@@ -10,8 +10,7 @@
 // and 1.6e-7 for the two kernels below, FP32 MFMA 5.7e-7; with 5% of P
 // nonzero 1.3e-7, 1.0e-7 and 1.3e-7).  The BF16 rate is 16 times the FP32 one
 // (2.5 PFLOP/s against 157 TFLOP/s), so six products cost 3/8 of the FP32
-// ones.  When P holds signs (y = sgn(u): 0 and +-1 are BF16 numbers) three
-// products do.
+// ones.
 //
 // Range.  Sums that overflow, hold an infinity or NaN, or lie so low that
 // parts of an operand fall under the BF16 or FP32 range are recomputed with
@@ -65,23 +64,21 @@ __device__ __forceinline__ uint32_t pack_bf16(float a, float b) {
 __device__ __forceinline__ float low_of(uint32_t h) { return __uint_as_float(h << 16); }
 __device__ __forceinline__ float high_of(uint32_t h) { return __uint_as_float(h & 0xffff0000u); }
 
-// The BF16 parts of four consecutive FP32 values (NP = 1: the first only);
-// amax gathers the largest magnitude.
-template <int NP>
+// The BF16 parts of four consecutive FP32 values; amax gathers the largest
+// magnitude.
+constexpr int NP = 3;  // parts of a value
 __device__ __forceinline__ void split4(fx4 x, ux2 (&w)[NP], float& amax) {
   amax = fmaxf(fmaxf(amax, fabsf(x.x)), fabsf(x.y));
   amax = fmaxf(fmaxf(amax, fabsf(x.z)), fabsf(x.w));
   uint32_t a = pack_bf16(x.x, x.y), b = pack_bf16(x.z, x.w);
   w[0] = ux2{a, b};
-  if constexpr (NP == 3) {
-    const float r0 = x.x - low_of(a), r1 = x.y - high_of(a);
-    const float r2 = x.z - low_of(b), r3 = x.w - high_of(b);
-    a = pack_bf16(r0, r1);
-    b = pack_bf16(r2, r3);
-    w[1] = ux2{a, b};
-    w[2] = ux2{pack_bf16(r0 - low_of(a), r1 - high_of(a)),
-               pack_bf16(r2 - low_of(b), r3 - high_of(b))};
-  }
+  const float r0 = x.x - low_of(a), r1 = x.y - high_of(a);
+  const float r2 = x.z - low_of(b), r3 = x.w - high_of(b);
+  a = pack_bf16(r0, r1);
+  b = pack_bf16(r2, r3);
+  w[1] = ux2{a, b};
+  w[2] = ux2{pack_bf16(r0 - low_of(a), r1 - high_of(a)),
+             pack_bf16(r2 - low_of(b), r3 - high_of(b))};
 }
 
 // Four consecutive values of a row from K position k (zero from kend on).
@@ -99,7 +96,7 @@ __device__ __forceinline__ fx4 load_tail(const float* s, int k, int kend) {
 
 // the part products of one block column, smallest terms first: all but h h'
 // into small[i], h h' into acc[i] (the two may be the same)
-template <int FM, int NP>
+template <int FM>
 __device__ __forceinline__ void mfma_parts(const bf8 (&q)[3], const bf8 (&p)[FM][NP],
                                            fx4 (&small)[FM], fx4 (&acc)[FM]) {
   auto mm = [&](int a, int b, fx4 (&c)[FM]) {
@@ -107,18 +104,12 @@ __device__ __forceinline__ void mfma_parts(const bf8 (&q)[3], const bf8 (&p)[FM]
     for (int i = 0; i < FM; ++i)
       c[i] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(q[b], p[i][a], c[i], 0, 0, 0);
   };
-  if constexpr (NP == 1) {
-    mm(0, 2, small);
-    mm(0, 1, small);
-    mm(0, 0, acc);
-  } else {
-    mm(0, 2, small);
-    mm(2, 0, small);
-    mm(1, 1, small);
-    mm(0, 1, small);
-    mm(1, 0, small);
-    mm(0, 0, acc);
-  }
+  mm(0, 2, small);
+  mm(2, 0, small);
+  mm(1, 1, small);
+  mm(0, 1, small);
+  mm(1, 0, small);
+  mm(0, 0, acc);
 }
 
 // Whether a sum may have lost accuracy to the range of the parts.  With
@@ -178,28 +169,21 @@ __device__ __forceinline__ float wave_max(float x) {
   return x;
 }
 
-// Block -> (tile, split) as in gemm_nt_kernel: unsplit, runs of consecutive
-// tiles stay on one XCD (blocks are dealt to the 8 XCDs in turn); split, the
-// split index is fastest.
-__device__ __forceinline__ void tile_of(int b, int splits, int tiles_mn, int* tile, int* split) {
-  if (splits == 1) {
-    const int per_xcd = tiles_mn / 8;
-    if (b < per_xcd * 8) b = (b % 8) * per_xcd + b / 8;
-  }
-  *split = b % splits;
-  *tile = b / splits;
+// Block -> tile as in gemm_nt_kernel: runs of consecutive tiles stay on one XCD
+// (blocks are dealt to the 8 XCDs in turn).
+__device__ __forceinline__ int tile_of(int b, int tiles) {
+  const int per_xcd = tiles / 8;
+  return b < per_xcd * 8 ? (b % 8) * per_xcd + b / 8 : b;
 }
 
 // ---------------------------------------------------------------------------
 // Large tiles
 // ---------------------------------------------------------------------------
 
-template <int BM, int BN, int WM, int WN, int NP>
+template <int BM, int BN, int WM, int WN>
 __global__ __launch_bounds__(WM* WN* kWave, 2) void split_pp_kernel(
     const float* __restrict__ P, int64_t ldp, const float* __restrict__ Q, int64_t ldq,
-    float* __restrict__ C, int64_t ldc, int M, int N, int K, int tiles_m, int tiles_mn,
-    int splits, int kslabs_per_split, int64_t split_stride, const int32_t* __restrict__ gate,
-    int32_t gate_run) {
+    float* __restrict__ C, int64_t ldc, int M, int N, int K, int tiles_m, int tiles_mn) {
   constexpr int NT = WM * WN * kWave;
   constexpr int TM = BM / WM, TN = BN / WN, FM = TM / 16, FN = TN / 16;
   constexpr int RPV = NT / 8;  // rows per load round (8 lanes of 16 bytes a row)
@@ -208,14 +192,10 @@ __global__ __launch_bounds__(WM* WN* kWave, 2) void split_pp_kernel(
   constexpr int kStage = kPBytes + BN / 16 * 3 * 1024;
   static_assert(BM % RPV == 0 && TM % 16 == 0 && TN % 16 == 0, "tile split");
   __shared__ __attribute__((aligned(16))) char lds[2 * kStage];
-  if (gate != nullptr && *gate != gate_run) return;
 
-  int tile, split;
-  tile_of(blockIdx.x, splits, tiles_mn, &tile, &split);
+  const int tile = tile_of(blockIdx.x, tiles_mn);
   const int m0 = (tile % tiles_m) * BM, n0 = (tile / tiles_m) * BN;
-  const int kbeg = split * kslabs_per_split * kSlab;
-  int kend = kbeg + kslabs_per_split * kSlab;
-  kend = kend < K ? kend : K;
+  const int kbeg = 0, kend = K;
   // slabs: a partial one (K not a multiple of 32) goes first, where the
   // loop's loads need no guard for it
   const int nfull = kend > kbeg ? (kend - kbeg) / kSlab : 0;
@@ -278,9 +258,9 @@ __global__ __launch_bounds__(WM* WN* kWave, 2) void split_pp_kernel(
   ux2 kp[VP][NP], kq[VQ][3];
   auto convert = [&](const Regs& r, int v) {
     if (v < VP)
-      split4<NP>(r.p[v], kp[v], amax_p);
+      split4(r.p[v], kp[v], amax_p);
     else
-      split4<3>(r.q[v - VP], kq[v - VP], amax_q);
+      split4(r.q[v - VP], kq[v - VP], amax_q);
   };
   const int wc = c4 / 2;
   const int woff = (wc * 16 + ((frow & 15) ^ (2 * wc))) * 16 + (c4 & 1) * 8;
@@ -367,7 +347,7 @@ __global__ __launch_bounds__(WM* WN* kWave, 2) void split_pp_kernel(
         fx4 small[FM];
 #pragma unroll
         for (int i = 0; i < FM; ++i) small[i] = fx4{0.f, 0.f, 0.f, 0.f};
-        mfma_parts<FM, NP>(qf[j], pf, small, acc[j]);
+        mfma_parts<FM>(qf[j], pf, small, acc[j]);
 #pragma unroll
         for (int i = 0; i < FM; ++i) acc[j][i] += small[i];
 #pragma unroll
@@ -381,9 +361,9 @@ __global__ __launch_bounds__(WM* WN* kWave, 2) void split_pp_kernel(
         }
         // two vector instructions in the shadow of every MFMA
 #pragma unroll
-        for (int g = 0; g < FM * (NP == 1 ? 3 : 6); ++g) {
+        for (int g = 0; g < FM * 6; ++g) {
           __builtin_amdgcn_sched_group_barrier(0x8, 1, 0);
-          __builtin_amdgcn_sched_group_barrier(0x2, NP == 1 ? 3 : 2, 0);
+          __builtin_amdgcn_sched_group_barrier(0x2, 2, 0);
         }
       }
       turn();
@@ -405,7 +385,7 @@ __global__ __launch_bounds__(WM* WN* kWave, 2) void split_pp_kernel(
     amax_q = fmaxf(amax_q, red[2 * w + 1]);
   }
 
-  float* Cs = C + (int64_t)split * split_stride;
+  float* Cs = C;
   const bool vec = ldc % 4 == 0 && ((uintptr_t)Cs & 15) == 0;
   const int lr = lane % 16, lc = lane / 16;
   // Rows of C that are not 16-byte aligned go through LDS, 16 rows of the
@@ -473,7 +453,7 @@ constexpr size_t ks_lds_bytes(int waves) {
   return slabs > parts ? slabs : parts;
 }
 
-template <int FM, int FN, int NP>
+template <int FM, int FN>
 __device__ __forceinline__ void ks_tile(const float* __restrict__ P, int64_t ldp,
                                         const float* __restrict__ Q, int64_t ldq,
                                         float* __restrict__ Cs, int64_t ldc, int M, int N, int m0,
@@ -491,13 +471,12 @@ __device__ __forceinline__ void ks_tile(const float* __restrict__ P, int64_t ldp
 
   float amax_p = 0.f, amax_q = 0.f;
   // a fragment: lane (row lr, lc) holds k = 4 lc .. +3 and 16 + 4 lc .. +3
-  auto split_frag = [&](const fx4 (&x)[2], auto& out, float& amax) {
-    constexpr int PARTS = sizeof(out) / sizeof(bf8);
-    ux2 a[PARTS], b[PARTS];
-    split4<PARTS>(x[0], a, amax);
-    split4<PARTS>(x[1], b, amax);
+  auto split_frag = [&](const fx4 (&x)[2], bf8 (&out)[NP], float& amax) {
+    ux2 a[NP], b[NP];
+    split4(x[0], a, amax);
+    split4(x[1], b, amax);
 #pragma unroll
-    for (int q = 0; q < PARTS; ++q)
+    for (int q = 0; q < NP; ++q)
       out[q] = __builtin_bit_cast(bf8, ux4{a[q].x, a[q].y, b[q].x, b[q].y});
   };
   fx4 acc[FN][FM];
@@ -559,11 +538,11 @@ __device__ __forceinline__ void ks_tile(const float* __restrict__ P, int64_t ldp
       split_frag(rq[0], q[0], amax_q);
 #pragma unroll
       for (int j = 0; j < FN; ++j) {
-        mfma_parts<FM, NP>(q[j & 1], pf, acc[j], acc[j]);
+        mfma_parts<FM>(q[j & 1], pf, acc[j], acc[j]);
         if (j + 1 < FN) split_frag(rq[j + 1], q[(j + 1) & 1], amax_q);
         if constexpr (FM * FN >= 16) {
 #pragma unroll
-          for (int g = 0; g < FM * (NP == 1 ? 3 : 6); ++g) {
+          for (int g = 0; g < FM * 6; ++g) {
             __builtin_amdgcn_sched_group_barrier(0x8, 1, 0);
             __builtin_amdgcn_sched_group_barrier(0x2, 3, 0);
           }
@@ -592,7 +571,7 @@ __device__ __forceinline__ void ks_tile(const float* __restrict__ P, int64_t ldp
       bf8 q[3];
       load_frag(rq[j], Qb, (uint32_t)ldq, row);
       split_frag(rq[j], q, amax_q);
-      mfma_parts<FM, NP>(q, pf, acc[j], acc[j]);
+      mfma_parts<FM>(q, pf, acc[j], acc[j]);
     }
   }
   amax_p = wave_max(amax_p);
@@ -655,23 +634,15 @@ __device__ __forceinline__ void ks_tile(const float* __restrict__ P, int64_t ldp
 
 constexpr int kKsWaves = 8;
 
-template <int FM, int FN, int NP, int OCC>
+template <int FM, int FN, int OCC>
 __global__ __launch_bounds__(kKsWaves* kWave, OCC) void split_ks_kernel(
     const float* __restrict__ P, int64_t ldp, const float* __restrict__ Q, int64_t ldq,
-    float* __restrict__ C, int64_t ldc, int M, int N, int K, int tiles_m, int tiles_mn,
-    int splits, int kslabs_per_split, int64_t split_stride, const int32_t* __restrict__ gate,
-    int32_t gate_run) {
+    float* __restrict__ C, int64_t ldc, int M, int N, int K, int tiles_m, int tiles_mn) {
   extern __shared__ __attribute__((aligned(16))) char lds[];
   __shared__ float red[2 * kKsWaves];
-  if (gate != nullptr && *gate != gate_run) return;
-  int tile, split;
-  tile_of(blockIdx.x, splits, tiles_mn, &tile, &split);
-  const int kbeg = split * kslabs_per_split * kSlab;
-  int kend = kbeg + kslabs_per_split * kSlab;
-  kend = kend < K ? kend : K;
-  ks_tile<FM, FN, NP>(P, ldp, Q, ldq, C + (int64_t)split * split_stride, ldc, M, N,
-                      (tile % tiles_m) * FM * 16, (tile / tiles_m) * FN * 16, kbeg, kend, lds,
-                      red);
+  const int tile = tile_of(blockIdx.x, tiles_mn);
+  ks_tile<FM, FN>(P, ldp, Q, ldq, C, ldc, M, N, (tile % tiles_m) * FM * 16,
+                  (tile / tiles_m) * FN * 16, 0, K, lds, red);
 }
 
 // Compiled tiles.  Times of one workgroup step in microseconds, as measured
@@ -681,77 +652,41 @@ __global__ __launch_bounds__(kKsWaves* kWave, OCC) void split_ks_kernel(
 // loads, the sums over the waves and the store.
 struct SplitShape {
   int bm, bn, waves;  // waves > 0: K shared by that many waves
-  double step, step_full, step_sgn, step_sgn_full, fixed;
+  double step, step_full, fixed;
 };
 constexpr SplitShape kSplitShapes[] = {
-    {256, 160, 0, 2.13, 2.87, 1.25, 1.65, 12.0},
-    {256, 128, 0, 1.75, 2.35, 1.00, 1.35, 12.0},
-    {64, 80, 8, 3.30, 4.10, 2.20, 2.85, 4.0},
-    {64, 64, 8, 2.70, 3.40, 1.75, 2.25, 3.5},
-    {64, 32, 8, 1.85, 2.30, 1.20, 1.50, 2.5},
-    {32, 32, 8, 1.20, 1.50, 0.85, 1.05, 2.2},
-    {64, 16, 8, 1.43, 1.80, 0.90, 1.15, 2.2},
-    {16, 16, 8, 0.60, 0.75, 0.45, 0.55, 2.0},
+    {256, 160, 0, 2.13, 2.87, 12.0},
+    {256, 128, 0, 1.75, 2.35, 12.0},
+    {64, 80, 8, 3.30, 4.10, 4.0},
+    {64, 64, 8, 2.70, 3.40, 3.5},
+    {64, 32, 8, 1.85, 2.30, 2.5},
+    {32, 32, 8, 1.20, 1.50, 2.2},
+    {64, 16, 8, 1.43, 1.80, 2.2},
+    {16, 16, 8, 0.60, 0.75, 2.0},
 };
 constexpr int kNumSplit = (int)(sizeof(kSplitShapes) / sizeof(kSplitShapes[0]));
 
-template <int BM, int BN, int WM, int WN, int NP>
+template <int BM, int BN, int WM, int WN>
 void launch_pp(hipStream_t st, const float* P, int64_t ldp, const float* Q, int64_t ldq, float* C,
-               int64_t ldc, int64_t M, int64_t N, int64_t K, int splits, int64_t split_stride,
-               const int32_t* gate, int32_t gate_run) {
+               int64_t ldc, int64_t M, int64_t N, int64_t K) {
   const int tm = (int)ceil_div(M, BM), tn = (int)ceil_div(N, BN);
-  const int per = (int)ceil_div(ceil_div(K, (int64_t)kSlab), (int64_t)splits);
-  hipLaunchKernelGGL((split_pp_kernel<BM, BN, WM, WN, NP>), dim3((unsigned)(tm * tn * splits)),
+  hipLaunchKernelGGL((split_pp_kernel<BM, BN, WM, WN>), dim3((unsigned)(tm * tn)),
                      dim3(WM * WN * kWave), 0, st, P, ldp, Q, ldq, C, ldc, (int)M, (int)N, (int)K,
-                     tm, tm * tn, splits, per, split_stride, gate, gate_run);
+                     tm, tm * tn);
 }
 
-template <int FM, int FN, int NP, int OCC>
+template <int FM, int FN, int OCC>
 void launch_ks(hipStream_t st, const float* P, int64_t ldp, const float* Q, int64_t ldq, float* C,
-               int64_t ldc, int64_t M, int64_t N, int64_t K, int waves, int splits,
-               int64_t split_stride, const int32_t* gate, int32_t gate_run) {
+               int64_t ldc, int64_t M, int64_t N, int64_t K) {
   const int tm = (int)ceil_div(M, 16 * FM), tn = (int)ceil_div(N, 16 * FN);
-  const int per = (int)ceil_div(ceil_div(K, (int64_t)kSlab), (int64_t)splits);
+  const int slabs = (int)ceil_div(K, (int64_t)kSlab);
   // few slabs and workgroups for every CU anyway: fewer waves, two slabs
   // each, and more workgroups at once (24 x 26299 x 219: 13.0 to 10.9 us)
-  if (per < 2 * waves && (int64_t)tm * tn * splits >= 512) waves = per < 4 ? 2 : (per + 1) / 2;
-  hipLaunchKernelGGL((split_ks_kernel<FM, FN, NP, OCC>), dim3((unsigned)(tm * tn * splits)),
+  int waves = kKsWaves;
+  if (slabs < 2 * waves && (int64_t)tm * tn >= 512) waves = slabs < 4 ? 2 : (slabs + 1) / 2;
+  hipLaunchKernelGGL((split_ks_kernel<FM, FN, OCC>), dim3((unsigned)(tm * tn)),
                      dim3(waves * kWave), (ks_lds_bytes<FM, FN>(waves)), st, P, ldp, Q, ldq, C,
-                     ldc, (int)M, (int)N, (int)K, tm, tm * tn, splits, per, split_stride, gate,
-                     gate_run);
-}
-
-template <int NP>
-void dispatch_split(int v, hipStream_t st, const float* P, int64_t ldp, const float* Q,
-                    int64_t ldq, float* C, int64_t ldc, int64_t M, int64_t N, int64_t K,
-                    int splits, int64_t stride, const int32_t* gate, int32_t gate_run) {
-  const int w = kSplitShapes[v].waves;
-  switch (v) {
-    case 0:
-      launch_pp<256, 160, 4, 2, NP>(st, P, ldp, Q, ldq, C, ldc, M, N, K, splits, stride, gate, gate_run);
-      break;
-    case 1:
-      launch_pp<256, 128, 4, 2, NP>(st, P, ldp, Q, ldq, C, ldc, M, N, K, splits, stride, gate, gate_run);
-      break;
-    case 2:
-      launch_ks<4, 5, NP, 2>(st, P, ldp, Q, ldq, C, ldc, M, N, K, w, splits, stride, gate, gate_run);
-      break;
-    case 3:
-      launch_ks<4, 4, NP, 2>(st, P, ldp, Q, ldq, C, ldc, M, N, K, w, splits, stride, gate, gate_run);
-      break;
-    case 4:
-      launch_ks<4, 2, NP, 2>(st, P, ldp, Q, ldq, C, ldc, M, N, K, w, splits, stride, gate, gate_run);
-      break;
-    case 5:
-      launch_ks<2, 2, NP, 4>(st, P, ldp, Q, ldq, C, ldc, M, N, K, w, splits, stride, gate, gate_run);
-      break;
-    case 6:
-      launch_ks<4, 1, NP, 2>(st, P, ldp, Q, ldq, C, ldc, M, N, K, w, splits, stride, gate, gate_run);
-      break;
-    default:
-      launch_ks<1, 1, NP, 4>(st, P, ldp, Q, ldq, C, ldc, M, N, K, w, splits, stride, gate, gate_run);
-      break;
-  }
+                     ldc, (int)M, (int)N, (int)K, tm, tm * tn);
 }
 
 }  // namespace
@@ -771,33 +706,23 @@ bool split_possible(int64_t K, int64_t ldp, int64_t ldq) {
   return K >= kSplitMinK && ldp <= (1 << 21) && ldq <= (1 << 21);
 }
 
-GemmPlan model_plan_split(int64_t M, int64_t N, int64_t K, int max_splits, bool signs,
-                          int fixed_splits, double* us_out) {
-  GemmPlan best{kSplitShape0, 1};
+int model_plan_split(int64_t M, int64_t N, int64_t K, double* us_out) {
+  int best = kSplitShape0;
   double best_us = 1e300;
-  const int64_t kslabs = ceil_div(K, (int64_t)kSlab);
+  const int64_t slabs = ceil_div(K, (int64_t)kSlab);
   for (int v = 0; v < kNumSplit; ++v) {
     const SplitShape& sh = kSplitShapes[v];
     if (sh.bm > 16 && M <= sh.bm / 2) continue;  // mostly padding rows
-    const double lo = signs ? sh.step_sgn : sh.step;
-    const double hi = signs ? sh.step_sgn_full : sh.step_full;
-    const int64_t tiles = ceil_div(M, (int64_t)sh.bm) * ceil_div(N, (int64_t)sh.bn);
-    for (int splits = fixed_splits > 0 ? fixed_splits : 1; splits <= max_splits; splits *= 2) {
-      const int64_t per = ceil_div(kslabs, (int64_t)splits);
-      if (fixed_splits > 0 ? splits != fixed_splits : splits > 1 && per < 8)
-        break;  // too little K per split
-      const int64_t wgs = tiles * splits;
-      const double steps = (double)(sh.waves > 0 ? ceil_div(per, (int64_t)sh.waves) : per);
-      // rounds of 256 workgroups, the last one partly filled (and faster)
-      const int64_t full = wgs / 256, rest = wgs % 256;
-      double us = (double)full * (steps * hi + sh.fixed);
-      if (rest > 0) us += steps * (lo + (hi - lo) * (double)rest / 256.0) + sh.fixed;
-      // the partial sums' traffic (written, then read by the next kernel)
-      if (splits > 1) us += 1.0 + (double)splits * (double)M * (double)N * 8.0 / 4.0e6;
-      if (us < best_us * 0.999) {
-        best_us = us;
-        best = GemmPlan{kSplitShape0 + v, splits};
-      }
+    const int64_t wgs = ceil_div(M, (int64_t)sh.bm) * ceil_div(N, (int64_t)sh.bn);
+    const double steps = (double)(sh.waves > 0 ? ceil_div(slabs, (int64_t)sh.waves) : slabs);
+    // rounds of 256 workgroups, the last one partly filled (and faster)
+    const int64_t full = wgs / 256, rest = wgs % 256;
+    double us = (double)full * (steps * sh.step_full + sh.fixed);
+    if (rest > 0)
+      us += steps * (sh.step + (sh.step_full - sh.step) * (double)rest / 256.0) + sh.fixed;
+    if (us < best_us * 0.999) {
+      best_us = us;
+      best = kSplitShape0 + v;
     }
   }
   *us_out = best_us;
@@ -805,16 +730,18 @@ GemmPlan model_plan_split(int64_t M, int64_t N, int64_t K, int max_splits, bool 
 }
 
 void gemm_nt_split(hipStream_t st, const float* P, int64_t ldp, const float* Q, int64_t ldq,
-                   float* C, int64_t ldc, int64_t M, int64_t N, int64_t K, const int32_t* gate,
-                   int32_t gate_run, GemmPlan plan, int64_t split_stride, bool signs) {
+                   float* C, int64_t ldc, int64_t M, int64_t N, int64_t K, int shape) {
   if (M <= 0 || N <= 0) return;
-  const int v = plan.shape - kSplitShape0;
-  if (signs)
-    dispatch_split<1>(v, st, P, ldp, Q, ldq, C, ldc, M, N, K, plan.splits, split_stride, gate,
-                      gate_run);
-  else
-    dispatch_split<3>(v, st, P, ldp, Q, ldq, C, ldc, M, N, K, plan.splits, split_stride, gate,
-                      gate_run);
+  switch (shape - kSplitShape0) {
+    case 0: launch_pp<256, 160, 4, 2>(st, P, ldp, Q, ldq, C, ldc, M, N, K); break;
+    case 1: launch_pp<256, 128, 4, 2>(st, P, ldp, Q, ldq, C, ldc, M, N, K); break;
+    case 2: launch_ks<4, 5, 2>(st, P, ldp, Q, ldq, C, ldc, M, N, K); break;
+    case 3: launch_ks<4, 4, 2>(st, P, ldp, Q, ldq, C, ldc, M, N, K); break;
+    case 4: launch_ks<4, 2, 2>(st, P, ldp, Q, ldq, C, ldc, M, N, K); break;
+    case 5: launch_ks<2, 2, 4>(st, P, ldp, Q, ldq, C, ldc, M, N, K); break;
+    case 6: launch_ks<4, 1, 2>(st, P, ldp, Q, ldq, C, ldc, M, N, K); break;
+    default: launch_ks<1, 1, 4>(st, P, ldp, Q, ldq, C, ldc, M, N, K); break;
+  }
 }
 
 }  // namespace spca

@@ -145,30 +145,26 @@ GemmPlan model_plan_gemm_nt(int64_t M, int64_t N, int64_t K, int max_splits,
 // where those are faster: same K split, same bits.  us_out: modelled time
 // (0 for a tuning-table entry).
 GemmPlan plan_f32(int64_t M, int64_t N, int64_t K, int max_splits, double* us_out = nullptr);
-// the faster of plan_f32 and the BF16-part tiles (gemm_split.hip); a
-// tuning-table entry decides if there is one.  signs: P holds 0 and +-1
-// only.  fixed_splits > 0: the K split to use with either.  us_out: as above.
-GemmPlan plan_product_f32(int64_t M, int64_t N, int64_t K, int max_splits, int64_t ldp,
-                          int64_t ldq, bool signs, int fixed_splits = 0,
-                          double* us_out = nullptr);
+// one product: the faster of plan_f32 and the BF16-part tiles (gemm_split.hip),
+// unsplit; a tuning-table entry decides if there is one
+GemmPlan plan_product_f32(int64_t M, int64_t N, int64_t K, int64_t ldp, int64_t ldq);
 int gemm_num_shapes();
-// FP32 products on BF16 parts (gemm_split.hip): number of tiles, whether a
-// product can use them, the model's choice among them, and the launch
 // one-wave FP32 tiles (gemm_stream.hip): the bits of gemm_nt_kernel's tiles
 int gemm_num_stream_shapes();
 int model_stream(int64_t M, int64_t N, int64_t K, int splits, double* us_out);
 void gemm_nt_stream(hipStream_t st, const float* P, int64_t ldp, const float* Q, int64_t ldq,
                     float* C, int64_t ldc, int64_t M, int64_t N, int64_t K, const int32_t* gate,
                     int32_t gate_run, GemmPlan plan, int64_t split_stride);
+// FP32 products on BF16 parts (gemm_split.hip), for products outside a solve:
+// number of tiles, whether a product can use them, the model's choice among
+// them (a shape) with its time, and the launch
 int gemm_num_split_shapes();
 int split_shape_bm(int shape);
 constexpr int64_t kSplitMinK = 192;
 bool split_possible(int64_t K, int64_t ldp, int64_t ldq);
-GemmPlan model_plan_split(int64_t M, int64_t N, int64_t K, int max_splits, bool signs,
-                          int fixed_splits, double* us_out);
+int model_plan_split(int64_t M, int64_t N, int64_t K, double* us_out);
 void gemm_nt_split(hipStream_t st, const float* P, int64_t ldp, const float* Q, int64_t ldq,
-                   float* C, int64_t ldc, int64_t M, int64_t N, int64_t K, const int32_t* gate,
-                   int32_t gate_run, GemmPlan plan, int64_t split_stride, bool signs);
+                   float* C, int64_t ldc, int64_t M, int64_t N, int64_t K, int shape);
 // rows of the output tile of a shape (0 for an unknown shape)
 int gemm_shape_bm(int shape);
 // largest power-of-two split count (<= max_splits) that leaves every split
@@ -187,13 +183,13 @@ void tune_table_clear();
 // plan.splits > 1, K split s writes its partial product at
 // C + s * split_stride.  When gate != nullptr the kernel runs only if
 // *gate == gate_run.  When kdev != nullptr, K is read from *kdev on the
-// device (plan.splits must then be 1, its shape below kSplitShape0).  signs:
-// P holds 0 and +-1 only (used by the BF16-part tiles).
+// device (plan.splits must then be 1, its shape below kSplitShape0).  Shapes
+// from kSplitShape0 on take neither a gate nor splits.
 void gemm_nt_f32(hipStream_t st, const float* P, int64_t ldp, const float* Q,
                  int64_t ldq, float* C, int64_t ldc, int64_t M, int64_t N,
                  int64_t K, const int32_t* gate, int32_t gate_run,
                  GemmPlan plan, int64_t split_stride,
-                 const int32_t* kdev = nullptr, bool signs = false);
+                 const int32_t* kdev = nullptr);
 
 // The same product with BF16 operands (bit patterns, ld multiple of 8 and
 // 16-byte aligned rows), FP32 accumulation and output.

@@ -64,16 +64,13 @@ inline int list_cap_of(int64_t p) {
 
 constexpr int kMaxSplits = 16;  // K splits of the dense A x product
 static_assert(kMaxSplits <= kSplitsMax, "the y-update sums at most kSplitsMax partials");
-// A solve's first iterations decide which stationary point a start ends at:
-// near-ties of the selection (and signs of u near zero) fall as the sums
-// round.  They stay on the FP32 MFMA sums, bit for bit, for this many
-// iterations; the products on BF16 parts, of another rounding (smaller
-// errors), take over once the supports have settled.  1000 x 10000, F1 and
-// F2, 1024 starts, 18 solves continued on the parts: from iteration 0 on 8
-// starts ended elsewhere, from 4 on 2, from 8 on 1, from 16 on none; 36 more
-// solves of 64 to 400 starts: from 16 on 2, from 24 on 1, from 32 on none.
-// The 32 iterations cost 2.4 ms of the 36 ms that 200 take at that size.
-constexpr int kSettleIters = 32;
+// The products of a solve stay on the FP32 MFMA sums, bit for bit: near ties of
+// a selection (and signs of u near zero) fall as the sums round, and a start
+// then ends at another stationary point.  BF16 parts (gemm_split.hip), of smaller
+// errors but another rounding, took 36 instead of 48 ms for 200 iterations of
+// 1000 x 10000 with 1024 starts, but one start of 1024 ended elsewhere in 1 of
+// 40 such solves with parts from iteration 32 on, in 3 of 300 from 64 on and in
+// 2 of 300 from 96 on.
 constexpr int kTimeSample = 8;  // SPCA_FLAG_TIME_SAMPLED: events every 8th iteration
 
 struct Layout {
@@ -614,30 +611,16 @@ int spca_am_solve_ex(spca_ctx* ctx, void* stream, const spca_problem* prob,
   } else {
     max_norm_column_start(st, A, ldA, n, p, colsq, X, L.ldx);
   }
-  // The products' tiles: FP32 MFMA sums for the first iterations, from
-  // parts_from on those of plan_product_f32 (same A X split count, which the
-  // planner and the y-update know).  Y holds signs (0 and +-1) under L1
-  // variance.
-  const bool signs = l1_variance(fid);
-  GemmPlan late_ax{}, late_aty{};
-  int32_t parts_from = INT32_MAX;
+  // The products' tiles (the layout's are those of the workgroup tiles; one-wave
+  // tiles have the same splits and bits).
   auto plan_products = [&]() {
     if (bf16) {
-      L.plan_ax = late_ax = plan_gemm_nt(r, n, p, kMaxSplits, 2);
-      L.plan_aty = late_aty = plan_gemm_nt(r, p, n, kMaxSplits, 2);
+      L.plan_ax = plan_gemm_nt(r, n, p, kMaxSplits, 2);
+      L.plan_aty = plan_gemm_nt(r, p, n, kMaxSplits, 2);
       return;
     }
-    double us = 0.0, late_us = 0.0;
     L.plan_ax = plan_f32(r, n, p, kMaxSplits);
-    L.plan_aty = plan_f32(r, p, n, kMaxSplits, &us);
-    late_ax = plan_product_f32(r, n, p, kMaxSplits, L.ldx, L.ldat, false, L.plan_ax.splits);
-    late_aty = plan_product_f32(r, p, n, kMaxSplits, L.ldu, ldA, signs, 0, &late_us);
-    // a second graph costs about 0.2 ms to capture: not for a few iterations
-    // or a small product (the eager loop follows the same rule)
-    const int64_t from = (int64_t)kSettleIters + (warm ? opts->warmup_iters : 0);
-    const bool worth = late_aty.shape >= kSplitShape0 &&
-                       (late_us == 0.0 || (us - late_us) * (double)(opts->maxit - from) > 300.0);
-    parts_from = !otf && worth ? (int32_t)from : INT32_MAX;
+    L.plan_aty = plan_f32(r, p, n, kMaxSplits);
   };
   plan_products();
   if (opts->flags & SPCA_FLAG_AUTOTUNE) {
@@ -716,16 +699,15 @@ int spca_am_solve_ex(spca_ctx* ctx, void* stream, const spca_problem* prob,
   // Every launch reads its control data (mode, active starts, sizes) from
   // the device-side plan, so the same sequence serves every iteration and
   // can be captured once into a graph.
-  auto iteration = [&](hipStream_t q, bool tm, bool late) -> int {
-    const GemmPlan g_ax = late ? late_ax : L.plan_ax, g_aty = late ? late_aty : L.plan_aty;
+  auto iteration = [&](hipStream_t q, bool tm) -> int {
     // u = A x and the y-update
     if (tm) SPCA_HIP_TRY(ctx->t_ax.mark(q));
     if (bf16)
       gemm_nt_bf16(q, Xb, L.ldxb, Atb, L.ldatb, U, L.ldu, r, n, p, &plan->mode,
-                   kAxDense, g_ax, r * L.ldu);
+                   kAxDense, L.plan_ax, r * L.ldu);
     else
       gemm_nt_f32(q, X, L.ldx, At, L.ldat, U, L.ldu, r, n, p, &plan->mode,
-                  kAxDense, g_ax, r * L.ldu);
+                  kAxDense, L.plan_ax, r * L.ldu);
     if (tm) SPCA_HIP_TRY(ctx->t_ax.mark(q));
     if (!bf16 && union_on) {  // the planner can pick the union product
       union_gather(q, X, L.ldx, r, A, ldA, n, ulist, plan, Xc, ldc_u, Qc, ldc_u);
@@ -751,11 +733,11 @@ int spca_am_solve_ex(spca_ctx* ctx, void* stream, const spca_problem* prob,
     if (tm) SPCA_HIP_TRY(ctx->t_aty.mark(q));
     if (bf16)
       gemm_nt_bf16(q, Yb, L.ldyb, Ab, L.ldab, V, L.ldx, r, p, n, nullptr, 0,
-                   g_aty, r * L.ldx);
+                   L.plan_aty, r * L.ldx);
     else
       gemm_nt_f32(q, Y, L.ldu, A, ldA, V, L.ldx, r, p, n, nullptr, 0,
-                  g_aty, r * L.ldx, nullptr, signs);
-    sum_splits(q, V, r * L.ldx, g_aty.splits, r * L.ldx);
+                  L.plan_aty, r * L.ldx);
+    sum_splits(q, V, r * L.ldx, L.plan_aty.splits, r * L.ldx);
     if (tm) SPCA_HIP_TRY(ctx->t_aty.mark(q));
     if (dk > 0) deflate_v(q, V, L.ldx, p, r, s, defl);
     if (tm) SPCA_HIP_TRY(ctx->t_xup.mark(q));
@@ -803,15 +785,14 @@ int spca_am_solve_ex(spca_ctx* ctx, void* stream, const spca_problem* prob,
     // launches only.
     rc = ensure_capture_stream(ctx);
     if (rc != SPCA_OK) return rc;
-    // one graph per union_on state and product plan, captured when first
-    // needed; a block of iterations across parts_from runs eagerly
-    hipGraphExec_t execs[4] = {nullptr, nullptr, nullptr, nullptr};
-    auto capture = [&](hipGraphExec_t* exec, bool late) -> int {
+    // one graph per union_on state, captured when first needed
+    hipGraphExec_t execs[2] = {nullptr, nullptr};
+    auto capture = [&](hipGraphExec_t* exec) -> int {
       hipGraph_t graph = nullptr;
       SPCA_HIP_TRY(hipStreamBeginCapture(ctx->capture, hipStreamCaptureModeThreadLocal));
       int body_rc = SPCA_OK;
       for (int32_t k = 0; k < every && body_rc == SPCA_OK; ++k)
-        body_rc = iteration(ctx->capture, false, late);
+        body_rc = iteration(ctx->capture, false);
       hipError_t end_rc = hipStreamEndCapture(ctx->capture, &graph);
       if (body_rc != SPCA_OK) {
         if (graph) (void)hipGraphDestroy(graph);
@@ -825,23 +806,16 @@ int spca_am_solve_ex(spca_ctx* ctx, void* stream, const spca_problem* prob,
     };
     int loop_rc = SPCA_OK;
     while (!done && it + every <= loop_max) {
-      const bool late = it >= parts_from;
-      if (!late && parts_from - it < every) {
-        for (int32_t k = 0; k < every && loop_rc == SPCA_OK; ++k)
-          loop_rc = iteration(st, false, it + k >= parts_from);
+      hipGraphExec_t& exec = execs[union_on ? 1 : 0];
+      if (exec == nullptr) {
+        loop_rc = capture(&exec);
         if (loop_rc != SPCA_OK) break;
-      } else {
-        hipGraphExec_t& exec = execs[(union_on ? 1 : 0) + (late ? 2 : 0)];
-        if (exec == nullptr) {
-          loop_rc = capture(&exec, late);
-          if (loop_rc != SPCA_OK) break;
-        }
-        hipError_t e = hipGraphLaunch(exec, st);
-        if (e != hipSuccess) {
-          set_error(std::string("hipGraphLaunch: ") + hipGetErrorString(e));
-          loop_rc = SPCA_EHIP;
-          break;
-        }
+      }
+      hipError_t e = hipGraphLaunch(exec, st);
+      if (e != hipSuccess) {
+        set_error(std::string("hipGraphLaunch: ") + hipGetErrorString(e));
+        loop_rc = SPCA_EHIP;
+        break;
       }
       it += every;
       if (it < loop_max) {
@@ -854,7 +828,7 @@ int spca_am_solve_ex(spca_ctx* ctx, void* stream, const spca_problem* prob,
     if (loop_rc != SPCA_OK) return loop_rc;
   }
   for (; !done && it < loop_max; ++it) {
-    rc = iteration(st, timed && (!sampled || it % kTimeSample == 0), it >= parts_from);
+    rc = iteration(st, timed && (!sampled || it % kTimeSample == 0));
     if (rc != SPCA_OK) return rc;
     if ((it + 1) % every == 0 && it + 1 < loop_max) {
       rc = none_active(&done);
@@ -1519,7 +1493,7 @@ int spca_gemm_nt_f32(void* stream, const float* P, int64_t ldp, const float* Q,
   SPCA_REQUIRE((uintptr_t)P % 16 == 0 && (uintptr_t)Q % 16 == 0,
                "P and Q must be 16-byte aligned");
   gemm_nt_f32((hipStream_t)stream, P, ldp, Q, ldq, C, ldc, M, N, K, nullptr, 0,
-              plan_product_f32(M, N, K, 1, ldp, ldq, false), 0);
+              plan_product_f32(M, N, K, ldp, ldq), 0);
   SPCA_LAUNCH_CHECK("gemm_nt_f32");
   return SPCA_OK;
 }

@@ -1,15 +1,11 @@
 """FP32 products on BF16 parts (gemm_split.hip): every tile against an FP64
-product at the edges of tiles, slabs and K splits, and the values that the
+product at the edges of tiles and slabs, and the values that the
 parts cannot hold (infinities, NaN, overflow, tiny operands) against the FP32
 tiles."""
 import math
 
 import numpy as np
 import pytest
-
-import oracle
-import workloads
-from gpu_helpers import compare_solve, gpu_stepper, to_device_colmajor, to_device_rows
 
 pytestmark = pytest.mark.gpu
 
@@ -112,28 +108,3 @@ def test_split_product_special_values(spca, shape):
     for sp, sq in ((1.0, 1e-36), (1.0, 1e-40), (1e-20, 1e-20), (1e30, 1e-36), (1e18, 1e18),
                    (1e20, 1e20), (0.0, 1.0)):
         case(P0 * sp, Q0 * sq, tol)
-
-
-@pytest.mark.parametrize("shape,splits", [(64, 2), (67, 8), (71, 4)])
-@pytest.mark.parametrize("fid", [1, 2])
-def test_split_tiles_in_a_k_split_solve(spca, shape, splits, fid):
-    """Both products of a dense solve on one BF16-part tile with a K split
-    (fid 2: the A^T Y of signs), against the oracle."""
-    print(f"split solve shape={shape} splits={splits} F{fid}", flush=True)
-    n, p, r = 700, 2100, 40
-    sp = workloads.spiked_matrix(83 + fid, n, p, thetas=(60.0, 30.0), spike_nnz=20)
-    X0n = workloads.random_unit_starts(84 + fid, r, p)
-    A, X0 = to_device_colmajor(sp.A), to_device_rows(X0n)
-    kw = dict(tol=-1.0, flags=spca.FLAG_DENSE_ONLY)
-    spca.tune_table_import(
-        f"4 16 {_bucket(r)} {_bucket(n)} {_bucket(p)} {shape} {splits}\n"
-        f"4 16 {_bucket(r)} {_bucket(p)} {_bucket(n)} {shape} {splits}\n")
-    try:
-        got = spca.am_solve(A, fid, 20.0, X0, maxit=60, return_X=True, **kw)
-        got["X_final"] = got["X_final"].cpu().numpy()
-        ref = oracle.am_multi(sp.A.astype(np.float64), fid, 20.0, X0n.astype(np.float64), -1.0,
-                              60, nthreads=8)
-        compare_solve(got, ref, f"split {shape}/{splits} F{fid}", sp.A, fid, 20.0, X0=X0n,
-                      stepper=gpu_stepper(spca.am_solve, A, fid, 20.0, X0, **kw))
-    finally:
-        spca.tune_table_clear()
