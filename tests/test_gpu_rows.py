@@ -68,3 +68,20 @@ def test_selection_counts(spca, p, s):
     s = min(s, p)
     _check(spca, 1, V_h, s, 1, 0)
     _check(spca, 3, V_h, float(s), 1, 0)
+
+
+@pytest.mark.parametrize("p", [5001, 20001])
+@pytest.mark.parametrize("fid,par", [(1, 40), (1, 3000), (3, 30.0), (5, 4.0), (7, 1.5)])
+def test_in_place(spca, fid, par, p):
+    """X = V: long rows then take the paths that do not keep state in X."""
+    V_h = _rows(p, np.random.default_rng(p + fid))
+    V = torch.from_numpy(V_h).cuda()
+    X, phi, nnz = spca.x_update(fid, V, par)
+    W = V.clone()
+    out = (W, torch.empty_like(phi), torch.empty_like(nnz))
+    spca.x_update(fid, W, par, out=out)
+    torch.cuda.synchronize()
+    assert torch.equal(out[2], nnz) and torch.allclose(out[1], phi, rtol=1e-13, atol=0)
+    # the same decisions and values; norms summed in another order
+    assert torch.equal(W != 0, X != 0)
+    assert float((W - X).abs().max()) <= 2.0 ** -24
