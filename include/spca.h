@@ -366,15 +366,20 @@ int spca_gemm_nt_bf16(void* stream, const uint16_t* P, int64_t ldp,
                       const uint16_t* Q, int64_t ldq, float* C, int64_t ldc,
                       int64_t M, int64_t N, int64_t K);
 /* The BF16 product with a given tile shape and K split, as
- * spca_gemm_nt_f32_shape (C holds `splits` partial products).             */
+ * spca_gemm_nt_f32_shape (C holds `splits` partial products).  Shapes 0 to
+ * 11 are the workgroup tiles, 96 to 101 (one split, K >= 64) those loaded
+ * straight to LDS: 16x16, 16x32, 32x32, 64x64 and 128x64 with K shared by
+ * the waves, and 256x224.                                                  */
 int spca_gemm_nt_bf16_shape(void* stream, const uint16_t* P, int64_t ldp,
                             const uint16_t* Q, int64_t ldq, float* C, int64_t ldc,
                             int64_t M, int64_t N, int64_t K, int shape, int splits);
 
 /* Tuning and testing variant of spca_gemm_nt_f32 with a forced tile shape
- * (0 .. 8: BMxBN of 128x128, 128x160, 128x96, 128x64, 64x128, 32x128,
- * 64x256, 256x128, 256x256) and
- * K split count (1 .. 64).  With splits > 1, C must hold splits x M rows:
+ * and K split count (1 .. 64).  Shapes 0 to 11 are workgroup tiles (BMxBN of
+ * 128x128, 128x160, 128x96, 128x64, 64x128, 32x128, 64x256, 256x128, 256x256
+ * by 2x2, 2x4 and 4x2 waves, 64x128 with two slabs in flight), 32 to 37
+ * one-wave tiles (64x32, 32x64, 32x32, 64x16, 16x32, 16x16; the same bits),
+ * 64 to 71 tiles on BF16 parts (one split, K >= 192, ldp, ldq <= 2^21).  With splits > 1, C must hold splits x M rows:
  * split s writes its partial product (K slabs s*ceil(K/32/splits) onward)
  * at C + s * M * ldc, and the product is the sum of the partials.       */
 int spca_gemm_nt_f32_shape(void* stream, const float* P, int64_t ldp,
@@ -382,8 +387,6 @@ int spca_gemm_nt_f32_shape(void* stream, const float* P, int64_t ldp,
                            int64_t M, int64_t N, int64_t K, int shape,
                            int splits);
 
-/* The FP32 tile shape and K split the library picks for an M x N x K product
- * (deterministic, from a model of CU occupancy and tile efficiency).     */
 /* Tuning table of the product tiles: one line per entry,
  *   "elem_bytes max_splits bucket(M) bucket(N) bucket(K) shape splits"
  * with bucket(x) = round(2 log2 x).  Export writes the table as text into
@@ -392,13 +395,17 @@ int spca_gemm_nt_f32_shape(void* stream, const float* P, int64_t ldp,
  * import adds (or replaces) entries from such text (EINVAL on a malformed
  * line, and then nothing is imported); clear removes every entry.  Plans
  * (spca_gemm_nt_f32_plan and the solves) use an entry of their bucket
- * before the cost model.  Shapes 64 to 71 (elem_bytes 4) are the tiles on
- * BF16 parts, which hold for spca_gemm_nt_f32 alone: solves stay on FP32
- * tiles.  Host-only: no device is touched.                                */
+ * before the cost model.  Shapes are those of spca_gemm_nt_f32_shape (0 to
+ * 11 for elem_bytes 2); 64 to 71, the tiles on BF16 parts, hold for
+ * spca_gemm_nt_f32 alone: solves stay on FP32 tiles.  Host-only: no device is touched.                                */
 int spca_tune_table_export(char* buf, size_t cap, size_t* len);
 int spca_tune_table_import(const char* text);
 int spca_tune_table_clear(void);
 
+/* The tile shape and K split the library picks for an M x N x K product
+ * (deterministic, from models of the tiles' times): for max_splits = 1 those
+ * of spca_gemm_nt_f32 on rows of round_up(K, 4) floats, else those of an FP32
+ * solve (whose max_splits is 16).                                          */
 int spca_gemm_nt_f32_plan(int64_t M, int64_t N, int64_t K, int max_splits,
                           int* shape, int* splits);
 

@@ -543,7 +543,8 @@ def gemm_nt_shape(P, Q, shape, splits=1, stream=None):
 
 
 def gemm_plan(M, N, K, max_splits=1):
-    """(shape, splits) the library picks for an M x N x K product."""
+    """(shape, splits) that runs an M x N x K product: of ``gemm_nt`` for
+    max_splits = 1, of an FP32 solve for its 16 (``spca_gemm_nt_f32_plan``)."""
     sh, sp = ctypes.c_int(), ctypes.c_int()
     _check(load().spca_gemm_nt_f32_plan(int(M), int(N), int(K), int(max_splits),
                                         ctypes.byref(sh), ctypes.byref(sp)))

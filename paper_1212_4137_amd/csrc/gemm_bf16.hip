@@ -412,12 +412,13 @@ constexpr KsShape kKsShapes[] = {
     {16, 16, 8, 0.40, 0.50, 0.7}, {16, 32, 8, 0.42, 1.05, 1.3}, {32, 32, 8, 0.55, 1.10, 1.5},
     {64, 64, 8, 2.10, 3.20, 2.0}, {128, 64, 4, 1.60, 2.80, 3.0}, {kTM, kTN, 1, 1.40, 2.00, 9.0},
 };
+constexpr int kNumKs = (int)(sizeof(kKsShapes) / sizeof(kKsShapes[0]));
 
 // The quickest of those, and its time.
 int plan_ks(int64_t M, int64_t N, int64_t K, double* us_out) {
   int best = 0;
   double best_us = 1e300;
-  for (int v = 0; v < (int)(sizeof(kKsShapes) / sizeof(kKsShapes[0])); ++v) {
+  for (int v = 0; v < kNumKs; ++v) {
     const KsShape& s = kKsShapes[v];
     if (M <= s.bm / 2 && s.bm > 64) continue;  // mostly padding rows
     const int64_t wgs = ceil_div(M, (int64_t)s.bm) * ceil_div(N, (int64_t)s.bn);
@@ -437,14 +438,22 @@ int plan_ks(int64_t M, int64_t N, int64_t K, double* us_out) {
 
 }  // namespace
 
-bool gemm_nt_bf16_ks(hipStream_t st, const uint16_t* P, int64_t ldp, const uint16_t* Q,
-                     int64_t ldq, float* C, int64_t ldc, int64_t M, int64_t N, int64_t K,
-                     double other_us) {
-  if (M <= 0 || N <= 0 || K < kSlabK) return false;
+bool bf16_direct_possible(int shape, int64_t K) {
+  return shape >= kBf16Shape0 && shape < kBf16Shape0 + kNumKs && K >= kSlabK;
+}
+
+int plan_bf16_direct(int64_t M, int64_t N, int64_t K, double other_us) {
+  if (K < kSlabK) return -1;
   double us;
   const int v = plan_ks(M, N, K, &us);
-  if (us >= 0.9 * other_us) return false;
-  switch (v) {
+  return us >= 0.9 * other_us ? -1 : kBf16Shape0 + v;
+}
+
+void gemm_nt_bf16_direct(hipStream_t st, const uint16_t* P, int64_t ldp, const uint16_t* Q,
+                         int64_t ldq, float* C, int64_t ldc, int64_t M, int64_t N, int64_t K,
+                         int shape) {
+  if (M <= 0 || N <= 0) return;
+  switch (shape - kBf16Shape0) {
     case 0: launch_ks<1, 1, 8, 2>(st, P, ldp, Q, ldq, C, ldc, M, N, K); break;
     case 1: launch_ks<1, 2, 8, 2>(st, P, ldp, Q, ldq, C, ldc, M, N, K); break;
     case 2: launch_ks<2, 2, 8, 1>(st, P, ldp, Q, ldq, C, ldc, M, N, K); break;
@@ -452,7 +461,6 @@ bool gemm_nt_bf16_ks(hipStream_t st, const uint16_t* P, int64_t ldp, const uint1
     case 4: launch_ks<8, 4, 4, 1>(st, P, ldp, Q, ldq, C, ldc, M, N, K); break;
     default: launch_tile(st, P, ldp, Q, ldq, C, ldc, M, N, K); break;
   }
-  return true;
 }
 
 }  // namespace spca

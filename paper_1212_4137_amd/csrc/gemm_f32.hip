@@ -450,9 +450,10 @@ std::mutex g_tune_mu;
 std::map<TuneKey, GemmPlan> g_tune;
 
 int bucket(int64_t x) { return (int)std::lround(2.0 * std::log2((double)(x > 0 ? x : 1))); }
-// a compiled FP32 / BF16 tile, or (FP32 only) a BF16-part tile
+// a workgroup tile, or (FP32 only) a one-wave or a BF16-part tile
 bool shape_known(int shape, int eb) {
   return (shape >= 0 && shape < kNumShapes) ||
+         (eb == 4 && shape >= kStreamShape0 && shape < kStreamShape0 + gemm_num_stream_shapes()) ||
          (eb == 4 && shape >= kSplitShape0 && shape < kSplitShape0 + gemm_num_split_shapes());
 }
 TuneKey key_of(int64_t M, int64_t N, int64_t K, int ms, int eb) {
@@ -545,7 +546,7 @@ double f32_model_us(double cycles) { return cycles * 1.2 / 2400.0 + 3.0; }
 GemmPlan plan_f32(int64_t M, int64_t N, int64_t K, int max_splits, double* us_out) {
   GemmPlan t;
   if (us_out != nullptr) *us_out = 0.0;
-  if (tuned_plan(M, N, K, max_splits, 4, &t) && t.shape < kStreamShape0)
+  if (tuned_plan(M, N, K, max_splits, 4, &t) && t.shape < kSplitShape0)
     return plan_gemm_nt(M, N, K, max_splits, 4);
   double cycles = 0.0, stream_us = 0.0;
   GemmPlan g = model_plan_gemm_nt(M, N, K, max_splits, 4, &cycles);
@@ -642,6 +643,7 @@ double gemm_bf16_us(int64_t M, int64_t N, int64_t K, int shape) {
 int gemm_num_shapes() { return kNumShapes; }
 int gemm_shape_bm(int shape) {
   if (shape >= kSplitShape0) return split_shape_bm(shape);
+  if (shape >= kStreamShape0) return stream_shape_bm(shape);
   return shape >= 0 && shape < kNumShapes ? kShapes[shape].bm : 0;
 }
 

@@ -256,6 +256,10 @@ void launch_stream(hipStream_t st, const float* P, int64_t ldp, const float* Q, 
 }  // namespace
 
 int gemm_num_stream_shapes() { return kNumStream; }
+int stream_shape_bm(int shape) {
+  const int v = shape - kStreamShape0;
+  return v >= 0 && v < kNumStream ? 16 * kStreamShapes[v].fm : 0;
+}
 
 // The tile with the least modelled time at a given K split (which the sums
 // depend on): 5 us of launch and first loads, then the slabs of a round of

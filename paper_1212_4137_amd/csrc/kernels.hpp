@@ -151,6 +151,7 @@ GemmPlan plan_product_f32(int64_t M, int64_t N, int64_t K, int64_t ldp, int64_t 
 int gemm_num_shapes();
 // one-wave FP32 tiles (gemm_stream.hip): the bits of gemm_nt_kernel's tiles
 int gemm_num_stream_shapes();
+int stream_shape_bm(int shape);
 int model_stream(int64_t M, int64_t N, int64_t K, int splits, double* us_out);
 void gemm_nt_stream(hipStream_t st, const float* P, int64_t ldp, const float* Q, int64_t ldq,
                     float* C, int64_t ldc, int64_t M, int64_t N, int64_t K, const int32_t* gate,
@@ -197,11 +198,15 @@ void gemm_nt_bf16(hipStream_t st, const uint16_t* P, int64_t ldp,
                   const uint16_t* Q, int64_t ldq, float* C, int64_t ldc,
                   int64_t M, int64_t N, int64_t K, const int32_t* gate,
                   int32_t gate_run, GemmPlan plan, int64_t split_stride);
-// The unsplit product with K shared by the waves of small tiles (gemm_bf16.hip);
-// false (nothing launched) where that takes longer than other_us.
-bool gemm_nt_bf16_ks(hipStream_t st, const uint16_t* P, int64_t ldp, const uint16_t* Q,
-                     int64_t ldq, float* C, int64_t ldc, int64_t M, int64_t N, int64_t K,
-                     double other_us);
+// The unsplit BF16 product with the operands loaded straight to LDS
+// (gemm_bf16.hip), tiles from kBf16Shape0 on: whether a shape can take it, the
+// model's choice (-1 where other_us is less), and the launch.
+constexpr int kBf16Shape0 = 96;
+bool bf16_direct_possible(int shape, int64_t K);
+int plan_bf16_direct(int64_t M, int64_t N, int64_t K, double other_us);
+void gemm_nt_bf16_direct(hipStream_t st, const uint16_t* P, int64_t ldp, const uint16_t* Q,
+                         int64_t ldq, float* C, int64_t ldc, int64_t M, int64_t N, int64_t K,
+                         int shape);
 // Estimated microseconds of an unsplit product with a BF16 tile of gemm_nt_kernel.
 double gemm_bf16_us(int64_t M, int64_t N, int64_t K, int shape);
 

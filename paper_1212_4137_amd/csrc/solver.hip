@@ -1511,8 +1511,10 @@ int spca_gemm_nt_f32_shape(void* stream, const float* P, int64_t ldp,
                "ldp and ldq must be multiples of 4");
   SPCA_REQUIRE((uintptr_t)P % 16 == 0 && (uintptr_t)Q % 16 == 0,
                "P and Q must be 16-byte aligned");
-  SPCA_REQUIRE(shape >= 0 && shape < gemm_num_shapes(), "shape index out of range");
+  SPCA_REQUIRE(shape >= 0 && gemm_shape_bm(shape) > 0, "shape index out of range");
   SPCA_REQUIRE(splits >= 1 && splits <= 64, "splits must be in 1..64");
+  SPCA_REQUIRE(shape < kSplitShape0 || (splits == 1 && split_possible(K, ldp, ldq)),
+               "tiles on BF16 parts take one split, K >= 192 and ldp, ldq <= 2^21");
   gemm_nt_f32((hipStream_t)stream, P, ldp, Q, ldq, C, ldc, M, N, K, nullptr, 0,
               GemmPlan{shape, splits}, M * ldc);
   SPCA_LAUNCH_CHECK("gemm_nt_f32");
@@ -1530,10 +1532,14 @@ int spca_gemm_nt_bf16_shape(void* stream, const uint16_t* P, int64_t ldp,
   SPCA_REQUIRE(ldp % 8 == 0 && ldq % 8 == 0, "ldp and ldq must be multiples of 8");
   SPCA_REQUIRE((uintptr_t)P % 16 == 0 && (uintptr_t)Q % 16 == 0,
                "P and Q must be 16-byte aligned");
-  SPCA_REQUIRE(shape >= 0 && shape < gemm_num_shapes(), "shape index out of range");
+  const bool direct = bf16_direct_possible(shape, K) && splits == 1;
+  SPCA_REQUIRE(direct || (shape >= 0 && shape < gemm_num_shapes()), "shape index out of range");
   SPCA_REQUIRE(splits >= 1 && splits <= 64, "splits must be in 1..64");
-  gemm_nt_bf16((hipStream_t)stream, P, ldp, Q, ldq, C, ldc, M, N, K, nullptr, 0,
-               GemmPlan{shape, splits}, M * ldc);
+  if (direct)
+    gemm_nt_bf16_direct((hipStream_t)stream, P, ldp, Q, ldq, C, ldc, M, N, K, shape);
+  else
+    gemm_nt_bf16((hipStream_t)stream, P, ldp, Q, ldq, C, ldc, M, N, K, nullptr, 0,
+                 GemmPlan{shape, splits}, M * ldc);
   SPCA_LAUNCH_CHECK("gemm_nt_bf16");
   return SPCA_OK;
 }
@@ -1552,9 +1558,12 @@ int spca_gemm_nt_bf16(void* stream, const uint16_t* P, int64_t ldp,
                "P and Q must be 16-byte aligned");
   const GemmPlan g = plan_gemm_nt(M, N, K, 1, 2);
   GemmPlan tuned;  // a tuning table entry holds
-  if (tuned_plan(M, N, K, 1, 2, &tuned) ||
-      !gemm_nt_bf16_ks((hipStream_t)stream, P, ldp, Q, ldq, C, ldc, M, N, K,
-                       gemm_bf16_us(M, N, K, g.shape)))
+  const int direct = tuned_plan(M, N, K, 1, 2, &tuned)
+                         ? -1
+                         : plan_bf16_direct(M, N, K, gemm_bf16_us(M, N, K, g.shape));
+  if (direct >= 0)
+    gemm_nt_bf16_direct((hipStream_t)stream, P, ldp, Q, ldq, C, ldc, M, N, K, direct);
+  else
     gemm_nt_bf16((hipStream_t)stream, P, ldp, Q, ldq, C, ldc, M, N, K, nullptr, 0, g, 0);
   SPCA_LAUNCH_CHECK("gemm_nt_bf16");
   return SPCA_OK;
@@ -1590,7 +1599,9 @@ int spca_gemm_nt_f32_plan(int64_t M, int64_t N, int64_t K, int max_splits,
   SPCA_REQUIRE(shape && splits, "shape and splits must not be NULL");
   SPCA_REQUIRE(M >= 1 && N >= 1 && K >= 1 && max_splits >= 1,
                "sizes and max_splits must be >= 1");
-  GemmPlan g = plan_gemm_nt(M, N, K, max_splits);
+  const GemmPlan g = max_splits == 1
+                         ? plan_product_f32(M, N, K, round_up(K, 4), round_up(K, 4))
+                         : plan_f32(M, N, K, max_splits);
   *shape = g.shape;
   *splits = g.splits;
   return SPCA_OK;
