@@ -193,11 +193,11 @@ typedef struct {
 #define SPCA_FLAG_GRAPH 1
 #define SPCA_FLAG_CHECK_FINITE 2 /* reject A holding NaN or Inf (EINVAL)     */
 #define SPCA_FLAG_DENSE_ONLY 4   /* never use the sparse A x product         */
-/* SPCA_FLAG_AUTOTUNE: before iterating, time every compiled tile shape and
- * K split of the two products on this solve's own operands (products whose
- * size bucket already has a tuning-table entry are skipped) and record the
- * fastest in the process-wide tuning table, which later plans use.  A
- * product's result depends on its K split, so tuned solves are
+/* SPCA_FLAG_AUTOTUNE: before iterating, time every compiled FP32 (or BF16)
+ * tile shape and K split of the two products on this solve's own operands
+ * (products whose size bucket already has a tuning-table entry are skipped)
+ * and record the fastest in the process-wide tuning table, which later plans
+ * use.  A product's result depends on its K split, so tuned solves are
  * reproducible given the table (see spca_tune_table_export).              */
 #define SPCA_FLAG_AUTOTUNE 8
 /* SPCA_FLAG_NO_UNION: never use the union-of-supports product; its gather

@@ -221,10 +221,11 @@ static int ensure_capture_stream(spca_ctx* ctx) {
 
 using namespace spca;
 
-// Times `launch` for every compiled shape and every power-of-two split up to
-// split_cap (3 runs after 1 warm-up, HIP events on the stream) and records
-// the fastest in the tuning table under (M, N, K, max_splits).  Shapes whose
-// rows would be mostly padding are skipped, as in the model.
+// Times `launch` for every compiled shape (FP32: the one-wave tiles too) and
+// every power-of-two split up to split_cap (3 runs after 1 warm-up, HIP events
+// on the stream) and records the fastest in the tuning table under (M, N, K,
+// max_splits).  Shapes whose rows would be mostly padding are skipped, as in
+// the model.
 template <typename F>
 static int autotune_product(hipStream_t st, int64_t M, int64_t N, int64_t K,
                             int split_cap, int max_splits, int eb, F launch) {
@@ -239,7 +240,9 @@ static int autotune_product(hipStream_t st, int64_t M, int64_t N, int64_t K,
   float best_ms = 3.4e38f;
   hipError_t err = hipSuccess;
   const int cap = max_feasible_splits(K, split_cap, eb);
-  for (int shape = 0; shape < gemm_num_shapes() && err == hipSuccess; ++shape) {
+  const int one_wave = eb == 4 ? gemm_num_stream_shapes() : 0;
+  for (int v = 0; v < gemm_num_shapes() + one_wave && err == hipSuccess; ++v) {
+    const int shape = v < gemm_num_shapes() ? v : kStreamShape0 + v - gemm_num_shapes();
     const int bm = gemm_shape_bm(shape);
     if (bm > 32 && M <= bm / 2) continue;
     for (int splits = 1; splits <= cap && err == hipSuccess; splits *= 2) {

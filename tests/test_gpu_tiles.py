@@ -96,3 +96,28 @@ def test_plan_is_what_runs(spca):
         P, Q = (_operand(g, rows, K, 4, torch.float32) for rows in (M, N))
         assert torch.equal(spca.gemm_nt(P, Q),
                            spca.gemm_nt_shape(P, Q, *spca.gemm_plan(M, N, K))[0])
+
+
+def test_autotune_times_the_one_wave_tiles(spca):
+    """Few starts: the one-wave tiles take a third to two thirds of the
+    workgroup tiles' time on both products, and the table holds them."""
+    g = torch.Generator(device="cuda").manual_seed(6)
+    n, p, r = 1000, 8000, 12
+    A = torch.randn(p, n, generator=g, device="cuda").t()
+    X0 = torch.randn(r, p, generator=g, device="cuda")
+    X0 /= X0.norm(dim=1, keepdim=True)
+    spca.tune_table_clear()
+    try:
+        tuned = spca.am_solve(A, 1, 20.0, X0, tol=-1.0, maxit=3, flags=spca.FLAG_AUTOTUNE,
+                              return_X=True)
+        table = spca.tune_table_export()
+        shapes = [int(line.split()[5]) for line in table.splitlines()]
+        assert any(32 <= shape < 38 for shape in shapes), table
+        assert spca.gemm_plan(r, n, p, 16)[0] in shapes
+        again = spca.am_solve(A, 1, 20.0, X0, tol=-1.0, maxit=3, return_X=True)
+        assert torch.equal(tuned["X_final"], again["X_final"])  # from the table
+        spca.tune_table_clear()
+        spca.tune_table_import(table)
+        assert spca.tune_table_export() == table
+    finally:
+        spca.tune_table_clear()
