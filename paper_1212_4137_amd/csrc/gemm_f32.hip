@@ -552,12 +552,14 @@ GemmPlan plan_f32(int64_t M, int64_t N, int64_t K, int max_splits, double* us_ou
   GemmPlan g = model_plan_gemm_nt(M, N, K, max_splits, 4, &cycles);
   double us = f32_model_us(cycles);
   // One-wave tiles where few tiles and a long K loop leave the workgroup
-  // tiles waiting for memory: 64 x 2000 x 2500 86 to 29 us, 16 x 300 x 750 29
-  // to 8 us, 1024 x 1000 x 1250 54 to 38 us.  Where the matrix cores are
-  // busy the workgroup tiles are as fast (64 x 20000 x 1000: 56 and 50 us),
-  // hence the margin.
+  // tiles waiting for memory: 16 x 1000 x 8000 24 to 12 us, 12 x 162 x 24937
+  // 57 to 21, 339 x 653 x 10114 76 to 61, 64 x 2000 x 20000 72 to 65.  From 128
+  // rows on the workgroup tiles without padding do up to a tenth better than
+  // their model, hence the margin there: 128 x 10000 x 1000 35 us on them and
+  // 40 on one-wave tiles, 1024 x 1000 x 1250 34 and 36, 256 x 10000 x 1000
+  // (in a solve) 56.5 and 62.
   const int v = model_stream(M, N, K, g.splits, &stream_us);
-  if (stream_us < 0.85 * us) {
+  if (stream_us < (M >= 128 ? 0.9 : 1.0) * us) {
     us = stream_us;
     g.shape = kStreamShape0 + v;
   }

@@ -229,15 +229,15 @@ __global__ __launch_bounds__(kStreamWaves* kWave, OCC) void stream_group_kernel(
                          kend, lds + wave * StreamTile<FM, FN>::kFloats);
 }
 
-// Compiled tiles (FM, FN) and the time of a slab in microseconds, measured at
-// 64 x 2000 x 2500 and 16 x 8000 x 1000.  A workgroup puts one wave on each
-// SIMD of a CU; with more workgroups than CUs the times add up.
+// Compiled tiles (FM, FN) and the time of a slab in microseconds, measured over
+// 80 products of 1 to 1024 rows.  A workgroup puts one wave on each SIMD of a
+// CU; with more workgroups than CUs the times add up.
 struct StreamShape {
   int fm, fn;
   double slab_us;
 };
-constexpr StreamShape kStreamShapes[] = {{4, 2, 1.24}, {2, 4, 1.22}, {2, 2, 0.73},
-                                         {4, 1, 0.87}, {1, 2, 0.49}, {1, 1, 0.31}};
+constexpr StreamShape kStreamShapes[] = {{4, 2, 1.60}, {2, 4, 1.45}, {2, 2, 0.92},
+                                         {4, 1, 1.00}, {1, 2, 0.66}, {1, 1, 0.38}};
 constexpr int kNumStream = (int)(sizeof(kStreamShapes) / sizeof(kStreamShapes[0]));
 
 template <int FM, int FN, int D, int OCC>
