@@ -28,6 +28,27 @@ __device__ __forceinline__ void spread(uint32_t lo, uint32_t hi, uint32_t (&t)[N
   }
 }
 
+// A step of the search for lambda_s among keys: the sums of (|v| - t)_+ and of
+// its square at the thresholds t of spread() halve [lo, hi) around the largest
+// key with ||.||_1 >= rs ||.||_2.  The first threshold that fails bounds it
+// from above and those before it from below, so that the bracket shrinks with
+// every step even where rounding makes the comparison fall either way (s equal
+// entries: the two sides agree at every t).
+template <int NC>
+__device__ __forceinline__ void lambda_step(const uint32_t (&t)[NC], const double (&acc)[2 * NC],
+                                            double rs, uint32_t& lo, uint32_t& hi) {
+  bool below = true;
+#pragma unroll
+  for (int c = 0; c < NC; ++c) {
+    if (!below || t[c] >= hi) continue;
+    below = acc[2 * c + 1] > 0.0 && acc[2 * c] >= rs * sqrt(acc[2 * c + 1]);
+    if (below)
+      lo = t[c];
+    else
+      hi = t[c];
+  }
+}
+
 // Four floats of a row, loaded and stored with one 16-byte instruction: global
 // memory asks for 4-byte alignment only, so rows of any leading dimension
 // and offset take it (900 x 12285: T_s 31 us, lambda_s 50, U_g 19; one

@@ -966,18 +966,7 @@ __global__ __launch_bounds__(kLT) void wide_lambda_kernel(
           }
         }
         block_sum_n<double, 2 * kNCd>(acc, dred);
-        uint32_t nlo = lo, nhi = hi;
-#pragma unroll
-        for (int c = 0; c < kNCd; ++c) {
-          if (t[c] >= hi) continue;
-          const bool pred = acc[2 * c + 1] > 0.0 && acc[2 * c] >= rs * sqrt(acc[2 * c + 1]);
-          if (pred)
-            nlo = t[c] > nlo ? t[c] : nlo;
-          else
-            nhi = t[c] < nhi ? t[c] : nhi;
-        }
-        lo = nlo;
-        hi = nhi;
+        lambda_step<kNCd>(t, acc, rs, lo, hi);
       }
       const double tl = (double)__uint_as_float(lo), th = (double)__uint_as_float(hi);
       sums(__uint_as_float(lo + 1u), set3);
