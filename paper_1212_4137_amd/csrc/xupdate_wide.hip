@@ -712,7 +712,7 @@ __global__ __launch_bounds__(kRT, 2) void wide_merge_kernel(
     if (tid == 0) s.nnz[j] = -1;
     return;
   }
-  Bracket b{0u, mk + 1u, (uint32_t)slots, 0u, 0u, mk, nan};
+  Bracket b{0u, mk + 1u, (uint32_t)slots, 0u, 0u, mk, nan, false};
   uint32_t need, t;
   if (KIND == kTopS) {
     // the chunks' thresholds are what cp.need of cp.len entries reach
@@ -922,17 +922,21 @@ __global__ __launch_bounds__(kLT) void wide_lambda_kernel(
   if (frozen) {
     lam = wm.gam[j];
   } else {
-    double set3[3];
-    double nans = 0.0;
+    double set3[3] = {0.0, 0.0, 0.0};
     uint32_t mk = 0u;
-    each([&](float vv) {
+    each([&](float vv) {  // all nonzero entries
       const uint32_t key = key_of(vv);
       mk = key > mk ? key : mk;
+      const bool in = fabsf(vv) > 0.f;
+      const double a = (double)(in ? fabsf(vv) : 0.f);
+      set3[0] += in ? 1.0 : 0.0;
+      set3[1] += a;
+      set3[2] += a * a;
     });
     mk = block_max(mk, ured);
-    nans = mk > 0x7f800000u ? 1.0 : 0.0;
-    sums(__uint_as_float(1u), set3);
-    bool done = nans > 0.0 || !(set3[1] > rs * sqrt(set3[2]));  // inactive: lambda = 0
+    block_sum_n<double, 3>(set3, dred);
+    // inactive (or NaN): lambda = 0
+    bool done = mk > 0x7f800000u || !(set3[1] > rs * sqrt(set3[2]));
     for (int round = 0; !done && round < kLamRoundsFull; ++round) {
       const double kk = set3[0];
       if (!(kk > s_par)) break;

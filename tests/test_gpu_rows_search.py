@@ -36,3 +36,59 @@ def test_lambda_s_of_s_equal_entries(spca, p, k):
     np.testing.assert_allclose(phi, want, rtol=1e-11)
     # any lambda below the entries is a root, and they end equal
     assert np.max(np.abs(X - np.sign(V) / np.sqrt(k))) <= 2.0 ** -24
+
+
+def _check(spca, fid, V_h, par):
+    X, phi, nnz = (t.cpu().numpy() for t in spca.x_update(fid, torch.from_numpy(V_h).cuda(), par))
+    for j, v in enumerate(V_h.astype(np.float64)):
+        w, ph = oracle.x_operator(fid, v, par)
+        nrm = np.linalg.norm(w)
+        x = w / nrm if nrm > 0 else w
+        # FP64 sums of p terms in another order, and one FP32 rounding of x
+        assert abs(phi[j] - ph) <= 1e-11 * abs(ph), (fid, par, j)
+        assert np.max(np.abs(X[j] - x)) <= 2.0 ** -24, (fid, par, j)
+        if fid == 1:
+            np.testing.assert_array_equal(X[j] != 0, x != 0)
+
+
+def _time(f, n=20):
+    f()
+    best = float("inf")
+    for _ in range(5):
+        e0, e1 = torch.cuda.Event(enable_timing=True), torch.cuda.Event(enable_timing=True)
+        e0.record()
+        for _ in range(n):
+            f()
+        e1.record()
+        torch.cuda.synchronize()
+        best = min(best, e0.elapsed_time(e1) / n)
+    return best
+
+
+@pytest.mark.parametrize("p", [500, 9999, 20001])
+@pytest.mark.parametrize("scale", [1.0, 1e-14, 1e-22, 1e14, 1e18])
+def test_lambda_s_near_the_inactive_constraint(spca, p, scale):
+    """s around (||v||_1 / ||v||_2)^2, where lambda_s turns zero; scales at
+    which FP32 squares under- and overflow."""
+    print(f"inactive lambda_s p={p} scale={scale}", flush=True)
+    rng = np.random.default_rng(p)
+    V = (rng.standard_normal((4, p)) * scale).astype(np.float32)
+    V[1, p // 20:] = 0.0
+    V[2] *= np.exp(2.0 * rng.standard_normal(p)).astype(np.float32)
+    V[3] = 0.0
+    _check(spca, 3, V[3:], 3.0)
+    for j in range(3):
+        v = np.abs(V[j].astype(np.float64))
+        edge = (v.sum() / np.linalg.norm(v)) ** 2
+        for f in (0.9, 1 - 1e-3, 1 - 1e-5, 1 + 1e-5, 1 + 1e-3, 1.5):
+            _check(spca, 3, V[j:j + 1], max(1.0, min(edge * f, float(p))))
+
+
+def test_inactive_constraints_cost_no_search(spca):
+    """Sparse rows and a large s: lambda_s = 0, a pass like V_gamma's."""
+    g = torch.Generator(device="cuda").manual_seed(1)
+    V = torch.randn(1024, 10000, generator=g, device="cuda")
+    V *= torch.rand(1024, 10000, generator=g, device="cuda") < 0.01
+    out = spca.x_update(7, V, 0.0001)
+    plain = _time(lambda: spca.x_update(7, V, 0.0001, out=out))
+    assert _time(lambda: spca.x_update(3, V, 1000.0, out=out)) <= 2.0 * plain
