@@ -336,7 +336,10 @@ __device__ __forceinline__ double lambda_of(const double (&set3)[3], double s_pa
 // as all nonzero entries.  t has the 8 s largest entries or more above it (a
 // row of noise and s larger entries keeps about 5 s) and at most kSelCap, and
 // the rounds run over those alone (c, if few); S from the whole row does so
-// once it has come down to that.
+// once it has come down to that.  Entries equal to the bound itself (ties at t)
+// can place l below it: the bound then stays, and S loses them.  Where more
+// than s entries equal the largest, no root lies below that: l ends there, S is
+// empty and w = 0, as from the search.
 template <int NPT>
 __device__ __forceinline__ bool lambda_root(float (&v)[NPT], int p, double s_par, RSmem& sm,
                                             float (&c)[kSelPer], bool& few, Bracket& b,
@@ -368,8 +371,9 @@ __device__ __forceinline__ bool lambda_root(float (&v)[NPT], int p, double s_par
   for (int round = 0; round < kLamRoundsFull; ++round) {
     const double kk = set3[0];
     if (!(kk > s_par)) break;
-    const double l = lambda_of(set3, s_par);
-    if (!(l > lam)) break;  // rounding: left to the caller's search
+    double l = lambda_of(set3, s_par);
+    const bool held = !(l > lam);
+    if (held) l = lam;
     if (!few && kk <= (double)kSelCap) {
       compact(v, f, sm, c);
       few = true;
@@ -380,7 +384,15 @@ __device__ __forceinline__ bool lambda_root(float (&v)[NPT], int p, double s_par
     else
       sums_from<NPT>(v, f, set3, sm.dred);
     lam = l;
-    if (set3[0] == kk) return true;  // nested sets of equal size: unchanged
+    if (set3[0] == 0.0) {
+      const double top = (double)__uint_as_float(b.mk);
+      lam = l < top ? l : top;
+      return true;
+    }
+    if (set3[0] == kk) {  // nested sets of equal size: unchanged
+      if (held) break;    // rounding: left to the caller's search
+      return true;
+    }
   }
   few = false;
   return false;

@@ -806,12 +806,16 @@ __global__ __launch_bounds__(kRT, 2) void wide_merge_kernel(
     }
     for (int round = 0; ok && !done && round < kLamRoundsFull; ++round) {
       const double kk = set3[0];
-      const double l = lambda_of(set3, param);
-      ok = kk > param && l > lam;
+      ok = kk > param;
       if (!ok) break;
+      double l = lambda_of(set3, param);
+      const bool held = !(l > lam);
+      if (held) l = lam;
       sums_from<kPer>(c, float_above(l), set3, dred);
       lam = l;
-      done = set3[0] == kk;
+      ok = !held || set3[0] != kk;  // (else rounding)
+      done = ok && (set3[0] == kk || set3[0] == 0.0);
+      if (set3[0] == 0.0) lam = fmin(l, (double)__uint_as_float(mk));
     }
     if (!done) {
       if (tid == 0) s.nnz[j] = -1;
@@ -944,7 +948,8 @@ __global__ __launch_bounds__(kLT) void wide_lambda_kernel(
       if (!(l > lam)) break;
       sums(float_above(l), set3);
       lam = l;
-      done = set3[0] == kk;
+      done = set3[0] == kk || set3[0] == 0.0;
+      if (set3[0] == 0.0) lam = fmin(l, (double)__uint_as_float(mk));
     }
     if (!done) {
       // the largest key t with ||(|v| - t)_+||_1 >= sqrt(s) ||(|v| - t)_+||_2,

@@ -92,3 +92,33 @@ def test_inactive_constraints_cost_no_search(spca):
     out = spca.x_update(7, V, 0.0001)
     plain = _time(lambda: spca.x_update(7, V, 0.0001, out=out))
     assert _time(lambda: spca.x_update(3, V, 1000.0, out=out)) <= 2.0 * plain
+
+
+def _tied(p):
+    """Rows of few distinct magnitudes, with and without a crowd below them."""
+    rng = np.random.default_rng(p)
+    V = rng.integers(-3, 4, size=(4, p)).astype(np.float32)
+    V[1] = np.where(rng.random(p) < 0.1, 2.0, 1.0) * np.sign(rng.standard_normal(p))
+    V[2] = np.float32(0.1) * rng.integers(-40, 41, size=p)
+    V[3, p // 3:] = rng.standard_normal(p - p // 3) * 0.01
+    return V
+
+
+@pytest.mark.parametrize("p", [500, 3001, 12288, 20001])
+def test_ties(spca, p):
+    V = _tied(p)
+    for s in (1, 5, p // 20, p // 10, p // 5, p // 2, p):
+        _check(spca, 1, V, s)
+        if s < p:
+            _check(spca, 3, V, float(s))
+
+
+def test_ties_cost_no_long_search(spca):
+    """lambda_s from tied rows ends in rounds of the closed form, as from rows
+    without ties."""
+    g = torch.Generator(device="cuda").manual_seed(2)
+    V = torch.randn(512, 1000, generator=g, device="cuda")
+    W = torch.randint(-3, 4, (512, 1000), generator=g, device="cuda").float()
+    out = spca.x_update(3, V, 100.0)
+    plain = _time(lambda: spca.x_update(3, V, 100.0, out=out))
+    assert _time(lambda: spca.x_update(3, W, 100.0, out=out)) <= 2.0 * plain
