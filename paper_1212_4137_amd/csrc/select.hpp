@@ -37,16 +37,18 @@ __device__ __forceinline__ void spread(uint32_t lo, uint32_t hi, uint32_t (&t)[N
 template <int NC>
 __device__ __forceinline__ void lambda_step(const uint32_t (&t)[NC], const double (&acc)[2 * NC],
                                             double rs, uint32_t& lo, uint32_t& hi) {
-  bool below = true;
+  bool open = true;  // no threshold has failed yet
+  uint32_t nlo = lo, nhi = hi;
 #pragma unroll
   for (int c = 0; c < NC; ++c) {
-    if (!below || t[c] >= hi) continue;
-    below = acc[2 * c + 1] > 0.0 && acc[2 * c] >= rs * sqrt(acc[2 * c + 1]);
-    if (below)
-      lo = t[c];
-    else
-      hi = t[c];
+    const bool in = open && t[c] < hi;
+    const bool above = acc[2 * c + 1] > 0.0 && acc[2 * c] >= rs * sqrt(acc[2 * c + 1]);
+    nlo = in && above ? t[c] : nlo;
+    nhi = in && !above ? t[c] : nhi;
+    open = in && above;
   }
+  lo = nlo;
+  hi = nhi;
 }
 
 // Four floats of a row, loaded and stored with one 16-byte instruction: global
