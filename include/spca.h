@@ -430,8 +430,8 @@ int spca_x_update(void* stream, int formulation, const float* V, int64_t ldv,
  * on holds until the process ends, instead of allocating it.  The call
  * neither allocates, frees nor synchronizes: it enqueues kernels on the
  * stream and returns.  SPCA_EINVAL (nothing launched) when r rows of
- * length p need more scratch than that (about 19 KB per row at p = 200000;
- * split the rows into batches).  Every call on one device shares that
+ * length p need more scratch than that (T_s of a large s, or X overlapping
+ * V: about 9.5 KB per row at p = 200000; split the rows into batches).  Every call on one device shares that
  * device's array: calls that overlap in time on one device (different
  * streams, or host threads) race and must be serialized by the caller.
  * The call clears what must start at zero itself.  The first call on a

@@ -65,7 +65,9 @@ extern "C" int spca_x_update_noalloc(void* stream, int formulation, const float*
   int rc = check_problem(1, p, 1, formulation, s_or_gamma, r, 0.0, 1);
   if (rc != SPCA_OK) return rc;
   SPCA_REQUIRE(ldv >= p && ldx >= p, "leading dimensions too small");
-  const size_t wb = x_update_wide_bytes(formulation, r, p);
+  const size_t wb = x_update_wide_scratch(formulation, s_or_gamma, V, ldv, r, p, X, ldx)
+                        ? x_update_wide_bytes(formulation, r, p)
+                        : 0;
   if (wb > kScratchBytes) {
     set_error("x-update scratch of " + std::to_string(wb) + " bytes for r = " +
               std::to_string(r) + ", p = " + std::to_string(p) +
@@ -78,9 +80,6 @@ extern "C" int spca_x_update_noalloc(void* stream, int formulation, const float*
   if (wb) {
     rc = scratch_on_current_device(&wide);
     if (rc != SPCA_OK) return rc;
-    if (!x_update_wide_scratch(formulation, s_or_gamma, V, ldv, r, p, X, ldx)) wide = nullptr;
-  }
-  if (wide) {
     // the digit histograms must start at zero (the kernels leave them
     // zero, but an earlier call's state is not relied on)
     const int64_t words = x_update_wide_clear_words(r);

@@ -34,7 +34,6 @@ constexpr int kWN = 16;               // elements per thread
 constexpr int kWCH = kWT * kWN;       // chunk length
 constexpr int kWBins = 2048;          // largest digit (11 bits)
 constexpr int kNWv = kWT / kWave;
-constexpr int kMaxCandW = 2048;       // (sizes the scratch, see x_update_wide_bytes)
 
 struct alignas(64) WRow {
   uint32_t prefix;   // key bits fixed so far (the full key after pass 3)
@@ -65,24 +64,25 @@ struct Wide {
   double* gam;      // r: parameter of each start under the warm-up
 };
 
-Wide carve_wide(void* base, int64_t r, int64_t p) {
+// The scratch of r rows of p entries at base; *bytes: its size.
+Wide carve_wide(void* base, int64_t r, int64_t p, size_t* bytes = nullptr) {
   Wide w;
   w.nch = (int)ceil_div(p, kWCH);
   w.len = (int)round_up(ceil_div(p, w.nch), 4);
   w.xrec = nullptr;
   w.ldx = 0;
-  char* c = (char*)base;
-  size_t off = 0;
-  auto take = [&](size_t bytes) {
-    char* q = c + off;
-    off += (bytes + 255) / 256 * 256;
-    return q;
+  uintptr_t c = (uintptr_t)base;
+  auto take = [&](size_t n) {
+    const uintptr_t q = c;
+    c += (n + 255) / 256 * 256;
+    return (void*)q;
   };
   w.ghist = (uint32_t*)take(sizeof(uint32_t) * kWBins * r);
   w.rows = (WRow*)take(sizeof(WRow) * r);
   w.eqcnt = (int32_t*)take(sizeof(int32_t) * r * w.nch);
   w.cnt = (int32_t*)take(sizeof(int32_t) * r * w.nch);
   w.part = (double*)take(sizeof(double) * 2 * r * w.nch);
+  if (bytes != nullptr) *bytes = (size_t)(c - (uintptr_t)base);
   w.warm_K = 0;
   w.warm_target = 0;
   w.gam = nullptr;
@@ -1138,12 +1138,9 @@ bool x_update_wide_scratch(int fid, double s_or_gamma, const float* V, int64_t l
 size_t x_update_wide_bytes(int fid, int64_t r, int64_t p) {
   (void)fid;
   if (p <= kWideMinP || r < 1) return 0;
-  const int64_t nch = ceil_div(p, kWCH);
-  auto up = [](size_t b) { return (b + 255) / 256 * 256; };
-  return up(sizeof(uint32_t) * kWBins * r) + up(sizeof(WRow) * r) +
-         2 * up(sizeof(int32_t) * r * nch) + up(sizeof(double) * 2 * r * nch) +
-         up(sizeof(double) * 4 * r * nch) + up(sizeof(uint32_t) * r * nch) +
-         up(sizeof(float) * kMaxCandW * r);
+  size_t bytes = 0;
+  (void)carve_wide(nullptr, r, p, &bytes);
+  return bytes;
 }
 
 hipError_t x_update_wide_reset(hipStream_t st, void* scratch, int64_t r) {

@@ -122,3 +122,17 @@ def test_ties_cost_no_long_search(spca):
     out = spca.x_update(3, V, 100.0)
     plain = _time(lambda: spca.x_update(3, V, 100.0, out=out))
     assert _time(lambda: spca.x_update(3, W, 100.0, out=out)) <= 2.0 * plain
+
+
+@pytest.mark.parametrize("fid,par,r", [(3, 20.0, 9000), (1, 20, 9000), (5, 9.0, 9000),
+                                       (1, 3000, 6000)])
+def test_noalloc_refuses_only_what_exceeds_its_scratch(spca, fid, par, r):
+    """Long rows that need no scratch in batches of any size; T_s of a large s
+    as far as the 64 MiB hold its 8.5 KB a row."""
+    V = torch.randn(r, 12500, generator=torch.Generator(device="cuda").manual_seed(r), device="cuda")
+    out = (torch.empty_like(V), torch.empty(r, dtype=torch.float64, device="cuda"),
+           torch.empty(r, dtype=torch.int32, device="cuda"))
+    spca.x_update(fid, V, par, out=out, noalloc=True)
+    ref = spca.x_update(fid, V, par)
+    for a, b in zip(out, ref):
+        assert torch.equal(a, b)
