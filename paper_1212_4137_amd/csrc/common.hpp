@@ -256,6 +256,26 @@ __device__ __forceinline__ float bf16_to_f32(uint16_t h) {
   return __uint_as_float((uint32_t)h << 16);
 }
 
+// Marks in C: a product on BF16 parts leaves one at the first element of every 16
+// x 16 block that it cannot serve, and a second launch on FP32 tiles, each of
+// which looks for marks in its own part of C, computes the tiles that hold one.
+// The mark is a quiet NaN with a payload that no sum of the first launch stores.
+constexpr uint32_t kMark = 0x7fc5a9a5u;
+constexpr int kMarkBlock = 16;
+
+// Whether rows [m0, m0 + BM) by columns [n0, n0 + BN) of C hold a mark
+// (wave-uniform, the same in every wave that asks).
+template <int BM, int BN>
+__device__ __forceinline__ bool marked(const float* C, int64_t ldc, int M, int N, int m0, int n0) {
+  constexpr int NM = BM / kMarkBlock, NB = NM * (BN / kMarkBlock);
+  bool hit = false;
+  for (int b = threadIdx.x % kWave; b < NB; b += kWave) {
+    const int row = m0 + (b % NM) * kMarkBlock, col = n0 + (b / NM) * kMarkBlock;
+    if (row < M && col < N) hit |= __float_as_uint(C[(int64_t)row * ldc + col]) == kMark;
+  }
+  return __any(hit);
+}
+
 // Per-start state machine shared by the iteration kernels.
 constexpr int32_t kRunning = -1;
 

@@ -294,7 +294,7 @@ __global__ __launch_bounds__(WM* WN* kWave, DEPTH == 2 ? 3 : 1) void gemm_nt_ker
     int64_t ldq, float* __restrict__ C, int64_t ldc, int M, int N, int K,
     int tiles_m, int tiles_mn, int splits, int kslabs_per_split,
     int64_t split_stride, const int32_t* __restrict__ gate, int32_t gate_run,
-    const int32_t* __restrict__ kdev) {
+    const int32_t* __restrict__ kdev, int marks) {
   using Cfg = GemmCfg<BM, BN, WM, WN>;
   constexpr int SK = kChunks * Elem<T>::kPerChunk;  // K elements per slab
   if (gate != nullptr && *gate != gate_run) return;
@@ -323,6 +323,8 @@ __global__ __launch_bounds__(WM* WN* kWave, DEPTH == 2 ? 3 : 1) void gemm_nt_ker
   const int kbeg = split * kslabs_per_split * SK;
   int kend = kbeg + kslabs_per_split * SK;
   kend = kend < K ? kend : K;
+  // (a wave stores only after the barriers of the K loop: all have looked)
+  if (marks && !marked<BM, BN>(C, ldc, M, N, tm * BM, tn * BN)) return;
   gemm_tile<T, BM, BN, WM, WN, DEPTH>(P, ldp, Q, ldq, C + (int64_t)split * split_stride, ldc,
                                M, N, tm * BM, tn * BN, kbeg, kend, lds);
 }
@@ -360,7 +362,7 @@ template <typename T, int BM, int BN, int WM, int WN, int DEPTH = 1>
 void launch(hipStream_t st, const T* P, int64_t ldp, const T* Q,
             int64_t ldq, float* C, int64_t ldc, int64_t M, int64_t N,
             int64_t K, int splits, int64_t split_stride, const int32_t* gate,
-            int32_t gate_run, const int32_t* kdev) {
+            int32_t gate_run, const int32_t* kdev, int marks) {
   const int tiles_m = (int)ceil_div(M, BM);
   const int tiles_n = (int)ceil_div(N, BN);
   const int kslabs = (int)ceil_div(K, kChunks * Elem<T>::kPerChunk);
@@ -369,50 +371,50 @@ void launch(hipStream_t st, const T* P, int64_t ldp, const T* Q,
   hipLaunchKernelGGL((gemm_nt_kernel<T, BM, BN, WM, WN, DEPTH>), dim3(total),
                      dim3(WM * WN * kWave), 0, st, P, ldp, Q, ldq, C, ldc,
                      (int)M, (int)N, (int)K, tiles_m, tiles_m * tiles_n, splits,
-                     per_split, split_stride, gate, gate_run, kdev);
+                     per_split, split_stride, gate, gate_run, kdev, marks);
 }
 
 template <typename T>
 void dispatch(int shape, hipStream_t st, const T* P, int64_t ldp,
               const T* Q, int64_t ldq, float* C, int64_t ldc, int64_t M,
               int64_t N, int64_t K, int splits, int64_t split_stride,
-              const int32_t* gate, int32_t gate_run, const int32_t* kdev) {
+              const int32_t* gate, int32_t gate_run, const int32_t* kdev, int marks) {
   switch (shape) {
     case 0:
-      launch<T, 128, 128, 2, 2>(st, P, ldp, Q, ldq, C, ldc, M, N, K, splits, split_stride, gate, gate_run, kdev);
+      launch<T, 128, 128, 2, 2>(st, P, ldp, Q, ldq, C, ldc, M, N, K, splits, split_stride, gate, gate_run, kdev, marks);
       break;
     case 1:
-      launch<T, 128, 160, 4, 1>(st, P, ldp, Q, ldq, C, ldc, M, N, K, splits, split_stride, gate, gate_run, kdev);
+      launch<T, 128, 160, 4, 1>(st, P, ldp, Q, ldq, C, ldc, M, N, K, splits, split_stride, gate, gate_run, kdev, marks);
       break;
     case 2:
-      launch<T, 128, 96, 4, 1>(st, P, ldp, Q, ldq, C, ldc, M, N, K, splits, split_stride, gate, gate_run, kdev);
+      launch<T, 128, 96, 4, 1>(st, P, ldp, Q, ldq, C, ldc, M, N, K, splits, split_stride, gate, gate_run, kdev, marks);
       break;
     case 3:
-      launch<T, 128, 64, 2, 2>(st, P, ldp, Q, ldq, C, ldc, M, N, K, splits, split_stride, gate, gate_run, kdev);
+      launch<T, 128, 64, 2, 2>(st, P, ldp, Q, ldq, C, ldc, M, N, K, splits, split_stride, gate, gate_run, kdev, marks);
       break;
     case 4:
-      launch<T, 64, 128, 2, 2>(st, P, ldp, Q, ldq, C, ldc, M, N, K, splits, split_stride, gate, gate_run, kdev);
+      launch<T, 64, 128, 2, 2>(st, P, ldp, Q, ldq, C, ldc, M, N, K, splits, split_stride, gate, gate_run, kdev, marks);
       break;
     case 5:
-      launch<T, 32, 128, 1, 4>(st, P, ldp, Q, ldq, C, ldc, M, N, K, splits, split_stride, gate, gate_run, kdev);
+      launch<T, 32, 128, 1, 4>(st, P, ldp, Q, ldq, C, ldc, M, N, K, splits, split_stride, gate, gate_run, kdev, marks);
       break;
     case 6:
-      launch<T, 64, 256, 1, 4>(st, P, ldp, Q, ldq, C, ldc, M, N, K, splits, split_stride, gate, gate_run, kdev);
+      launch<T, 64, 256, 1, 4>(st, P, ldp, Q, ldq, C, ldc, M, N, K, splits, split_stride, gate, gate_run, kdev, marks);
       break;
     case 7:
-      launch<T, 256, 128, 2, 2>(st, P, ldp, Q, ldq, C, ldc, M, N, K, splits, split_stride, gate, gate_run, kdev);
+      launch<T, 256, 128, 2, 2>(st, P, ldp, Q, ldq, C, ldc, M, N, K, splits, split_stride, gate, gate_run, kdev, marks);
       break;
     case 8:
-      launch<T, 256, 256, 2, 2>(st, P, ldp, Q, ldq, C, ldc, M, N, K, splits, split_stride, gate, gate_run, kdev);
+      launch<T, 256, 256, 2, 2>(st, P, ldp, Q, ldq, C, ldc, M, N, K, splits, split_stride, gate, gate_run, kdev, marks);
       break;
     case 9:
-      launch<T, 256, 256, 2, 4>(st, P, ldp, Q, ldq, C, ldc, M, N, K, splits, split_stride, gate, gate_run, kdev);
+      launch<T, 256, 256, 2, 4>(st, P, ldp, Q, ldq, C, ldc, M, N, K, splits, split_stride, gate, gate_run, kdev, marks);
       break;
     case 10:
-      launch<T, 256, 256, 4, 2>(st, P, ldp, Q, ldq, C, ldc, M, N, K, splits, split_stride, gate, gate_run, kdev);
+      launch<T, 256, 256, 4, 2>(st, P, ldp, Q, ldq, C, ldc, M, N, K, splits, split_stride, gate, gate_run, kdev, marks);
       break;
     default:
-      launch<T, 64, 128, 2, 2, 2>(st, P, ldp, Q, ldq, C, ldc, M, N, K, splits, split_stride, gate, gate_run, kdev);
+      launch<T, 64, 128, 2, 2, 2>(st, P, ldp, Q, ldq, C, ldc, M, N, K, splits, split_stride, gate, gate_run, kdev, marks);
       break;
   }
 }
@@ -652,19 +654,20 @@ int gemm_shape_bm(int shape) {
 void gemm_nt_f32(hipStream_t st, const float* P, int64_t ldp, const float* Q,
                  int64_t ldq, float* C, int64_t ldc, int64_t M, int64_t N,
                  int64_t K, const int32_t* gate, int32_t gate_run,
-                 GemmPlan plan, int64_t split_stride, const int32_t* kdev) {
+                 GemmPlan plan, int64_t split_stride, const int32_t* kdev, bool marks) {
   if (M <= 0 || N <= 0) return;
   if (plan.shape >= kSplitShape0) {
     gemm_nt_split(st, P, ldp, Q, ldq, C, ldc, M, N, K, plan.shape);
     return;
   }
   if (plan.shape >= kStreamShape0) {
-    gemm_nt_stream(st, P, ldp, Q, ldq, C, ldc, M, N, K, gate, gate_run, plan, split_stride);
+    gemm_nt_stream(st, P, ldp, Q, ldq, C, ldc, M, N, K, gate, gate_run, plan, split_stride,
+                   marks);
     return;
   }
   if (kdev != nullptr) plan.splits = 1;
   dispatch<float>(plan.shape, st, P, ldp, Q, ldq, C, ldc, M, N, K, plan.splits,
-                  split_stride, gate, gate_run, kdev);
+                  split_stride, gate, gate_run, kdev, marks);
 }
 
 void gemm_nt_bf16(hipStream_t st, const uint16_t* P, int64_t ldp,
@@ -673,7 +676,7 @@ void gemm_nt_bf16(hipStream_t st, const uint16_t* P, int64_t ldp,
                   int32_t gate_run, GemmPlan plan, int64_t split_stride) {
   if (M <= 0 || N <= 0) return;
   dispatch<uint16_t>(plan.shape, st, P, ldp, Q, ldq, C, ldc, M, N, K,
-                     plan.splits, split_stride, gate, gate_run, nullptr);
+                     plan.splits, split_stride, gate, gate_run, nullptr, 0);
 }
 
 }  // namespace spca

@@ -12,11 +12,12 @@
 // (2.5 PFLOP/s against 157 TFLOP/s), so six products cost 3/8 of the FP32
 // ones.
 //
-// Range.  Sums that overflow, hold an infinity or NaN, or lie so low that
-// parts of an operand fall under the BF16 or FP32 range are recomputed with
-// FP32 MFMAs straight from global memory (redo, below): infinities and NaN
-// come out as the FP32 instructions give them, and operands down to the
-// denormals keep their FP32 accuracy.
+// Range.  16 x 16 blocks of C with a sum that overflows, holds an infinity or
+// NaN, or lies so low that parts of an operand fall under the BF16 or FP32
+// range are marked (common.hpp), and a second launch computes the tiles of the
+// FP32 product that hold a mark: infinities and NaN come out as its
+// instructions give them, and operands down to the denormals keep their FP32
+// accuracy.  That launch takes 3 to 4 us where it finds nothing.
 //
 // split_pp_kernel, large tiles (256 x 160 or 256 x 128 per workgroup of 8
 // waves, 64 x 80 or 64 x 64 per wave): both operands staged through LDS as
@@ -128,30 +129,6 @@ __device__ __forceinline__ bool suspect(float s, float amax_p, float amax_q) {
   return a < floor_;
 }
 
-// FP32 MFMAs straight from global memory: the 16 x 16 block (C layout of the
-// 16x16 MFMAs) of rows m0.. of P and n0.. of Q over [kbeg, kend).  Rows past
-// the end repeat the last one.  K enters in the order of gemm_nt_kernel (8 at
-// a time: 0 4, 1 5, 2 6, 3 7), so that sums which overflow end the same way.
-__device__ __forceinline__ fx4 f32_block(const float* __restrict__ P, int64_t ldp,
-                                         const float* __restrict__ Q, int64_t ldq, int M, int N,
-                                         int m0, int n0, int kbeg, int kend) {
-  const int lane = threadIdx.x % kWave, lr = lane % 16, lc = lane / 16;
-  const float* p = P + (int64_t)(m0 + lr < M ? m0 + lr : M - 1) * ldp;
-  const float* q = Q + (int64_t)(n0 + lr < N ? n0 + lr : N - 1) * ldq;
-  fx4 c = {0.f, 0.f, 0.f, 0.f};
-  const int ko = (lc >> 1) + 4 * (lc & 1);
-#pragma unroll 1
-  for (int k8 = kbeg; k8 < kend; k8 += 8) {
-#pragma unroll
-    for (int k = k8 + ko, h = 0; h < 2; ++h, k += 2) {
-      const bool in = k < kend;
-      const float a = in ? q[k] : 0.f, b = in ? p[k] : 0.f;
-      c = __builtin_amdgcn_mfma_f32_16x16x4f32(a, b, c, 0, 0, 0);
-    }
-  }
-  return c;
-}
-
 // Four consecutive columns of C (16-byte aligned)
 __device__ __forceinline__ void store_cols(float* c, int col, int N, fx4 v) {
   if (col + 3 < N) {
@@ -161,6 +138,11 @@ __device__ __forceinline__ void store_cols(float* c, int col, int N, fx4 v) {
     for (int e = 0; e < 3; ++e)
       if (col + e < N) c[e] = v[e];
   }
+}
+
+__device__ __forceinline__ void mark_block(float* C, int64_t ldc, int M, int N, int row,
+                                           int col) {
+  if (row < M && col < N) C[(int64_t)row * ldc + col] = __uint_as_float(kMark);
 }
 
 __device__ __forceinline__ float wave_max(float x) {
@@ -195,11 +177,10 @@ __global__ __launch_bounds__(WM* WN* kWave, 2) void split_pp_kernel(
 
   const int tile = tile_of(blockIdx.x, tiles_mn);
   const int m0 = (tile % tiles_m) * BM, n0 = (tile / tiles_m) * BN;
-  const int kbeg = 0, kend = K;
   // slabs: a partial one (K not a multiple of 32) goes first, where the
   // loop's loads need no guard for it
-  const int nfull = kend > kbeg ? (kend - kbeg) / kSlab : 0;
-  const int part = kend > kbeg && (kend - kbeg) % kSlab != 0 ? 1 : 0;
+  const int nfull = K / kSlab;
+  const int part = K % kSlab != 0 ? 1 : 0;
   const int nslabs = nfull + part;
 
   const int tid = threadIdx.x, lane = tid % kWave;
@@ -208,8 +189,8 @@ __global__ __launch_bounds__(WM* WN* kWave, 2) void split_pp_kernel(
   const int frow = tid / 8, c4 = tid % 8;
 
   // byte offsets of this lane's loads from the tile's first rows
-  const char* Pb = reinterpret_cast<const char*>(P + (int64_t)m0 * ldp + kbeg);
-  const char* Qb = reinterpret_cast<const char*>(Q + (int64_t)n0 * ldq + kbeg);
+  const char* Pb = reinterpret_cast<const char*>(P + (int64_t)m0 * ldp);
+  const char* Qb = reinterpret_cast<const char*>(Q + (int64_t)n0 * ldq);
   uint32_t po[VP], qo[VQ];
 #pragma unroll
   for (int v = 0; v < VP; ++v) {
@@ -234,12 +215,10 @@ __global__ __launch_bounds__(WM* WN* kWave, 2) void split_pp_kernel(
       const int k = nfull * kSlab + 4 * c4;
 #pragma unroll
       for (int v = 0; v < VP; ++v)
-        r.p[v] = load_tail(reinterpret_cast<const float*>(Pb + nfull * 4 * kSlab + po[v]), k,
-                           kend - kbeg);
+        r.p[v] = load_tail(reinterpret_cast<const float*>(Pb + nfull * 4 * kSlab + po[v]), k, K);
 #pragma unroll
       for (int v = 0; v < VQ; ++v)
-        r.q[v] = load_tail(reinterpret_cast<const float*>(Qb + nfull * 4 * kSlab + qo[v]), k,
-                           kend - kbeg);
+        r.q[v] = load_tail(reinterpret_cast<const float*>(Qb + nfull * 4 * kSlab + qo[v]), k, K);
     } else {
       const int kb = kbyte(sl);
 #pragma unroll
@@ -336,7 +315,7 @@ __global__ __launch_bounds__(WM* WN* kWave, 2) void split_pp_kernel(
       // (with a single, partial slab: the rows' first 32 entries, which K >=
       // kSplitMinK makes sure of; never used)
       const int kn = ks + 3 < last ? ks + 3 : last;
-      const int kb = kn < part ? -4 * kbeg : kbyte(kn);
+      const int kb = kn < part ? 0 : kbyte(kn);
       const char* Pn = Pb + kb;
       const char* Qn = Qb + kb;
 #pragma unroll
@@ -394,7 +373,6 @@ __global__ __launch_bounds__(WM* WN* kWave, 2) void split_pp_kernel(
   constexpr int kRow = TN + 4;
   float* strip = reinterpret_cast<float*>(lds) + 64 + wave * 16 * kRow;
   static_assert((64 + WM * WN * 16 * kRow) * 4 <= 2 * kStage, "row strips fit in the stages");
-  bool bad = false;
   auto store_blocks = [&](int i, auto block) {  // the FN blocks of row block i
     const int r0 = m0 + wm * TM + i * 16, c0 = n0 + wn * TN;
     if (vec) {
@@ -417,25 +395,18 @@ __global__ __launch_bounds__(WM* WN* kWave, 2) void split_pp_kernel(
     }
     __builtin_amdgcn_fence(__ATOMIC_SEQ_CST, "wavefront");
   };
+  // a row of blocks with a sum that the parts cannot serve is marked instead
 #pragma unroll
   for (int i = 0; i < FM; ++i) {
+    bool bad = false;
 #pragma unroll
     for (int j = 0; j < FN; ++j)
 #pragma unroll
       for (int e = 0; e < 4; ++e) bad |= suspect(acc[j][i][e], amax_p, amax_q);
-  }
-  if (!__any(bad)) {  // wave-uniform
-#pragma unroll
-    for (int i = 0; i < FM; ++i) store_blocks(i, [&](int j) { return acc[j][i]; });
-  } else {
-#pragma unroll 1
-    for (int i = 0; i < FM; ++i) {
-      fx4 b[FN];
-#pragma unroll
-      for (int j = 0; j < FN; ++j)
-        b[j] = f32_block(P, ldp, Q, ldq, M, N, m0 + wm * TM + i * 16, n0 + wn * TN + j * 16, kbeg,
-                         kend);
-      store_blocks(i, [&](int j) { return b[j]; });
+    if (!__any(bad)) {  // wave-uniform
+      store_blocks(i, [&](int j) { return acc[j][i]; });
+    } else if (lane < FN) {
+      mark_block(Cs, ldc, M, N, m0 + wm * TM + i * 16, n0 + wn * TN + lane * 16);
     }
   }
 }
@@ -457,17 +428,16 @@ template <int FM, int FN>
 __device__ __forceinline__ void ks_tile(const float* __restrict__ P, int64_t ldp,
                                         const float* __restrict__ Q, int64_t ldq,
                                         float* __restrict__ Cs, int64_t ldc, int M, int N, int m0,
-                                        int n0, int kbeg, int kend, char* lds, float* red) {
+                                        int n0, int K, char* lds, float* red) {
   constexpr int RB = (FM + FN) * 16;  // rows of a slab: P's, then Q's
   constexpr int FB = FM * FN;
-  const int nslabs = kend > kbeg ? (kend - kbeg + kSlab - 1) / kSlab : 0;
-  const int nfull = kend > kbeg ? (kend - kbeg) / kSlab : 0;
+  const int nslabs = (K + kSlab - 1) / kSlab, nfull = K / kSlab;
   const int lane = threadIdx.x % kWave;
   const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x / kWave);
   const int nw = blockDim.x / kWave;
   const int lr = lane % 16, lc = lane / 16;
-  const char* Pb = reinterpret_cast<const char*>(P + (int64_t)m0 * ldp + kbeg);
-  const char* Qb = reinterpret_cast<const char*>(Q + (int64_t)n0 * ldq + kbeg);
+  const char* Pb = reinterpret_cast<const char*>(P + (int64_t)m0 * ldp);
+  const char* Qb = reinterpret_cast<const char*>(Q + (int64_t)n0 * ldq);
 
   float amax_p = 0.f, amax_q = 0.f;
   // a fragment: lane (row lr, lc) holds k = 4 lc .. +3 and 16 + 4 lc .. +3
@@ -552,12 +522,12 @@ __device__ __forceinline__ void ks_tile(const float* __restrict__ P, int64_t ldp
     asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
   }
   if (nfull < nslabs && wave == nfull % nw) {  // the partial last slab
-    const int k0 = kbeg + nfull * kSlab;
+    const int k0 = nfull * kSlab;
     auto load_frag = [&](fx4 (&r)[2], const char* base, uint32_t ld, int row) {
       const float* s = reinterpret_cast<const float*>(base + nfull * 4 * kSlab +
                                                       (uint64_t)row * ld * 4u) + 4 * lc;
-      r[0] = load_tail(s, k0 + 4 * lc, kend);
-      r[1] = load_tail(s + 16, k0 + 16 + 4 * lc, kend);
+      r[0] = load_tail(s, k0 + 4 * lc, K);
+      r[1] = load_tail(s + 16, k0 + 16 + 4 * lc, K);
     };
 #pragma unroll
     for (int i = 0; i < FM; ++i) {
@@ -614,11 +584,14 @@ __device__ __forceinline__ void ks_tile(const float* __restrict__ P, int64_t ldp
 #pragma unroll
     for (int e = 0; e < 4; ++e) bad |= suspect(s[e], amax_p, amax_q);
     const int rm = m0 + (b / FN) * 16, cn = n0 + (b % FN) * 16;
-    if (__any(bad)) s = f32_block(P, ldp, Q, ldq, M, N, rm, cn, kbeg, kend);  // wave-uniform
     const int row = rm + lr, col = cn + 4 * lc;
+    bad = __any(bad);  // wave-uniform
+    const float m = __uint_as_float(kMark);
     if (!vec)
-      L[b * kWave + lane] = s;
-    else if (row < M)
+      L[b * kWave + lane] = bad ? fx4{m, m, m, m} : s;
+    else if (bad && lane == 0)
+      mark_block(Cs, ldc, M, N, rm, cn);
+    else if (!bad && row < M)
       store_cols(Cs + (int64_t)row * ldc + col, col, N, s);
   }
   if (vec) return;
@@ -642,7 +615,7 @@ __global__ __launch_bounds__(kKsWaves* kWave, OCC) void split_ks_kernel(
   __shared__ float red[2 * kKsWaves];
   const int tile = tile_of(blockIdx.x, tiles_mn);
   ks_tile<FM, FN>(P, ldp, Q, ldq, C, ldc, M, N, (tile % tiles_m) * FM * 16,
-                  (tile / tiles_m) * FN * 16, 0, K, lds, red);
+                  (tile / tiles_m) * FN * 16, K, lds, red);
 }
 
 // Compiled tiles.  Times of one workgroup step in microseconds, as measured
@@ -689,6 +662,20 @@ void launch_ks(hipStream_t st, const float* P, int64_t ldp, const float* Q, int6
                      ldc, (int)M, (int)N, (int)K, tm, tm * tn);
 }
 
+void launch_parts(hipStream_t st, const float* P, int64_t ldp, const float* Q, int64_t ldq,
+                  float* C, int64_t ldc, int64_t M, int64_t N, int64_t K, int shape) {
+  switch (shape - kSplitShape0) {
+    case 0: launch_pp<256, 160, 4, 2>(st, P, ldp, Q, ldq, C, ldc, M, N, K); break;
+    case 1: launch_pp<256, 128, 4, 2>(st, P, ldp, Q, ldq, C, ldc, M, N, K); break;
+    case 2: launch_ks<4, 5, 2>(st, P, ldp, Q, ldq, C, ldc, M, N, K); break;
+    case 3: launch_ks<4, 4, 2>(st, P, ldp, Q, ldq, C, ldc, M, N, K); break;
+    case 4: launch_ks<4, 2, 2>(st, P, ldp, Q, ldq, C, ldc, M, N, K); break;
+    case 5: launch_ks<2, 2, 4>(st, P, ldp, Q, ldq, C, ldc, M, N, K); break;
+    case 6: launch_ks<4, 1, 2>(st, P, ldp, Q, ldq, C, ldc, M, N, K); break;
+    default: launch_ks<1, 1, 4>(st, P, ldp, Q, ldq, C, ldc, M, N, K); break;
+  }
+}
+
 }  // namespace
 
 int gemm_num_split_shapes() { return kNumSplit; }
@@ -732,16 +719,10 @@ int model_plan_split(int64_t M, int64_t N, int64_t K, double* us_out) {
 void gemm_nt_split(hipStream_t st, const float* P, int64_t ldp, const float* Q, int64_t ldq,
                    float* C, int64_t ldc, int64_t M, int64_t N, int64_t K, int shape) {
   if (M <= 0 || N <= 0) return;
-  switch (shape - kSplitShape0) {
-    case 0: launch_pp<256, 160, 4, 2>(st, P, ldp, Q, ldq, C, ldc, M, N, K); break;
-    case 1: launch_pp<256, 128, 4, 2>(st, P, ldp, Q, ldq, C, ldc, M, N, K); break;
-    case 2: launch_ks<4, 5, 2>(st, P, ldp, Q, ldq, C, ldc, M, N, K); break;
-    case 3: launch_ks<4, 4, 2>(st, P, ldp, Q, ldq, C, ldc, M, N, K); break;
-    case 4: launch_ks<4, 2, 2>(st, P, ldp, Q, ldq, C, ldc, M, N, K); break;
-    case 5: launch_ks<2, 2, 4>(st, P, ldp, Q, ldq, C, ldc, M, N, K); break;
-    case 6: launch_ks<4, 1, 2>(st, P, ldp, Q, ldq, C, ldc, M, N, K); break;
-    default: launch_ks<1, 1, 4>(st, P, ldp, Q, ldq, C, ldc, M, N, K); break;
-  }
+  launch_parts(st, P, ldp, Q, ldq, C, ldc, M, N, K, shape);
+  // the tiles that it marked
+  gemm_nt_f32(st, P, ldp, Q, ldq, C, ldc, M, N, K, nullptr, 0, plan_f32(M, N, K, 1), 0, nullptr,
+              true);
 }
 
 }  // namespace spca

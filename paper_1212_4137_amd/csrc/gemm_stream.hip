@@ -180,7 +180,7 @@ __global__ __launch_bounds__(kStreamWaves* kWave, OCC) void stream_kernel(
     const float* __restrict__ P, int64_t ldp, const float* __restrict__ Q, int64_t ldq,
     float* __restrict__ C, int64_t ldc, int M, int N, int K, int tiles_m, int items, int splits,
     int kslabs_per_split, int64_t split_stride, const int32_t* __restrict__ gate,
-    int32_t gate_run) {
+    int32_t gate_run, int marks) {
   __shared__ __attribute__((aligned(16))) float lds[kStreamWaves * StreamTile<FM, FN>::kFloats];
   if (gate != nullptr && *gate != gate_run) return;
   const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x / kWave);
@@ -196,9 +196,10 @@ __global__ __launch_bounds__(kStreamWaves* kWave, OCC) void stream_kernel(
   const int kbeg = split * kslabs_per_split * kSlabK;
   int kend = kbeg + kslabs_per_split * kSlabK;
   kend = kend < K ? kend : K;
-  stream_tile<FM, FN, D>(P, ldp, Q, ldq, C + (int64_t)split * split_stride, ldc, M, N,
-                         (t % tiles_m) * FM * 16, (t / tiles_m) * FN * 16, kbeg, kend,
-                         lds + wave * StreamTile<FM, FN>::kFloats);
+  const int m0 = (t % tiles_m) * FM * 16, n0 = (t / tiles_m) * FN * 16;
+  if (marks && !marked<FM * 16, FN * 16>(C, ldc, M, N, m0, n0)) return;
+  stream_tile<FM, FN, D>(P, ldp, Q, ldq, C + (int64_t)split * split_stride, ldc, M, N, m0, n0,
+                         kbeg, kend, lds + wave * StreamTile<FM, FN>::kFloats);
 }
 
 // Grouped products: the tiles of several independent products, each owned
@@ -243,14 +244,14 @@ constexpr int kNumStream = (int)(sizeof(kStreamShapes) / sizeof(kStreamShapes[0]
 template <int FM, int FN, int D, int OCC>
 void launch_stream(hipStream_t st, const float* P, int64_t ldp, const float* Q, int64_t ldq,
                    float* C, int64_t ldc, int64_t M, int64_t N, int64_t K, int splits,
-                   int64_t split_stride, const int32_t* gate, int32_t gate_run) {
+                   int64_t split_stride, const int32_t* gate, int32_t gate_run, int marks) {
   const int tm = (int)ceil_div(M, 16 * FM), tn = (int)ceil_div(N, 16 * FN);
   const int per = (int)ceil_div(ceil_div(K, (int64_t)kSlabK), (int64_t)splits);
   const int items = tm * tn * splits;
   hipLaunchKernelGGL((stream_kernel<FM, FN, D, OCC>),
                      dim3((unsigned)ceil_div(items, kStreamWaves)), dim3(kStreamWaves * kWave), 0,
                      st, P, ldp, Q, ldq, C, ldc, (int)M, (int)N, (int)K, tm, items, splits, per,
-                     split_stride, gate, gate_run);
+                     split_stride, gate, gate_run, marks);
 }
 
 }  // namespace
@@ -286,16 +287,16 @@ int model_stream(int64_t M, int64_t N, int64_t K, int splits, double* us_out) {
 
 void gemm_nt_stream(hipStream_t st, const float* P, int64_t ldp, const float* Q, int64_t ldq,
                     float* C, int64_t ldc, int64_t M, int64_t N, int64_t K, const int32_t* gate,
-                    int32_t gate_run, GemmPlan plan, int64_t stride) {
+                    int32_t gate_run, GemmPlan plan, int64_t stride, bool marks) {
   if (M <= 0 || N <= 0) return;
   const int s = plan.splits;
   switch (plan.shape - kStreamShape0) {
-    case 0: launch_stream<4, 2, 2, 2>(st, P, ldp, Q, ldq, C, ldc, M, N, K, s, stride, gate, gate_run); break;
-    case 1: launch_stream<2, 4, 2, 2>(st, P, ldp, Q, ldq, C, ldc, M, N, K, s, stride, gate, gate_run); break;
-    case 2: launch_stream<2, 2, 4, 2>(st, P, ldp, Q, ldq, C, ldc, M, N, K, s, stride, gate, gate_run); break;
-    case 3: launch_stream<4, 1, 3, 2>(st, P, ldp, Q, ldq, C, ldc, M, N, K, s, stride, gate, gate_run); break;
-    case 4: launch_stream<1, 2, 5, 2>(st, P, ldp, Q, ldq, C, ldc, M, N, K, s, stride, gate, gate_run); break;
-    default: launch_stream<1, 1, 8, 2>(st, P, ldp, Q, ldq, C, ldc, M, N, K, s, stride, gate, gate_run); break;
+    case 0: launch_stream<4, 2, 2, 2>(st, P, ldp, Q, ldq, C, ldc, M, N, K, s, stride, gate, gate_run, marks); break;
+    case 1: launch_stream<2, 4, 2, 2>(st, P, ldp, Q, ldq, C, ldc, M, N, K, s, stride, gate, gate_run, marks); break;
+    case 2: launch_stream<2, 2, 4, 2>(st, P, ldp, Q, ldq, C, ldc, M, N, K, s, stride, gate, gate_run, marks); break;
+    case 3: launch_stream<4, 1, 3, 2>(st, P, ldp, Q, ldq, C, ldc, M, N, K, s, stride, gate, gate_run, marks); break;
+    case 4: launch_stream<1, 2, 5, 2>(st, P, ldp, Q, ldq, C, ldc, M, N, K, s, stride, gate, gate_run, marks); break;
+    default: launch_stream<1, 1, 8, 2>(st, P, ldp, Q, ldq, C, ldc, M, N, K, s, stride, gate, gate_run, marks); break;
   }
 }
 

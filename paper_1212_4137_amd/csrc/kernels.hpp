@@ -155,7 +155,7 @@ int stream_shape_bm(int shape);
 int model_stream(int64_t M, int64_t N, int64_t K, int splits, double* us_out);
 void gemm_nt_stream(hipStream_t st, const float* P, int64_t ldp, const float* Q, int64_t ldq,
                     float* C, int64_t ldc, int64_t M, int64_t N, int64_t K, const int32_t* gate,
-                    int32_t gate_run, GemmPlan plan, int64_t split_stride);
+                    int32_t gate_run, GemmPlan plan, int64_t split_stride, bool marks = false);
 // FP32 products on BF16 parts (gemm_split.hip), for products outside a solve:
 // number of tiles, whether a product can use them, the model's choice among
 // them (a shape) with its time, and the launch
@@ -185,12 +185,13 @@ void tune_table_clear();
 // C + s * split_stride.  When gate != nullptr the kernel runs only if
 // *gate == gate_run.  When kdev != nullptr, K is read from *kdev on the
 // device (plan.splits must then be 1, its shape below kSplitShape0).  Shapes
-// from kSplitShape0 on take neither a gate nor splits.
+// from kSplitShape0 on take neither a gate nor splits.  marks: only the tiles
+// that hold a mark of a launch on BF16 parts (common.hpp), unsplit.
 void gemm_nt_f32(hipStream_t st, const float* P, int64_t ldp, const float* Q,
                  int64_t ldq, float* C, int64_t ldc, int64_t M, int64_t N,
                  int64_t K, const int32_t* gate, int32_t gate_run,
                  GemmPlan plan, int64_t split_stride,
-                 const int32_t* kdev = nullptr);
+                 const int32_t* kdev = nullptr, bool marks = false);
 
 // The same product with BF16 operands (bit patterns, ld multiple of 8 and
 // 16-byte aligned rows), FP32 accumulation and output.
