@@ -286,15 +286,17 @@ __device__ __forceinline__ void gemm_tile(const T* __restrict__ P, int64_t ldp,
   }
 }
 
+// MARKS: only the tiles that hold a mark (a kernel of its own: one argument more
+// cost the products of a solve 1%).
 // DEPTH 2 holds two register sets of slabs; its one compiled shape
 // (64 x 128) is held to 168 registers so that a CU keeps three workgroups.
-template <typename T, int BM, int BN, int WM, int WN, int DEPTH = 1>
+template <typename T, int BM, int BN, int WM, int WN, int DEPTH = 1, bool MARKS = false>
 __global__ __launch_bounds__(WM* WN* kWave, DEPTH == 2 ? 3 : 1) void gemm_nt_kernel(
     const T* __restrict__ P, int64_t ldp, const T* __restrict__ Q,
     int64_t ldq, float* __restrict__ C, int64_t ldc, int M, int N, int K,
     int tiles_m, int tiles_mn, int splits, int kslabs_per_split,
     int64_t split_stride, const int32_t* __restrict__ gate, int32_t gate_run,
-    const int32_t* __restrict__ kdev, int marks) {
+    const int32_t* __restrict__ kdev) {
   using Cfg = GemmCfg<BM, BN, WM, WN>;
   constexpr int SK = kChunks * Elem<T>::kPerChunk;  // K elements per slab
   if (gate != nullptr && *gate != gate_run) return;
@@ -324,7 +326,7 @@ __global__ __launch_bounds__(WM* WN* kWave, DEPTH == 2 ? 3 : 1) void gemm_nt_ker
   int kend = kbeg + kslabs_per_split * SK;
   kend = kend < K ? kend : K;
   // (a wave stores only after the barriers of the K loop: all have looked)
-  if (marks && !marked<BM, BN>(C, ldc, M, N, tm * BM, tn * BN)) return;
+  if (MARKS && !marked<BM, BN>(C, ldc, M, N, tm * BM, tn * BN)) return;
   gemm_tile<T, BM, BN, WM, WN, DEPTH>(P, ldp, Q, ldq, C + (int64_t)split * split_stride, ldc,
                                M, N, tm * BM, tn * BN, kbeg, kend, lds);
 }
@@ -362,23 +364,31 @@ template <typename T, int BM, int BN, int WM, int WN, int DEPTH = 1>
 void launch(hipStream_t st, const T* P, int64_t ldp, const T* Q,
             int64_t ldq, float* C, int64_t ldc, int64_t M, int64_t N,
             int64_t K, int splits, int64_t split_stride, const int32_t* gate,
-            int32_t gate_run, const int32_t* kdev, int marks) {
+            int32_t gate_run, const int32_t* kdev, bool marks) {
   const int tiles_m = (int)ceil_div(M, BM);
   const int tiles_n = (int)ceil_div(N, BN);
   const int kslabs = (int)ceil_div(K, kChunks * Elem<T>::kPerChunk);
   const int per_split = (int)ceil_div(kslabs, splits);
   const int total = tiles_m * tiles_n * splits;
-  hipLaunchKernelGGL((gemm_nt_kernel<T, BM, BN, WM, WN, DEPTH>), dim3(total),
-                     dim3(WM * WN * kWave), 0, st, P, ldp, Q, ldq, C, ldc,
-                     (int)M, (int)N, (int)K, tiles_m, tiles_m * tiles_n, splits,
-                     per_split, split_stride, gate, gate_run, kdev, marks);
+  auto run = [&](auto kernel) {
+    hipLaunchKernelGGL(kernel, dim3(total), dim3(WM * WN * kWave), 0, st, P, ldp, Q, ldq, C, ldc,
+                       (int)M, (int)N, (int)K, tiles_m, tiles_m * tiles_n, splits, per_split,
+                       split_stride, gate, gate_run, kdev);
+  };
+  if constexpr (std::is_same_v<T, float>) {
+    if (marks) {
+      run(gemm_nt_kernel<T, BM, BN, WM, WN, DEPTH, true>);
+      return;
+    }
+  }
+  run(gemm_nt_kernel<T, BM, BN, WM, WN, DEPTH>);
 }
 
 template <typename T>
 void dispatch(int shape, hipStream_t st, const T* P, int64_t ldp,
               const T* Q, int64_t ldq, float* C, int64_t ldc, int64_t M,
               int64_t N, int64_t K, int splits, int64_t split_stride,
-              const int32_t* gate, int32_t gate_run, const int32_t* kdev, int marks) {
+              const int32_t* gate, int32_t gate_run, const int32_t* kdev, bool marks) {
   switch (shape) {
     case 0:
       launch<T, 128, 128, 2, 2>(st, P, ldp, Q, ldq, C, ldc, M, N, K, splits, split_stride, gate, gate_run, kdev, marks);
@@ -676,7 +686,7 @@ void gemm_nt_bf16(hipStream_t st, const uint16_t* P, int64_t ldp,
                   int32_t gate_run, GemmPlan plan, int64_t split_stride) {
   if (M <= 0 || N <= 0) return;
   dispatch<uint16_t>(plan.shape, st, P, ldp, Q, ldq, C, ldc, M, N, K,
-                     plan.splits, split_stride, gate, gate_run, nullptr, 0);
+                     plan.splits, split_stride, gate, gate_run, nullptr, false);
 }
 
 }  // namespace spca

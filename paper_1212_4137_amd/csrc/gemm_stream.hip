@@ -175,12 +175,13 @@ __device__ __forceinline__ void stream_tile(const float* __restrict__ P, int64_t
   }
 }
 
-template <int FM, int FN, int D, int OCC>
+// MARKS: only the tiles that hold a mark (common.hpp)
+template <int FM, int FN, int D, int OCC, bool MARKS = false>
 __global__ __launch_bounds__(kStreamWaves* kWave, OCC) void stream_kernel(
     const float* __restrict__ P, int64_t ldp, const float* __restrict__ Q, int64_t ldq,
     float* __restrict__ C, int64_t ldc, int M, int N, int K, int tiles_m, int items, int splits,
     int kslabs_per_split, int64_t split_stride, const int32_t* __restrict__ gate,
-    int32_t gate_run, int marks) {
+    int32_t gate_run) {
   __shared__ __attribute__((aligned(16))) float lds[kStreamWaves * StreamTile<FM, FN>::kFloats];
   if (gate != nullptr && *gate != gate_run) return;
   const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x / kWave);
@@ -197,7 +198,7 @@ __global__ __launch_bounds__(kStreamWaves* kWave, OCC) void stream_kernel(
   int kend = kbeg + kslabs_per_split * kSlabK;
   kend = kend < K ? kend : K;
   const int m0 = (t % tiles_m) * FM * 16, n0 = (t / tiles_m) * FN * 16;
-  if (marks && !marked<FM * 16, FN * 16>(C, ldc, M, N, m0, n0)) return;
+  if (MARKS && !marked<FM * 16, FN * 16>(C, ldc, M, N, m0, n0)) return;
   stream_tile<FM, FN, D>(P, ldp, Q, ldq, C + (int64_t)split * split_stride, ldc, M, N, m0, n0,
                          kbeg, kend, lds + wave * StreamTile<FM, FN>::kFloats);
 }
@@ -244,14 +245,19 @@ constexpr int kNumStream = (int)(sizeof(kStreamShapes) / sizeof(kStreamShapes[0]
 template <int FM, int FN, int D, int OCC>
 void launch_stream(hipStream_t st, const float* P, int64_t ldp, const float* Q, int64_t ldq,
                    float* C, int64_t ldc, int64_t M, int64_t N, int64_t K, int splits,
-                   int64_t split_stride, const int32_t* gate, int32_t gate_run, int marks) {
+                   int64_t split_stride, const int32_t* gate, int32_t gate_run, bool marks) {
   const int tm = (int)ceil_div(M, 16 * FM), tn = (int)ceil_div(N, 16 * FN);
   const int per = (int)ceil_div(ceil_div(K, (int64_t)kSlabK), (int64_t)splits);
   const int items = tm * tn * splits;
-  hipLaunchKernelGGL((stream_kernel<FM, FN, D, OCC>),
-                     dim3((unsigned)ceil_div(items, kStreamWaves)), dim3(kStreamWaves * kWave), 0,
-                     st, P, ldp, Q, ldq, C, ldc, (int)M, (int)N, (int)K, tm, items, splits, per,
-                     split_stride, gate, gate_run, marks);
+  auto run = [&](auto kernel) {
+    hipLaunchKernelGGL(kernel, dim3((unsigned)ceil_div(items, kStreamWaves)),
+                       dim3(kStreamWaves * kWave), 0, st, P, ldp, Q, ldq, C, ldc, (int)M, (int)N,
+                       (int)K, tm, items, splits, per, split_stride, gate, gate_run);
+  };
+  if (marks)
+    run(stream_kernel<FM, FN, D, OCC, true>);
+  else
+    run(stream_kernel<FM, FN, D, OCC>);
 }
 
 }  // namespace
