@@ -348,10 +348,12 @@ const char* spca_last_error(void);
  * of an AM iteration, Section 4: U^T = X^T A^T and V^T = Y^T A; solves form
  * theirs on the FP32 matrix instructions throughout).  From K = 192 on the
  * product runs, where that is faster, on BF16 matrix instructions over three
- * BF16 parts of each operand, whose sum is the FP32 value: errors no larger
- * than those of the FP32 instructions, infinities, NaN and tiny operands as
- * those treat them.  P is M x K,
- * Q is N x K, C is M x N, all row-major in device memory with leading
+ * BF16 parts of each operand, whose sum is the FP32 value: of dense rows the
+ * error against FP64 is below that of the FP32 instructions (normwise; 2.1e-7
+ * and 5.7e-7 for unit Gaussian rows of 1000).  Rows with more than a
+ * twentieth of zeros, infinities, NaN and sums of tiny operands are found on the
+ * device and computed with the FP32 instructions, with their bits.  P is M x
+ * K, Q is N x K, C is M x N, all row-major in device memory with leading
  * dimensions ldp, ldq >= K and ldc >= N.  ldp and ldq must be multiples of
  * 4 and P, Q 16-byte aligned (SPCA_EINVAL otherwise).                    */
 int spca_gemm_nt_f32(void* stream, const float* P, int64_t ldp, const float* Q,

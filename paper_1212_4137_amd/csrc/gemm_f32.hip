@@ -587,17 +587,16 @@ GemmPlan plan_product_f32(int64_t M, int64_t N, int64_t K, int64_t ldp, int64_t 
     if (t.shape >= kSplitShape0 && !split) return model_plan_gemm_nt(M, N, K, 1, 4);
     return plan_gemm_nt(M, N, K, 1, 4);
   }
-  // Both models in microseconds.  The FP32 tiles stay ahead only where K is
-  // short and the large tiles are mostly padding: 300 x 45359 x 240 takes 83
-  // us on them and 91 us on BF16 parts.  The models are good to a tenth, so
-  // the parts have to promise that much (62 x 24975 x 434, promised 5%: 32.2
-  // us on parts, 30.2 on FP32 tiles); over 100 sizes with 16 to 1024 rows, K
-  // from 200 to 50000, they are up to 20 times faster otherwise.
+  // Both models in microseconds, and 3 us for a launch, 7 for the two of the large
+  // tiles.  Over 140 sizes of 1 to 1024 rows, K from 192 to 50000, the choice is 2%
+  // from the better one of both, the parts up to 20 times faster; the FP32 tiles
+  // stay ahead where K is short (300 x 45359 x 240: 87 us on them, 100 on parts;
+  // 62 x 24975 x 434: 27 and 34).
   double us = 0.0, parts_us = 0.0;
   const GemmPlan f32 = plan_f32(M, N, K, 1, &us);
   if (!split) return f32;
   const int parts = model_plan_split(M, N, K, &parts_us);
-  return parts_us + 3.0 >= 0.9 * us ? f32 : GemmPlan{parts, 1};
+  return parts_us + (split_own_redo(parts) ? 3.0 : 7.0) < us ? GemmPlan{parts, 1} : f32;
 }
 
 GemmPlan model_plan_gemm_nt(int64_t M, int64_t N, int64_t K, int max_splits,

@@ -161,6 +161,7 @@ void gemm_nt_stream(hipStream_t st, const float* P, int64_t ldp, const float* Q,
 // them (a shape) with its time, and the launch
 int gemm_num_split_shapes();
 int split_shape_bm(int shape);
+bool split_own_redo(int shape);  // one launch, two otherwise
 constexpr int64_t kSplitMinK = 192;
 bool split_possible(int64_t K, int64_t ldp, int64_t ldq);
 int model_plan_split(int64_t M, int64_t N, int64_t K, double* us_out);
