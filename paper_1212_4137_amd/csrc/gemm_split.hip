@@ -16,8 +16,8 @@
 // C with a sum that overflows, holds an infinity or NaN, or lies so low that parts
 // of an operand fall under the BF16 or FP32 range (see suspect).  The small tiles
 // do so themselves; the large ones mark such blocks (common.hpp), and a second
-// launch computes the FP32 tiles that hold a mark, which takes 3 to 4 us where it
-// finds none.  1024 x 10000 x 1000: 117 us dense, 189 with 5 nonzeros in each row
+// launch computes the FP32 tiles that hold a mark, which takes 3 to 5 us where it
+// finds none.  1024 x 10000 x 1000: 113 us dense, 189 with 5 nonzeros in each row
 // of P, 280 with a NaN in every sum, on the FP32 tiles 180; 64 x 2000 x 20000: 90,
 // 150, 232 and 770.
 //
@@ -27,10 +27,10 @@
 // SIMD work in turns (an s_barrier per half step): while one issues its 120
 // MFMAs from registers, converting its share of a later slab between them,
 // the other writes converted parts to LDS and reads its next fragments.
-// Bound: the matrix cores, at the clock that the chip's power allows (1.9
-// GHz here: at full rate on random operands they settle there whatever feeds
-// them).  1024 x 10000 x 1000: 117 us with the second launch (FP32 MFMA 180 us);
-// of that 7 us go to the separate small sums; without the turns (one barrier per
+// Bound: the matrix cores and the vector ALUs that feed them, at the clock that the
+// chip's power allows (1024 x 10000 x 1000: busy 59% and 55% of the CUs' cycles at
+// 2.06 GHz, 86% of the CUs holding a tile).  There 113 us with the second launch
+// (FP32 MFMA 180 us); of that 7 us go to the separate small sums; without the turns (one barrier per
 // slab) 112 us where the loop as of then took 100, with 32 x 32 MFMAs 119-123.
 //
 // split_ks_kernel, small tiles (16 FM x 16 FN) of which the waves of a
@@ -39,7 +39,7 @@
 // fragment order and multiplies, with no barrier in the loop; the partial
 // tiles are summed in wave order at the end.  Bound: the conversions (7 vector
 // instructions per operand element; one of them finds thin rows, 2 to 12% of the
-// time).  Used where large tiles leave CUs idle: 1024 x 1000 x 10000 137 us (FP32
+// time; vector ALUs busy 68% of the CUs' cycles, matrix cores 46%).  Used where large tiles leave CUs idle: 1024 x 1000 x 10000 135 us (FP32
 // MFMA 401 us), 64 x 2000 x 20000 90 us (770 us), 16 x 300 x 1500 11 us (55 us).
 #include <algorithm>
 #include <cmath>

@@ -10,10 +10,12 @@
 // formed term by term in the order of the 32x32x2 MFMAs of gemm_nt_kernel:
 // the same bits as its tiles, whatever the tile.
 //
-// Bound: the chain of dependent MFMAs (32 cycles per 4 K) once enough slabs
-// are in flight.  gemm_nt_kernel keeps one slab of a workgroup in flight and
-// pays the memory latency, about 2 us, per slab: 8 requests of 16 x 300 x
-// 1500 took 47 us per launch there.
+// Bound: latency.  A 16 x 16 tile takes 0.38 us a slab, where its chain of eight
+// dependent MFMAs takes 0.11: a slab is written to LDS and read back before its
+// first MFMA, and half of the LDS cycles are bank conflicts (8 requests of 16 x 300
+// x 1500: matrix cores busy 15% of the CUs' cycles, LDS 43%).  gemm_nt_kernel keeps
+// one slab of a workgroup in flight and pays the memory latency, about 2 us, per
+// slab: those requests took 47 us per launch there, 14 here.
 #include <algorithm>
 
 #include "common.hpp"
