@@ -30,8 +30,9 @@
 // Bound: the matrix cores and the vector ALUs that feed them, at the clock that the
 // chip's power allows (1024 x 10000 x 1000: busy 59% and 55% of the CUs' cycles at
 // 2.06 GHz, 86% of the CUs holding a tile).  There 113 us with the second launch
-// (FP32 MFMA 180 us); of that 7 us go to the separate small sums; without the turns (one barrier per
-// slab) 112 us where the loop as of then took 100, with 32 x 32 MFMAs 119-123.
+// (FP32 MFMA 180 us); of that 7 us go to the separate small sums; without the turns
+// (one barrier per slab) 112 us where the loop as of then took 100, with 32 x 32
+// MFMAs 119-123.
 //
 // split_ks_kernel, small tiles (16 FM x 16 FN) of which the waves of a
 // workgroup share K: wave w takes the slabs w, w + waves, ..., loads them
@@ -39,8 +40,9 @@
 // fragment order and multiplies, with no barrier in the loop; the partial
 // tiles are summed in wave order at the end.  Bound: the conversions (7 vector
 // instructions per operand element; one of them finds thin rows, 2 to 12% of the
-// time; vector ALUs busy 68% of the CUs' cycles, matrix cores 46%).  Used where large tiles leave CUs idle: 1024 x 1000 x 10000 135 us (FP32
-// MFMA 401 us), 64 x 2000 x 20000 90 us (770 us), 16 x 300 x 1500 11 us (55 us).
+// time; vector ALUs busy 68% of the CUs' cycles, matrix cores 46%).  Used where
+// large tiles leave CUs idle: 1024 x 1000 x 10000 135 us (FP32 MFMA 401 us), 64 x
+// 2000 x 20000 90 us (770 us), 16 x 300 x 1500 11 us (55 us).
 #include <algorithm>
 #include <cmath>
 
@@ -159,10 +161,11 @@ __device__ __forceinline__ void lds_barrier() {
 }
 
 // From the first slabs, `seen` counts a row in thin[] and `pad` in each that lie
-// past K: whether the tile is to go to the FP32 tiles at once, because a row has
-// most of its quads thin (beyond what a fit row would show by chance; P with 5
-// nonzeros a row, 1024 x 10000 x 1000: 189 us, 278 when that shows at the end).  Rows that have shown nothing are looked through in
-// memory: rows of zeros are fit (up to 64 of them; rows with a nonzero are not).
+// past K: whether the tile is to go to the FP32 instructions at once, because a row
+// has most of its quads thin, beyond what a fit row would show by chance (P with 5
+// nonzeros a row, 1024 x 10000 x 1000: 189 us; 278 when that shows at the end).
+// Rows that have shown nothing are looked through in memory: rows of zeros are fit
+// (up to 64 of them), rows with a nonzero are not.
 // All threads call it, behind a barrier, and get the same answer.
 template <int ROWS>
 __device__ __forceinline__ bool unfit_start(Fitness<ROWS>& f, int rows_p, int seen, int pad,
