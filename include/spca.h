@@ -381,7 +381,8 @@ int spca_gemm_nt_bf16_shape(void* stream, const uint16_t* P, int64_t ldp,
  * 128x128, 128x160, 128x96, 128x64, 64x128, 32x128, 64x256, 256x128, 256x256
  * by 2x2, 2x4 and 4x2 waves, 64x128 with two slabs in flight), 32 to 37
  * one-wave tiles (64x32, 32x64, 32x32, 64x16, 16x32, 16x16; the same bits),
- * 64 to 71 tiles on BF16 parts (one split, K >= 192, ldp, ldq <= 2^21).  With splits > 1, C must hold splits x M rows:
+ * 64 to 71 tiles on BF16 parts (one split, K >= 192, ldp, ldq <= 2^21).  With
+ * splits > 1, C must hold splits x M rows:
  * split s writes its partial product (K slabs s*ceil(K/32/splits) onward)
  * at C + s * M * ldc, and the product is the sum of the partials.       */
 int spca_gemm_nt_f32_shape(void* stream, const float* P, int64_t ldp,
@@ -399,7 +400,8 @@ int spca_gemm_nt_f32_shape(void* stream, const float* P, int64_t ldp,
  * (spca_gemm_nt_f32_plan and the solves) use an entry of their bucket
  * before the cost model.  Shapes are those of spca_gemm_nt_f32_shape (0 to
  * 11 for elem_bytes 2); 64 to 71, the tiles on BF16 parts, hold for
- * spca_gemm_nt_f32 alone: solves stay on FP32 tiles.  Host-only: no device is touched.                                */
+ * spca_gemm_nt_f32 alone: solves stay on FP32 tiles.  Host-only: no device
+ * is touched.                                                              */
 int spca_tune_table_export(char* buf, size_t cap, size_t* len);
 int spca_tune_table_import(const char* text);
 int spca_tune_table_clear(void);
@@ -433,7 +435,8 @@ int spca_x_update(void* stream, int formulation, const float* V, int64_t ldv,
  * neither allocates, frees nor synchronizes: it enqueues kernels on the
  * stream and returns.  SPCA_EINVAL (nothing launched) when r rows of
  * length p need more scratch than that (T_s of a large s, or X overlapping
- * V: about 9.5 KB per row at p = 200000; split the rows into batches).  Every call on one device shares that
+ * V: about 9.5 KB per row at p = 200000; split the rows into batches).
+ * Every call on one device shares that
  * device's array: calls that overlap in time on one device (different
  * streams, or host threads) race and must be serialized by the caller.
  * The call clears what must start at zero itself.  The first call on a
